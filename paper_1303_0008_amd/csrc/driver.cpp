@@ -951,6 +951,23 @@ vmg_status vmg_levels_create(vmg_levels** out, const vmg_grid* grids, const vmg_
     return VMG_OK;
 }
 
+static ParentFill make_fill(const double* parent, const int32_t np[3], double H, const vmg_grid& g,
+                            const int32_t* origin, double* out, bool ghosts) {
+    ParentFill f;
+    f.parent = parent;
+    f.out = out;
+    f.H = H;
+    f.h = g.h;
+    for (int d = 0; d < 3; ++d) {
+        f.np[d] = np[d];
+        f.n[d] = g.n[d];
+        f.o[d] = origin[d];
+    }
+    f.ghosts = ghosts ? 1 : 0;
+    f.count = 0;
+    return f;
+}
+
 vmg_status vmg_levels_solve(vmg_levels* L, const double* delta, double* ghost, double* phi, vmg_result* out) {
     g_err.clear();
     if (!L || !delta || !phi || !out) return fail(VMG_EINVAL, "null argument");
@@ -958,16 +975,17 @@ vmg_status vmg_levels_solve(vmg_levels* L, const double* delta, double* ghost, d
     for (size_t i = 0; i < L->grids.size(); ++i) std::memset(&out[i], 0, sizeof(vmg_result));   // unsolved levels stay 0
     for (size_t d = 0; d < L->plans.size(); ++d) {
         const std::vector<int>& idx = L->members[d];
-        if (d > 0)
+        if (d > 0) {
+            ParentFills fills;
             for (int i : idx) {
                 const vmg_grid& g = L->grids[i];
                 const vmg_grid& P = L->grids[L->nest[i].parent];
-                const int* o = L->nest[i].origin;
-                CKH(launch_ghost_fill(phi + P.offset, P.n[0], P.n[1], P.n[2], P.h, g.n[0], g.n[1], g.n[2], g.h, o[0],
-                                      o[1], o[2], ghost + g.ghost_offset, L->stream));
-                CKH(launch_interior_fill(phi + P.offset, P.n[0], P.n[1], P.n[2], P.h, g.n[0], g.n[1], g.n[2], g.h,
-                                         o[0], o[1], o[2], phi + g.offset, L->stream));
+                const double* parent = phi + P.offset;
+                CKH(fills_add(fills, make_fill(parent, P.n, P.h, g, L->nest[i].origin, ghost + g.ghost_offset, true), L->stream));
+                CKH(fills_add(fills, make_fill(parent, P.n, P.h, g, L->nest[i].origin, phi + g.offset, false), L->stream));
             }
+            CKH(fills_launch(fills, L->stream));
+        }
         std::vector<vmg_result> res(idx.size());
         const vmg_status st = vmg_solve(L->plans[d], delta, d > 0 ? ghost : nullptr, nullptr, phi, res.data());
         for (size_t k = 0; k < idx.size(); ++k) out[idx[k]] = res[k];
@@ -1045,14 +1063,14 @@ vmg_status vmg_fill_ghosts(const double* parent, const int32_t np[3], double par
     if (!parent || !np || !grids || !origins || !ghost || n_grids < 1)
         return fail(VMG_EINVAL, "null argument");
     if (np[0] < 1 || np[1] < 1 || np[2] < 1 || !(parent_h > 0.0)) return fail(VMG_EINVAL, "bad parent grid");
+    ParentFills fills;
     for (int i = 0; i < n_grids; ++i) {
         const vmg_grid& g = grids[i];
         if (g.bc != VMG_DIRICHLET || g.n[0] < 1 || g.n[1] < 1 || g.n[2] < 1 || !(g.h > 0.0))
             return fail(VMG_EINVAL, "ghost fill needs Dirichlet grids with n >= 1 and h > 0");
-        CKH(launch_ghost_fill(parent, np[0], np[1], np[2], parent_h, g.n[0], g.n[1], g.n[2], g.h,
-                              origins[3 * i], origins[3 * i + 1], origins[3 * i + 2], ghost + g.ghost_offset,
-                              stream));
+        CKH(fills_add(fills, make_fill(parent, np, parent_h, g, origins + 3 * i, ghost + g.ghost_offset, true), stream));
     }
+    CKH(fills_launch(fills, stream));
     return VMG_OK;
 }
 
@@ -1061,13 +1079,14 @@ vmg_status vmg_fill_interior(const double* parent, const int32_t np[3], double p
     g_err.clear();
     if (!parent || !np || !grids || !origins || !phi || n_grids < 1) return fail(VMG_EINVAL, "null argument");
     if (np[0] < 1 || np[1] < 1 || np[2] < 1 || !(parent_h > 0.0)) return fail(VMG_EINVAL, "bad parent grid");
+    ParentFills fills;
     for (int i = 0; i < n_grids; ++i) {
         const vmg_grid& g = grids[i];
         if (g.n[0] < 1 || g.n[1] < 1 || g.n[2] < 1 || !(g.h > 0.0) || g.offset < 0)
             return fail(VMG_EINVAL, "interior fill needs grids with n >= 1, h > 0 and offset >= 0");
-        CKH(launch_interior_fill(parent, np[0], np[1], np[2], parent_h, g.n[0], g.n[1], g.n[2], g.h,
-                                 origins[3 * i], origins[3 * i + 1], origins[3 * i + 2], phi + g.offset, stream));
+        CKH(fills_add(fills, make_fill(parent, np, parent_h, g, origins + 3 * i, phi + g.offset, false), stream));
     }
+    CKH(fills_launch(fills, stream));
     return VMG_OK;
 }
 

@@ -207,15 +207,34 @@ hipError_t launch_gauge(const Geom& g, double* phi, const NormOut* no, hipStream
 hipError_t launch_fill(double* p, int64_t n, double v, hipStream_t s);
 hipError_t launch_check_finite(const double* p, int64_t n, double* partials, int* nblocks_out,
                                hipStream_t s);
-hipError_t launch_ghost_fill(const double* parent, int np0, int np1, int np2, double H,
-                             int n0, int n1, int n2, double h, int o0, int o1, int o2,
-                             double* ghost, hipStream_t s);
+// Ghost shell (compact order) or interior of one refinement, interpolated
+// trilinearly from a periodic parent of np cells of size H.
+struct ParentFill {
+    const double* parent;
+    double* out;
+    double H, h;
+    int np[3], n[3], o[3];   // parent cells, refinement cells, its origin in its own cells
+    int ghosts;              // 1: ghost shell, 0: interior
+    int64_t count;           // values written (set by fills_add)
+};
+// The fills of one launch travel as its arguments (no device table to keep or
+// to wait for); 40 of them fill the 4 KB of a kernel's argument segment.
+constexpr int FILL_MAX = 40;
+struct ParentFills {
+    int n = 0;
+    int first[FILL_MAX + 1];   // first block of each fill, and the end
+    ParentFill d[FILL_MAX];
+};
+static_assert(sizeof(ParentFills) <= 4096, "kernel arguments");
+static_assert(FILL_MAX <= 64, "the block search takes six steps");
+// Queue a fill (launches the queued ones when the table is full) / launch what
+// is queued.
+hipError_t fills_add(ParentFills& f, const ParentFill& fill, hipStream_t s);
+hipError_t fills_launch(ParentFills& f, hipStream_t s);
 // Psi = phi_N + phi/2 (psi may be null) and g = -grad Psi (gx, gy, gz blocks of N), periodic
 hipError_t launch_total_force(int n0, int n1, int n2, double h, const double* phin, const double* phi, double* psi,
                               double* g, hipStream_t s);
 int64_t total_force_blocks(int n0, int n1, int n2);
-hipError_t launch_interior_fill(const double* parent, int np0, int np1, int np2, double H, int n0, int n1, int n2,
-                                double h, int o0, int o1, int o2, double* phi, hipStream_t s);
 // Particles (np x 3, box units) -> delta on a periodic n0 x n1 x n2 grid;
 // scheme 1 cloud in cell, 2 triangular-shaped cloud (kernels_assign.hip).
 // work: mass_assign_workspace(np, n0, n1, n2) bytes, 256-byte aligned.
