@@ -60,9 +60,16 @@ hipError_t batch_set_level_cfg(Plan* P, int l, SmoothCfg cfg) {
     return upload(P, &B.d_sitems, items);
 }
 
-// Default work lists: the finest level uses the plan's schedule; coarser levels
-// shorten the z chunk, then the tile height, until the level has at least
-// MIN_TILED_BLOCKS items (or the shortest schedule).
+// Default schedules: bricks on the levels below the finest (they also refresh the
+// ghosts, a launch less per sweep) and on a finest level of few cells in all;
+// else marches of the finest level whose z chunk leaves enough work items.
+// V(2,2) cycles timed over batches of 1 to 128 grids of 16^3 to 128^3: mixed,
+// 8 x 32^3 / 48 ragged (1.6 M cells) / 96 of 16^3-64^3 (3.3 M): 506 / 1080 /
+// 1789 us so, 734 / 1245 / 2083 us with 64 x 8 x 16 tiles shortened on coarse
+// levels; FP64 267 / 589 / 986 us against 358 / 640 / 1062 us.  Bricks on the
+// finest level of the last two take 1240 and 2490 us (FP64 651 and 1192 us): the
+// rings' recomputation outweighs the march's fill once the chip is full.
+constexpr int64_t BATCH_BRICK_CELLS = (int64_t)1 << 19;
 hipError_t batch_build_smooth_items(Plan* P) {
     for (size_t l = 0; l < P->blev.size(); ++l) {
         const BatchLevel& B = P->blev[l];
@@ -75,11 +82,13 @@ hipError_t batch_build_smooth_items(Plan* P) {
             }
             return n;
         };
-        SmoothCfg cfg = P->cfg;
-        if (l > 0) {
-            while (cfg.zc > 2 && count(cfg) < MIN_TILED_BLOCKS) cfg.zc >>= 1;
-            if (count(cfg) < MIN_TILED_BLOCKS && cfg.ty > 4) cfg.ty = 4;
+        SmoothCfg cfg{8, 8, PIPE_BRICK};
+        if (l == 0 && B.cells_A > BATCH_BRICK_CELLS) {
+            if (P->mixed) cfg = SmoothCfg{16, count(SmoothCfg{16, 16, 1}) >= 1024 ? 16 : 8, 1};
+            else if (count(SmoothCfg{16, 16, 1}) >= 1024) cfg = SmoothCfg{16, 16, 1};
+            else cfg = SmoothCfg{8, count(SmoothCfg{8, 16, 1}) >= 512 ? 16 : 8, 1};
         }
+        if (l == 0) P->cfg = cfg.pipe == PIPE_BRICK ? SmoothCfg{8, 8, 1} : cfg;
         CKE(batch_set_level_cfg(P, (int)l, cfg));
     }
     return hipSuccess;

@@ -94,9 +94,9 @@ vmg_status build_plan(Plan* P, const vmg_grid* grids, int n_grids, const vmg_par
     if (P->nu1 == 0 && P->nu2 == 0) { P->nu1 = 2; P->nu2 = 2; }
     P->inner = p->inner_cycles > 0 ? p->inner_cycles : 2;
     P->ncoarse = 8;
-    P->cfg.ty = 8;
-    P->cfg.zc = 16;
     P->periodic = grids[0].bc == VMG_PERIODIC;
+    if (P->periodic) P->cfg = default_march(grids[0].n[0], grids[0].n[1], grids[0].n[2]);
+    else P->cfg = SmoothCfg{8, 16, 1};
     int64_t max_cells = 1;
     for (int gi = 0; gi < n_grids; ++gi) {
         const vmg_grid& d = grids[gi];
@@ -166,6 +166,8 @@ vmg_status build_plan(Plan* P, const vmg_grid* grids, int n_grids, const vmg_par
         if ((st = autotune(P)) != VMG_OK) return st;
         CKH(hipStreamSynchronize(stream));
     }
+    // (after the tuner, which times marches on the finest level)
+    P->small_finest = P->periodic && P->grids[0].lev.size() > 1 && P->grids[0].lev[0].g.ncell <= BRICK_CELLS;
     return VMG_OK;
 }
 
@@ -273,12 +275,14 @@ bool fold_prolong_here(const Plan* P, const Geom& g, const Geom& gc, const Smoot
     return can_fold_prolong(g, gc, zc) && fold_prolong_pays(g, zc);
 }
 
-// The finest level runs the plan's schedule; a coarser level its tuned one, else
-// the plan's schedule shortened by level_cfg.
+// The finest level runs the plan's schedule (bricks if it is small and no
+// schedule was installed on it); a coarser level its tuned one, else the default
+// rule, or the plan's installed schedule shortened by level_cfg.
 SmoothCfg level_schedule(const Plan* P, int l, const Geom& g) {
-    if (l == 0) return P->cfg;
+    if (l == 0) return P->small_finest && !P->user_cfg ? SmoothCfg{8, 8, PIPE_BRICK} : P->cfg;
     if ((int)P->lcfg.size() > l && P->lcfg[l].ty > 0) return P->lcfg[l];
-    return level_cfg(g.n0, g.n1, g.n2, P->cfg);
+    if (P->user_cfg) return level_cfg(g.n0, g.n1, g.n2, P->cfg);
+    return g.ncell <= BRICK_CELLS ? SmoothCfg{8, 8, PIPE_BRICK} : default_march(g.n0, g.n1, g.n2);
 }
 
 // First level (below the finest) at which the periodic coarse tail takes over,
@@ -360,7 +364,7 @@ hipError_t post_smooth(Plan* P, GridState& G, int l, int nu2) {
     const ProlongIn pro{C.g, C.phi[C.cur], C.phiold};
     if (!s0 && (e = launch_prolong(L.g, C.g, L.phi[L.cur], C.phi[C.cur], C.phiold, P->stream)) != hipSuccess)
         return e;
-    if (l > 0) return smooth_level_n(P, G, l, nu2, s0 ? &pro : nullptr);
+    if (l > 0 || !P->time_sweeps) return smooth_level_n(P, G, l, nu2, s0 ? &pro : nullptr);
     if (s0 && (e = smooth_level(P, G, l, &pro)) != hipSuccess) return e;
     if ((e = sweep_mark(P, true, nu2 - s0)) != hipSuccess) return e;
     if ((e = smooth_level_n(P, G, l, nu2 - s0)) != hipSuccess) return e;
@@ -1203,7 +1207,10 @@ vmg_status vmg_plan_set_schedule(vmg_plan* plan, int32_t level, int32_t tile_y, 
         return fail(VMG_EINVAL, "pipe 2 (bricks) runs on the coarser levels of a periodic plan or on any level of "
                                 "a Dirichlet batch");
     const SmoothCfg c{tile_y, z_chunk, pipe};
-    if (level == 0) P->cfg = c;
+    if (level == 0) {
+        P->cfg = c;
+        P->user_cfg = true;
+    }
     if (P->batched) {
         CKH(batch_set_level_cfg(P, level, c));
     } else if (level > 0) {
@@ -1220,7 +1227,9 @@ vmg_status vmg_plan_schedule(const vmg_plan* plan, int32_t level, int32_t* tile_
     const Plan* P = reinterpret_cast<const Plan*>(plan);
     if (level < 0 || level >= swept_level_count(P))
         return fail(VMG_EINVAL, "level " + std::to_string(level) + " has no fused sweep in this plan");
-    const SmoothCfg c = P->batched ? P->blev[level].cfg : level_schedule(P, level, P->grids[0].lev[level].g);
+    // (the finest periodic level reports its march, the only schedule it accepts)
+    const SmoothCfg c = P->batched ? P->blev[level].cfg
+                                   : (level == 0 ? P->cfg : level_schedule(P, level, P->grids[0].lev[level].g));
     if (tile_y) *tile_y = c.ty;
     if (z_chunk) *z_chunk = c.zc;
     if (pipe) *pipe = c.pipe;

@@ -157,18 +157,18 @@ __global__ void __launch_bounds__(sweep_threads(TY), sweep_waves(TY, DEFER, PRO)
 // Dirichlet grid of a batch at one level in one launch.  `proto` carries the
 // pooled level buffers and coefficients; geoms[w.x] locates grid w.x in them.
 
-// S sweeps (1 or 2) of a small periodic level with a FAS source, one BB^3 brick
-// per block (brick_sweeps); PRO adds the prolonged coarse correction first.  The
+// S sweeps (1 or 2) of a small periodic level, with or without a source, one BB^3
+// brick per block (brick_sweeps); PRO adds the prolonged coarse correction first.  The
 // two-sweep prolonging variant keeps one block per CU: at two its registers
 // spill (measured slower).
-template <int S, bool PRO>
+template <int S, bool PRO, bool HAS_F>
 __global__ void __launch_bounds__(BRICK_THREADS, (S == 2 && PRO) ? 2 : BRICK_WAVES) k_smooth_brick(SmoothArgs a) {
     const int nbx = (a.g.n0 + BB - 1) / BB, nby = (a.g.n1 + BB - 1) / BB;
     int b = xcd_remap(blockIdx.x, gridDim.x);
     const int bx = b % nbx;
     b /= nbx;
     const int by = b % nby, bz = b / nby;
-    const SmoothK<true> k(a, a.g, true);
+    const SmoothK<HAS_F> k(a, a.g, true);
     brick_sweeps<S, PRO>(k, a.g, bx * BB, by * BB, bz * BB);
 }
 
@@ -1248,6 +1248,14 @@ static hipError_t smooth_launch(const SmoothArgs& a, bool defer, hipStream_t s) 
     return hipGetLastError();
 }
 
+template <int S, bool HAS_F>
+static hipError_t brick_launch(const SmoothArgs& a, hipStream_t s) {
+    const dim3 nb(((a.g.n0 + BB - 1) / BB) * ((a.g.n1 + BB - 1) / BB) * ((a.g.n2 + BB - 1) / BB));
+    if (a.uc) hipLaunchKernelGGL((k_smooth_brick<S, true, HAS_F>), nb, dim3(BRICK_THREADS), 0, s, a);
+    else hipLaunchKernelGGL((k_smooth_brick<S, false, HAS_F>), nb, dim3(BRICK_THREADS), 0, s, a);
+    return hipGetLastError();
+}
+
 hipError_t launch_smooth(const Geom& g, const Coef& c, const double* pin, double* pout,
                          const double* delta, const double* f, const LevelScalars* sc,
                          SmoothCfg cfg, hipStream_t s, const ProlongIn* pro, int nsweeps) {
@@ -1255,23 +1263,16 @@ hipError_t launch_smooth(const Geom& g, const Coef& c, const double* pin, double
     std::memset(&a, 0, sizeof(a));
     a.g = g; a.c = c; a.pin = pin; a.pout = pout; a.delta = delta; a.f = f; a.sc = sc;
     if (cfg.pipe == PIPE_BRICK) {
-        // periodic coarse levels (with their FAS source), one or two sweeps
-        if (g.dir || !f || nsweeps < 1 || nsweeps > 2) return hipErrorInvalidValue;
+        // periodic levels, one or two sweeps
+        if (g.dir || nsweeps < 1 || nsweeps > 2) return hipErrorInvalidValue;
         if (pro) {
             if (!can_fold_prolong(g, pro->gc, 2)) return hipErrorInvalidValue;
             a.gc = pro->gc;
             a.uc = pro->uc;
             a.oc = pro->oc;
         }
-        const dim3 nb(((g.n0 + BB - 1) / BB) * ((g.n1 + BB - 1) / BB) * ((g.n2 + BB - 1) / BB));
-        if (nsweeps == 2) {
-            if (pro) hipLaunchKernelGGL((k_smooth_brick<2, true>), nb, dim3(BRICK_THREADS), 0, s, a);
-            else hipLaunchKernelGGL((k_smooth_brick<2, false>), nb, dim3(BRICK_THREADS), 0, s, a);
-        } else {
-            if (pro) hipLaunchKernelGGL((k_smooth_brick<1, true>), nb, dim3(BRICK_THREADS), 0, s, a);
-            else hipLaunchKernelGGL((k_smooth_brick<1, false>), nb, dim3(BRICK_THREADS), 0, s, a);
-        }
-        return hipGetLastError();
+        if (f) return nsweeps == 2 ? brick_launch<2, true>(a, s) : brick_launch<1, true>(a, s);
+        return nsweeps == 2 ? brick_launch<2, false>(a, s) : brick_launch<1, false>(a, s);
     }
     if (nsweeps != 1) return hipErrorInvalidValue;
     a.zc = cfg.zc > 0 ? cfg.zc : 16;

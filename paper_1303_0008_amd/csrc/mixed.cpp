@@ -91,7 +91,7 @@ hipError_t post_smooth_corr(Plan* P, GridState& G, int l, int nu2) {
     const ProlongInF pro{C.g, C.e[C.ecur], C.eold};
     if (!s0 && (e = launch_prolong_corr(L.g, C.g, L.e[L.ecur], C.e[C.ecur], C.eold, P->stream)) != hipSuccess)
         return e;
-    if (l > 0) return smooth_corr_level_n(P, G, l, nu2, false, s0 ? &pro : nullptr);
+    if (l > 0 || !P->time_sweeps) return smooth_corr_level_n(P, G, l, nu2, false, s0 ? &pro : nullptr);
     if (s0 && (e = smooth_corr_level(P, G, l, false, &pro)) != hipSuccess) return e;
     if ((e = sweep_mark(P, true, nu2 - s0)) != hipSuccess) return e;
     if ((e = smooth_corr_level_n(P, G, l, nu2 - s0, false, nullptr)) != hipSuccess) return e;
@@ -147,7 +147,7 @@ static hipError_t inner_vcycle(Plan* P, GridState& G, int l, bool zero_e, bool f
     // the sweep that reads no correction (zero_e) is another kernel: it is not timed
     const int nu1 = pre_sweeps(P, l);
     const int t1 = zero_e ? nu1 - 1 : nu1;
-    if (l > 0) {
+    if (l > 0 || !P->time_sweeps) {
         if ((e = smooth_corr_level_n(P, G, l, nu1, zero_e)) != hipSuccess) return e;
     } else {
         for (int s = 0; s < nu1; ++s) {

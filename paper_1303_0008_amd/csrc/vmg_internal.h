@@ -103,6 +103,27 @@ inline SmoothCfg level_cfg(int n0, int n1, int n2, SmoothCfg c) {
     return c;
 }
 
+// Schedules of plans that neither tuned nor installed one.  Timed as whole
+// V(2,2) cycles over 32^3..384^3 cubes and ragged grids, both precisions:
+// * periodic levels of at most BRICK_CELLS cells run bricks, the finest one
+//   included: the march's pipeline fill dominates there (FP64 cycle of a 32^3 /
+//   48^3 domain grid: 155 / 184 us on bricks, 162 / 197 us on the best march,
+//   251 / 278 us on 64 x 8 tiles of 16 planes; 64^3: 214, 210, 293 us; at 80^3
+//   the march is ahead, 278 against 292 us);
+// * larger ones march 16-row tiles with the longest z chunk that still gives
+//   the 256 CUs one and a half blocks each, or a whole number of blocks each
+//   (LDS holds one 16-row block per CU): FP64 cycles of 96^3 / 160^3 / 256^3 take
+//   304 / 543 / 939 us so, 347 / 555 / 1051 us on 64 x 8 x 16 tiles everywhere.
+constexpr int64_t BRICK_CELLS = (int64_t)1 << 18;
+inline SmoothCfg default_march(int n0, int n1, int n2) {
+    const int64_t xy = (int64_t)((n0 + TX - 1) / TX) * ((n1 + 15) / 16);
+    for (int zc = 64; zc > 4; zc >>= 1) {
+        const int64_t blocks = xy * ((n2 + zc - 1) / zc);
+        if (blocks >= 384 || blocks % 256 == 0) return SmoothCfg{16, zc, 1};
+    }
+    return SmoothCfg{16, 4, 1};
+}
+
 // ---- coarse tail (kernels_tail.hip) ----------------------------------------
 // Periodic levels with at most TAIL_CELLS cells, down to the coarsest, in one
 // single-workgroup launch (all arrays in LDS).

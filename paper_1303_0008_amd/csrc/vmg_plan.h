@@ -76,7 +76,10 @@ struct Plan {
     hipStream_t stream = nullptr;
     hipStream_t own_stream = nullptr;      // created when the caller passes stream 0
     SmoothCfg cfg;                         // finest-level schedule of the fused sweep
-    std::vector<SmoothCfg> lcfg;           // tuned schedules of levels >= 1 (empty: level_cfg rule)
+    bool user_cfg = false;                 // cfg was installed by vmg_plan_set_schedule
+    bool small_finest = false;             // periodic finest level of <= BRICK_CELLS cells: runs bricks
+                                           // unless a schedule was installed on it
+    std::vector<SmoothCfg> lcfg;           // tuned schedules of levels >= 1 (empty: level_schedule's rule)
     int nu1 = 2, nu2 = 2, ncoarse = 40;
     int inner = 2;                         // mixed: FP32 inner V-cycles per outer iteration
     int nu1c = 0, nu2c = 0;                // sweeps below the finest level (0, 0: nu1, nu2)
