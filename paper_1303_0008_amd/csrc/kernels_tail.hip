@@ -1,7 +1,9 @@
 // Coarse tail of a periodic V-cycle (Sec. III.C): every level with at most
-// TAIL_CELLS cells, down to the coarsest, handled by one workgroup with all of
-// those levels' arrays in LDS.  On these grids a separate launch per step costs
-// more than the step itself; here the whole sub-cycle is one launch.
+// TAIL_CELLS cells, down to the coarsest, in one single-workgroup launch with the
+// state in LDS.  On these grids a separate launch per step costs more than the
+// step itself.  A periodic level coarsens only while every axis keeps 4 cells,
+// so the tail is either 8^3 and 4^3 (k_tail8) or one coarsest level of any shape
+// (k_tail1).
 //
 // The arithmetic is the multi-kernel V-cycle's, step for step:
 //   * fused red-black sweep with snapshot semantics (red from the old state,
@@ -9,10 +11,20 @@
 //     registers, then written after a barrier;
 //   * residual d = L(phi) - f + cbar, 8-child averages of phi and d, then
 //     cbar <- (sum f + sum Q) / N for the level's later sweeps;
-//   * coarse rhs f^H = L^H(R phi) - R d and cbar^H = (sum f^H + sum Q^H) / N^H;
+//   * coarse rhs f^H = L^H(R phi) - R d;
 //   * coarsest level: cbar from the current sum of Q before every sweep;
 //   * cell-centred trilinear prolongation of phi^H - R phi (periodic wrap).
 // Reductions run in a fixed order, so results are bitwise reproducible.
+//
+// What bounds it: a serial chain of some 20 colour phases on one CU.  Each
+// thread therefore owns its cells for the whole launch (values, right-hand side
+// and per-cell constants in registers, neighbour offsets from compile-time
+// sizes), so a phase is 18 LDS reads, one root and one LDS write; the 8^3 level
+// runs on four waves (one cell of each colour per thread), and 4^3 on one wave,
+// whose phases need no barrier; sums across a wave use DPP adds.
+// 8^3 over 4^3 with V(2,2) and 4 (8) coarsest sweeps: FP64 8.4 (10.9) us, FP32
+// correction 9.2 us; with 512 threads, run-time sizes, a barrier per step on both
+// levels and values re-read from LDS it took 23.3 (32.8) and 26.8 us.
 #include <hip/hip_runtime.h>
 
 #include "device_common.h"
@@ -21,33 +33,41 @@ namespace vmg {
 
 namespace {
 
-constexpr int TAIL_NT = 512;
-constexpr int TAIL_POOL = 3 * TAIL_CELLS + 4 * (TAIL_CELLS / 8 + TAIL_CELLS / 64 + TAIL_CELLS / 512 + 1);
-
-__device__ __forceinline__ int tw(int i, int n) { return i < 0 ? i + n : (i >= n ? i - n : i); }
-
-struct TLev {
-    int n0, n1, n2, N;
-    double h2, inv_h2, inv_h4;
-    double *phi, *old, *f, *del;   // LDS, x fastest, unpadded
-};
-
-__device__ __forceinline__ void tail_decode(const TLev& L, int e, int& i, int& j, int& k) {
-    i = e % L.n0;
-    const int r = e / L.n0;
-    j = r % L.n1;
-    k = r / L.n1;
+// Sum over the wave, in every lane (row shifts, then row broadcasts; lane 63
+// holds the total).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_add(double v) {
+    const long long b = __builtin_bit_cast(long long, v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, ROWS, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, ROWS, 0xf, true);
+    return v + __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned)lo);
 }
 
-__device__ __forceinline__ int tail_idx(const TLev& L, int i, int j, int k) {
-    return (tw(k, L.n2) * L.n1 + tw(j, L.n1)) * L.n0 + tw(i, L.n0);
+__device__ __forceinline__ double wave_total(double v) {
+    v = dpp_add<0x111, 0xf>(v);   // row_shr:1
+    v = dpp_add<0x112, 0xf>(v);
+    v = dpp_add<0x114, 0xf>(v);
+    v = dpp_add<0x118, 0xf>(v);   // lane 15 of each row: the row's sum
+    v = dpp_add<0x142, 0xa>(v);   // row_bcast:15 into rows 1 and 3
+    v = dpp_add<0x143, 0xc>(v);   // row_bcast:31 into rows 2 and 3
+    const long long b = __builtin_bit_cast(long long, v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)b, 63);
+    const int hi = __builtin_amdgcn_readlane((int)(b >> 32), 63);
+    return __builtin_bit_cast(double, ((long long)hi << 32) | lo);
 }
 
-// Wrapped x offsets, row offsets and plane offsets of a cell and its two
-// neighbours along each axis ([0] = -1, [1] = the cell, [2] = +1): every
-// neighbour index is then a sum of three of them.
+// LDS written by a lane of this wave is read by another after this: the LDS
+// serves a wave's accesses in order, so only the compiler has to keep them so.
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// Offsets of a cell and its two neighbours along each axis ([0] = -1, [1] = the
+// cell, [2] = +1) with periodic wrap: a neighbour's index is the sum of three.
 struct TNbr {
     int x[3], y[3], z[3];
+    __device__ __forceinline__ int centre() const { return z[1] + y[1] + x[1]; }
 };
 
 __device__ __forceinline__ TNbr tail_nbr(int n0, int n1, int n2, int i, int j, int k) {
@@ -66,7 +86,7 @@ __device__ __forceinline__ TNbr tail_nbr(int n0, int n1, int n2, int i, int j, i
 }
 
 template <typename T>
-__device__ __forceinline__ void tail_gather_o(const TNbr& o, const T* u, NbT<T>& v) {
+__device__ __forceinline__ void tail_gather(const TNbr& o, const T* u, NbT<T>& v) {
     auto at = [&](int a, int b, int c) { return u[o.z[c] + o.y[b] + o.x[a]]; };
     v.xm = at(0, 1, 1);   v.xp = at(2, 1, 1);
     v.ym = at(1, 0, 1);   v.yp = at(1, 2, 1);
@@ -76,517 +96,408 @@ __device__ __forceinline__ void tail_gather_o(const TNbr& o, const T* u, NbT<T>&
     v.ypzp = at(1, 2, 2); v.ymzm = at(1, 0, 0); v.ypzm = at(1, 2, 0); v.ymzp = at(1, 0, 2);
 }
 
-template <typename T>
-__device__ __forceinline__ void tail_gather(const TLev& L, const T* u, int i, int j, int k, NbT<T>& v) {
-    tail_gather_o(tail_nbr(L.n0, L.n1, L.n2, i, j, k), u, v);
-}
-
-// Cell q of colour `colour` ((i+j+k) & 1) on an n0 x n1 x n2 grid with n0 even:
-// q runs over the row-pairs' halves, so every thread works on a cell of the colour.
-__device__ __forceinline__ void colour_cell(int n0, int n1, int q, int colour, int& i, int& j, int& k) {
-    const int h = n0 >> 1;
-    const int r = q / h;
-    j = r % n1;
-    k = r / n1;
-    i = 2 * (q - r * h) + ((j + k + colour) & 1);
-}
-
-// Block-wide sums of two values in a fixed order; every thread gets the totals.
-__device__ __forceinline__ void tail_sum2(double a, double b, double& A, double& B, double (*red)[2]) {
-    a = wave_sum(a);
-    b = wave_sum(b);
-    const int w = threadIdx.x >> 6;
-    if ((threadIdx.x & 63) == 0) {
-        red[w][0] = a;
-        red[w][1] = b;
-    }
-    __syncthreads();
-    A = 0.0;
-    B = 0.0;
-    for (int q = 0; q < TAIL_NT / 64; ++q) {
-        A += red[q][0];
-        B += red[q][1];
-    }
-    __syncthreads();
-}
-
-// One red-black sweep of level L: each colour's new values go to the LDS
-// scratch plane tmp first and are copied into phi after a barrier, so every
-// cell of a colour is computed from the same state.
-__device__ void tail_sweep(const TLev& L, double* tmp, const Coef& c, double cb) {
-    const int tid = threadIdx.x;
-    auto update = [&](int i, int j, int k) {
-        const int e = (k * L.n1 + j) * L.n0 + i;
-        Nb v;
-        tail_gather(L, L.phi, i, j, k, v);
-        double S, D;
-        const double Q = nl_root_d(v, L.del[e], c, L.inv_h4, S, D);
-        tmp[e] = kink_relax(L.phi[e], (S - L.h2 * (Q + L.f[e] - cb)) * (1.0 / 6.0), D, kink_k(L.h2));
+// The FP64 problem: per-cell constant delta.
+struct TailK {
+    using T = double;
+    static constexpr bool BASE = false;   // no base state phi~
+    struct Cell {
+        double del;
     };
-    for (int colour = 0; colour < 2; ++colour) {
-        if ((L.n0 & 1) == 0) {
-            for (int q = tid; q < (L.N >> 1); q += TAIL_NT) {
-                int i, j, k;
-                colour_cell(L.n0, L.n1, q, colour, i, j, k);
-                update(i, j, k);
-            }
-            __syncthreads();
-            for (int q = tid; q < (L.N >> 1); q += TAIL_NT) {
-                int i, j, k;
-                colour_cell(L.n0, L.n1, q, colour, i, j, k);
-                const int e = (k * L.n1 + j) * L.n0 + i;
-                L.phi[e] = tmp[e];
-            }
-        } else {
-            for (int e = tid; e < L.N; e += TAIL_NT) {
-                int i, j, k;
-                tail_decode(L, e, i, j, k);
-                if (((i + j + k) & 1) == colour) update(i, j, k);
-            }
-            __syncthreads();
-            for (int e = tid; e < L.N; e += TAIL_NT) {
-                int i, j, k;
-                tail_decode(L, e, i, j, k);
-                if (((i + j + k) & 1) == colour) L.phi[e] = tmp[e];
-            }
-        }
-        __syncthreads();
+    Coef c;
+    double h2, inv_h2, inv_h4;   // of one level
+    float kk;
+    __device__ TailK(const Coef& c_, double h) : c(c_) {
+        h2 = h * h;
+        inv_h2 = 1.0 / h2;
+        inv_h4 = inv_h2 * inv_h2;
+        kk = kink_k(h2);
     }
-}
-
-// Descriptor of tail level l: sizes from the arguments, arrays carved out of
-// the LDS pool in level order (phi, f, delta, and phiold below the top).  Built
-// on the fly so that nothing is indexed by a run-time level in private memory.
-__device__ __forceinline__ TLev tail_level(const TailArgs& a, double* pool, int l) {
-    int off = 0;
-    for (int q = 0; q < l; ++q) off += (q == 0 ? 3 : 4) * a.n[q][0] * a.n[q][1] * a.n[q][2];
-    TLev T;
-    T.n0 = a.n[l][0];
-    T.n1 = a.n[l][1];
-    T.n2 = a.n[l][2];
-    T.N = T.n0 * T.n1 * T.n2;
-    T.h2 = a.h[l] * a.h[l];
-    T.inv_h2 = 1.0 / T.h2;
-    T.inv_h4 = T.inv_h2 * T.inv_h2;
-    T.phi = pool + off;
-    T.f = T.phi + T.N;
-    T.del = T.f + T.N;
-    T.old = l > 0 ? T.del + T.N : nullptr;
-    return T;
-}
-
-}  // namespace
-
-__global__ void __launch_bounds__(TAIL_NT) k_tail(TailArgs a) {
-    __shared__ double pool[TAIL_POOL];
-    __shared__ double tmp[TAIL_CELLS];
-    __shared__ double red[TAIL_NT / 64][2];
-    __shared__ double cbar[TAIL_LEVELS];
-    const int tid = threadIdx.x;
-    const int nl = a.nlev;
-    {
-        const TLev T = tail_level(a, pool, 0);
-        for (int e = tid; e < T.N; e += TAIL_NT) {
-            T.phi[e] = a.phi[e];
-            T.f[e] = a.f ? a.f[e] : 0.0;
-        }
+    // root Q of a cell, its neighbour sum S and discriminant D
+    __device__ double root(const NbT<double>& v, const Cell& k, double& S, double& D) const {
+        return nl_root_d(v, k.del, c, inv_h4, S, D);
     }
-    for (int l = 0; l < nl; ++l) {
-        const TLev T = tail_level(a, pool, l);
-        for (int e = tid; e < T.N; e += TAIL_NT) T.del[e] = a.delta[l][e];
-    }
-    if (tid == 0) cbar[0] = a.sc->cbar;
-    __syncthreads();
-    const int last = nl - 1;
-    // ---- descent ------------------------------------------------------------
-    for (int l = 0; l < last; ++l) {
-        const TLev F = tail_level(a, pool, l);
-        const TLev C = tail_level(a, pool, l + 1);
-        for (int s = 0; s < a.nu1; ++s) tail_sweep(F, tmp, a.c, cbar[l]);
-        // residual of every fine cell into tmp, then the 8-child averages of phi
-        // and d (R d is kept as -R d in f^H); children are summed in a fixed order
-        double sq = 0.0, sf = 0.0;
-        for (int fe = tid; fe < F.N; fe += TAIL_NT) {
-            int i, j, k;
-            tail_decode(F, fe, i, j, k);
-            Nb v;
-            tail_gather(F, F.phi, i, j, k, v);
-            double S;
-            bool gd;
-            const double Q = nl_root(v, F.del[fe], a.c, F.inv_h4, S, gd);
-            tmp[fe] = (S - 6.0 * F.phi[fe]) * F.inv_h2 - Q - F.f[fe] + cbar[l];
-            sq += Q;
-            sf += F.f[fe];
-        }
-        __syncthreads();
-        for (int e = tid; e < C.N; e += TAIL_NT) {
-            int I, J, K;
-            tail_decode(C, e, I, J, K);
-            double sp = 0.0, sd = 0.0;
-#pragma unroll
-            for (int m = 0; m < 8; ++m) {
-                const int fe = ((2 * K + (m >> 2)) * F.n1 + 2 * J + ((m >> 1) & 1)) * F.n0 + 2 * I + (m & 1);
-                sd += tmp[fe];
-                sp += F.phi[fe];
-            }
-            C.phi[e] = 0.125 * sp;
-            C.old[e] = 0.125 * sp;
-            C.f[e] = -0.125 * sd;
-        }
-        double SQ, SF;
-        tail_sum2(sq, sf, SQ, SF, red);   // also orders the restriction before the rhs
-        if (tid == 0) cbar[l] = (SF + SQ) / (double)F.N;
-        // coarse rhs f^H = L^H(R phi) - R d
-        sq = 0.0;
-        sf = 0.0;
-        for (int e = tid; e < C.N; e += TAIL_NT) {
-            int I, J, K;
-            tail_decode(C, e, I, J, K);
-            Nb v;
-            tail_gather(C, C.phi, I, J, K, v);
-            double S;
-            bool gd;
-            const double Q = nl_root(v, C.del[e], a.c, C.inv_h4, S, gd);
-            const double fh = (S - 6.0 * C.phi[e]) * C.inv_h2 - Q + C.f[e];
-            C.f[e] = fh;
-            sq += Q;
-            sf += fh;
-        }
-        tail_sum2(sq, sf, SQ, SF, red);
-        if (tid == 0) cbar[l + 1] = (SF + SQ) / (double)C.N;
-        __syncthreads();
-    }
-    // ---- coarsest level: cbar from the current sum of Q before every sweep ---
-    {
-        const TLev C = tail_level(a, pool, last);
-        double sf = 0.0, dummy = 0.0, SF, D;
-        for (int e = tid; e < C.N; e += TAIL_NT) sf += C.f[e];
-        tail_sum2(sf, dummy, SF, D, red);
-        for (int s = 0; s < a.ncoarse; ++s) {
-            double sq = 0.0, SQ;
-            for (int e = tid; e < C.N; e += TAIL_NT) {
-                int i, j, k;
-                tail_decode(C, e, i, j, k);
-                Nb v;
-                tail_gather(C, C.phi, i, j, k, v);
-                double S;
-                bool gd;
-                sq += nl_root(v, C.del[e], a.c, C.inv_h4, S, gd);
-            }
-            tail_sum2(sq, dummy, SQ, D, red);
-            tail_sweep(C, tmp, a.c, (SF + SQ) / (double)C.N);
-        }
-    }
-    // ---- ascent: prolongation of the correction, post-smoothing -------------
-    for (int l = last - 1; l >= 0; --l) {
-        const TLev F = tail_level(a, pool, l);
-        const TLev C = tail_level(a, pool, l + 1);
-        for (int e = tid; e < F.N; e += TAIL_NT) {
-            int i, j, k;
-            tail_decode(F, e, i, j, k);
-            const int I = i >> 1, J = j >> 1, K = k >> 1;
-            const int si = (i & 1) ? 1 : -1, sj = (j & 1) ? 1 : -1, sk = (k & 1) ? 1 : -1;
-            double acc = 0.0;
-            for (int m = 0; m < 8; ++m) {
-                const int ai = m & 1, aj = (m >> 1) & 1, ak = m >> 2;
-                const double w = (ai ? 0.25 : 0.75) * (aj ? 0.25 : 0.75) * (ak ? 0.25 : 0.75);
-                const int ci = tail_idx(C, I + ai * si, J + aj * sj, K + ak * sk);
-                acc += w * (C.phi[ci] - C.old[ci]);
-            }
-            F.phi[e] += acc;
-        }
-        __syncthreads();
-        for (int s = 0; s < a.nu2; ++s) tail_sweep(F, tmp, a.c, cbar[l]);
-    }
-    {
-        const TLev T = tail_level(a, pool, 0);
-        for (int e = tid; e < T.N; e += TAIL_NT) a.phi[e] = T.phi[e];
-    }
-    if (tid == 0) a.sc->cbar = cbar[0];
-}
-
-// ---------------------------------------------------------------------------
-// Coarse tail of the mixed path's FP32 inner cycle: the same structure for the
-// correction problem  Lap e - dQ(e) = r - cbar_e  (e, r, phi~, t0 per level).
-// Below the tail's top level the base state phi~ is the 8-child average and
-// t0 = +-sqrt|D0| comes from the FP64 discriminant of phi~ and delta, as in the
-// multi-kernel inner cycle.
-// ---------------------------------------------------------------------------
-namespace {
-
-constexpr int CTAIL_POOL = 4 * TAIL_CELLS + 5 * (TAIL_CELLS / 8 + TAIL_CELLS / 64 + TAIL_CELLS / 512 + 1);
-
-struct CLev {
-    int n0, n1, n2, N;
-    float h2, inv_h2, a_ih4;
-    double inv_h4;
-    float *e, *r, *pt, *t0, *old;   // LDS
 };
 
-__device__ __forceinline__ CLev ctail_level(const TailCorrArgs& a, float* pool, int l) {
-    int off = 0;
-    for (int q = 0; q < l; ++q) off += (q == 0 ? 4 : 5) * a.n[q][0] * a.n[q][1] * a.n[q][2];
-    CLev T;
-    T.n0 = a.n[l][0];
-    T.n1 = a.n[l][1];
-    T.n2 = a.n[l][2];
-    T.N = T.n0 * T.n1 * T.n2;
-    const double h2 = a.h[l] * a.h[l];
-    T.h2 = (float)h2;
-    T.inv_h2 = (float)(1.0 / h2);
-    T.inv_h4 = 1.0 / (h2 * h2);
-    T.a_ih4 = (float)(a.c64.alpha * T.inv_h4);
-    T.e = pool + off;
-    T.r = T.e + T.N;
-    T.pt = T.r + T.N;
-    T.t0 = T.pt + T.N;
-    T.old = l > 0 ? T.t0 + T.N : nullptr;
-    return T;
-}
-
-__device__ __forceinline__ int ctail_idx(const CLev& L, int i, int j, int k) {
-    return (tw(k, L.n2) * L.n1 + tw(j, L.n1)) * L.n0 + tw(i, L.n0);
-}
-
-__device__ __forceinline__ void ctail_decode(const CLev& L, int e, int& i, int& j, int& k) {
-    i = e % L.n0;
-    const int r = e / L.n0;
-    j = r % L.n1;
-    k = r / L.n1;
-}
-
-template <typename T>
-__device__ __forceinline__ void ctail_gather(const CLev& L, const T* u, int i, int j, int k, NbT<T>& v) {
-    tail_gather_o(tail_nbr(L.n0, L.n1, L.n2, i, j, k), u, v);
-}
-
-// dQ(e) at cell (i,j,k) and the neighbour sum of e
-__device__ __forceinline__ float ctail_dq(const CLev& L, const CoefF& c, int i, int j, int k, int e, float& Se) {
-    const TNbr o = tail_nbr(L.n0, L.n1, L.n2, i, j, k);
-    NbT<float> ve, vp;
-    tail_gather_o(o, L.e, ve);
-    tail_gather_o(o, L.pt, vp);
-    return dQ_of(dq_corr(ve, vp, L.a_ih4, Se), L.t0[e], c);
-}
-
-// ctail_dq that also returns the discriminant of the corrected state
-__device__ __forceinline__ float ctail_dq_d(const CLev& L, const CoefF& c, int i, int j, int k, int e, float& Se,
-                                            float& D1) {
-    const TNbr o = tail_nbr(L.n0, L.n1, L.n2, i, j, k);
-    NbT<float> ve, vp;
-    tail_gather_o(o, L.e, ve);
-    tail_gather_o(o, L.pt, vp);
-    return dQ_of_d(dq_corr(ve, vp, L.a_ih4, Se), L.t0[e], c, D1);
-}
-
-__device__ void ctail_sweep(const CLev& L, float* tmp, const CoefF& c, float cb) {
-    const int tid = threadIdx.x;
-    auto update = [&](int i, int j, int k) {
-        const int e = (k * L.n1 + j) * L.n0 + i;
-        float Se, D1;
-        const float dQ = ctail_dq_d(L, c, i, j, k, e, Se, D1);
-        tmp[e] = kink_relax(L.e[e], (Se - L.h2 * (dQ + L.r[e] - cb)) * (1.0f / 6.0f), D1, kink_k(L.h2));
+// The mixed path's FP32 correction problem Lap e - dQ(e) = r - cbar_e: the base
+// state phi~ enters through six differences of its neighbours, which stay fixed
+// over the launch, and t0 = +-sqrt|D0|.
+struct TailCorrK {
+    using T = float;
+    static constexpr bool BASE = true;
+    struct Cell {
+        float dxy, dxz, dyz, bxy, bxz, byz;   // 2 x the differences of phi~
+        float t0;
     };
-    for (int colour = 0; colour < 2; ++colour) {
-        if ((L.n0 & 1) == 0) {
-            for (int q = tid; q < (L.N >> 1); q += TAIL_NT) {
-                int i, j, k;
-                colour_cell(L.n0, L.n1, q, colour, i, j, k);
-                update(i, j, k);
-            }
-            __syncthreads();
-            for (int q = tid; q < (L.N >> 1); q += TAIL_NT) {
-                int i, j, k;
-                colour_cell(L.n0, L.n1, q, colour, i, j, k);
-                const int e = (k * L.n1 + j) * L.n0 + i;
-                L.e[e] = tmp[e];
-            }
-        } else {
-            for (int e = tid; e < L.N; e += TAIL_NT) {
-                int i, j, k;
-                ctail_decode(L, e, i, j, k);
-                if (((i + j + k) & 1) == colour) update(i, j, k);
-            }
-            __syncthreads();
-            for (int e = tid; e < L.N; e += TAIL_NT) {
-                int i, j, k;
-                ctail_decode(L, e, i, j, k);
-                if (((i + j + k) & 1) == colour) L.e[e] = tmp[e];
-            }
-        }
-        __syncthreads();
+    CoefF c;
+    Coef c64;
+    float h2, inv_h2, a_ih4;
+    double inv_h4;
+    float kk;
+    __device__ TailCorrK(const Coef& c_, double h) : c64(c_) {
+        c.alpha = (float)c_.alpha;
+        c.c8 = (float)c_.c8;
+        c.a34 = c_.alpha != 0.0 ? (float)(3.0 / (4.0 * c_.alpha)) : 0.0f;
+        const double hh = h * h;
+        h2 = (float)hh;
+        inv_h2 = (float)(1.0 / hh);
+        inv_h4 = 1.0 / (hh * hh);
+        a_ih4 = (float)(c_.alpha * inv_h4);
+        kk = kink_k(h2);
     }
+    __device__ static void base_cell(const NbT<float>& p, Cell& k) {
+        const float sx = p.xp + p.xm, sy = p.yp + p.ym, sz = p.zp + p.zm;
+        k.dxy = 2.0f * (sx - sy);
+        k.dxz = 2.0f * (sx - sz);
+        k.dyz = 2.0f * (sy - sz);
+        k.bxy = 2.0f * ((p.xpyp + p.xmym) - (p.xpym + p.xmyp));
+        k.bxz = 2.0f * ((p.xpzp + p.xmzm) - (p.xpzm + p.xmzp));
+        k.byz = 2.0f * ((p.ypzp + p.ymzm) - (p.ypzm + p.ymzp));
+    }
+    // +-sqrt|D0| from the FP64 discriminant of phi~ and the density
+    __device__ float base_t0(const NbT<float>& p, double del) const {
+        Nb v;
+        v.xm = p.xm; v.xp = p.xp; v.ym = p.ym; v.yp = p.yp; v.zm = p.zm; v.zp = p.zp;
+        v.xpyp = p.xpyp; v.xmym = p.xmym; v.xpym = p.xpym; v.xmyp = p.xmyp;
+        v.xpzp = p.xpzp; v.xmzm = p.xmzm; v.xpzm = p.xpzm; v.xmzp = p.xmzp;
+        v.ypzp = p.ypzp; v.ymzm = p.ymzm; v.ypzm = p.ypzm; v.ymzp = p.ymzp;
+        const double D0 = base_discriminant(v, del, c64, inv_h4);
+        return (float)(D0 >= 0.0 ? sqrt(D0) : -sqrt(-D0));
+    }
+    __device__ float root(const NbT<float>& e, const Cell& k, float& Se, float& D1) const {
+        const float sx = e.xp + e.xm, sy = e.yp + e.ym, sz = e.zp + e.zm;
+        Se = sx + sy + sz;
+        const float dxy = sx - sy, dxz = sx - sz, dyz = sy - sz;
+        const float bxy = (e.xpyp + e.xmym) - (e.xpym + e.xmyp);
+        const float bxz = (e.xpzp + e.xmzm) - (e.xpzm + e.xmzp);
+        const float byz = (e.ypzp + e.ymzm) - (e.ypzm + e.ymzp);
+        const float pd = fmaf(k.dxy + dxy, dxy, fmaf(k.dxz + dxz, dxz, (k.dyz + dyz) * dyz));
+        const float pb = fmaf(k.bxy + bxy, bxy, fmaf(k.bxz + bxz, bxz, (k.byz + byz) * byz));
+        return dQ_of_d(fmaf(a_ih4 * (1.0f / 3.0f), pd, a_ih4 * 0.125f * pb), k.t0, c, D1);
+    }
+};
+
+// updated value of a cell (old value `old`, right-hand side f)
+template <typename K, typename T>
+__device__ __forceinline__ T tail_update(const K& k, const NbT<T>& v, const typename K::Cell& cell, T old, T f, T cb) {
+    T S, D;
+    const T Q = k.root(v, cell, S, D);
+    return kink_relax(old, (S - k.h2 * (Q + f - cb)) * T(1.0 / 6.0), D, k.kk);
 }
+
+constexpr int T8_NT = 256;
 
 }  // namespace
 
-__global__ void __launch_bounds__(TAIL_NT) k_tail_corr(TailCorrArgs a) {
-    __shared__ float pool[CTAIL_POOL];
-    __shared__ float tmp[TAIL_CELLS];
-    __shared__ double red[TAIL_NT / 64][2];
-    __shared__ float cbar[TAIL_LEVELS];
+// Arguments common to both problems (launch_tail, launch_tail_corr fill them).
+template <typename T>
+struct Tail {
+    int n[3];               // top level's cells
+    double h;               // its cell size
+    const double* delta;    // its density (FP64 problem)
+    const double* delta_c;  // density of the 4^3 level (k_tail8)
+    T* u;                   // its state (in/out)
+    const T* f;             // its right-hand side (may be null: zero)
+    const T *pt, *t0;       // correction problem: base state and +-sqrt|D0|
+    LevelScalars* sc;       // its cbar (in/out)
+    Coef c;
+    int nu1, nu2, ncoarse;
+};
+
+// 8^3 over 4^3.
+template <typename K>
+__global__ void __launch_bounds__(T8_NT) k_tail8(Tail<typename K::T> a) {
+    using T = typename K::T;
+    __shared__ T u8[512], d8[512], pt8[K::BASE ? 512 : 1];
+    __shared__ T u4[64], c4[64], pt4[K::BASE ? 64 : 1];
+    __shared__ double red[T8_NT / 64][2];
     const int tid = threadIdx.x;
-    const int nl = a.nlev;
-    CoefF cf;
-    cf.alpha = (float)a.c64.alpha;
-    cf.c8 = (float)a.c64.c8;
-    cf.a34 = a.c64.alpha != 0.0 ? (float)(3.0 / (4.0 * a.c64.alpha)) : 0.0f;
-    {
-        const CLev T = ctail_level(a, pool, 0);
-        for (int e = tid; e < T.N; e += TAIL_NT) {
-            T.e[e] = a.e[e];
-            T.r[e] = a.r[e];
-            T.pt[e] = a.pt[e];
-            T.t0[e] = a.t0[e];
-        }
-    }
-    if (tid == 0) cbar[0] = (float)a.sc->cbar;
-    __syncthreads();
-    const int last = nl - 1;
-    for (int l = 0; l < last; ++l) {
-        const CLev F = ctail_level(a, pool, l);
-        const CLev C = ctail_level(a, pool, l + 1);
-        for (int s = 0; s < a.nu1; ++s) ctail_sweep(F, tmp, cf, cbar[l]);
-        // residual d_e of every fine cell into tmp, then the 8-child averages of
-        // e, d_e (kept as -R d_e in r^H) and phi~, children summed in a fixed order
-        double sq = 0.0, sf = 0.0;
-        for (int fe = tid; fe < F.N; fe += TAIL_NT) {
-            int i, j, k;
-            ctail_decode(F, fe, i, j, k);
-            float Se;
-            const float dQ = ctail_dq(F, cf, i, j, k, fe, Se);
-            tmp[fe] = (Se - 6.0f * F.e[fe]) * F.inv_h2 - dQ - F.r[fe] + cbar[l];
-            sq += dQ;
-            sf += F.r[fe];
-        }
-        __syncthreads();
-        for (int e = tid; e < C.N; e += TAIL_NT) {
-            int I, J, K;
-            ctail_decode(C, e, I, J, K);
-            float se = 0.0f, sd = 0.0f, sp = 0.0f;
+    const K k8(a.c, a.h), k4(a.c, 2.0 * a.h);
+    // this thread's cells of the 8^3 level: colour 0 and 1 of one x pair of a row
+    const int j8 = (tid >> 2) & 7, z8 = tid >> 5;
+    TNbr o8[2];
 #pragma unroll
-            for (int m = 0; m < 8; ++m) {
-                const int fe = ((2 * K + (m >> 2)) * F.n1 + 2 * J + ((m >> 1) & 1)) * F.n0 + 2 * I + (m & 1);
-                sd += tmp[fe];
-                se += F.e[fe];
-                sp += F.pt[fe];
-            }
-            C.e[e] = 0.125f * se;
-            C.old[e] = 0.125f * se;
-            C.r[e] = -0.125f * sd;
-            C.pt[e] = 0.125f * sp;
+    for (int q = 0; q < 2; ++q) o8[q] = tail_nbr(8, 8, 8, 2 * (tid & 3) + ((j8 + z8 + q) & 1), j8, z8);
+    T v8[2], f8[2];
+    typename K::Cell g8[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const int e = o8[q].centre();
+        v8[q] = a.u[e];
+        f8[q] = a.f ? a.f[e] : T(0);
+        if constexpr (K::BASE) {
+            g8[q].t0 = a.t0[e];
+            pt8[e] = a.pt[e];
+        } else {
+            g8[q].del = a.delta[e];
         }
-        double SQ, SF;
-        tail_sum2(sq, sf, SQ, SF, red);
-        if (tid == 0) cbar[l] = (float)((SF + SQ) / (double)F.N);
-        // t0 of the coarse level from the FP64 discriminant of phi~ and delta
-        for (int e = tid; e < C.N; e += TAIL_NT) {
-            int I, J, K;
-            ctail_decode(C, e, I, J, K);
-            NbT<float> vp;
-            ctail_gather(C, C.pt, I, J, K, vp);
-            Nb vb;
-            vb.xm = vp.xm; vb.xp = vp.xp; vb.ym = vp.ym; vb.yp = vp.yp; vb.zm = vp.zm; vb.zp = vp.zp;
-            vb.xpyp = vp.xpyp; vb.xmym = vp.xmym; vb.xpym = vp.xpym; vb.xmyp = vp.xmyp;
-            vb.xpzp = vp.xpzp; vb.xmzm = vp.xmzm; vb.xpzm = vp.xpzm; vb.xmzp = vp.xmzp;
-            vb.ypzp = vp.ypzp; vb.ymzm = vp.ymzm; vb.ypzm = vp.ypzm; vb.ymzp = vp.ymzp;
-            const double D0 = base_discriminant(vb, a.delta[l + 1][e], a.c64, C.inv_h4);
-            C.t0[e] = (float)(D0 >= 0.0 ? sqrt(D0) : -sqrt(-D0));
-        }
-        __syncthreads();
-        // coarse rhs r^H = L_e^H(R e) - R d_e
-        sq = 0.0;
-        sf = 0.0;
-        for (int e = tid; e < C.N; e += TAIL_NT) {
-            int I, J, K;
-            ctail_decode(C, e, I, J, K);
-            float Se;
-            const float dQ = ctail_dq(C, cf, I, J, K, e, Se);
-            const float rh = (Se - 6.0f * C.e[e]) * C.inv_h2 - dQ + C.r[e];
-            C.r[e] = rh;
-            sq += dQ;
-            sf += rh;
-        }
-        tail_sum2(sq, sf, SQ, SF, red);
-        if (tid == 0) cbar[l + 1] = (float)((SF + SQ) / (double)C.N);
-        __syncthreads();
     }
-    // coarsest level: cbar_e from the current sum of dQ before every sweep
-    {
-        const CLev C = ctail_level(a, pool, last);
-        double sf = 0.0, dummy = 0.0, SF, D;
-        for (int e = tid; e < C.N; e += TAIL_NT) sf += C.r[e];
-        tail_sum2(sf, dummy, SF, D, red);
+    // the 4^3 level: one cell per lane of the first wave
+    const TNbr o4 = tail_nbr(4, 4, 4, tid & 3, (tid >> 2) & 3, (tid >> 4) & 3);
+    const double del4 = tid < 64 ? a.delta_c[tid] : 0.0;
+    T cb8 = (T)a.sc->cbar;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) u8[o8[q].centre()] = v8[q];
+    __syncthreads();
+    if constexpr (K::BASE) {
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            NbT<T> p;
+            tail_gather(o8[q], pt8, p);
+            K::base_cell(p, g8[q]);
+        }
+    }
+    auto sweeps8 = [&](int count) {
+        for (int s = 0; s < count; ++s)
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                NbT<T> v;
+                tail_gather(o8[q], u8, v);
+                v8[q] = tail_update(k8, v, g8[q], v8[q], f8[q], cb8);
+                __syncthreads();
+                u8[o8[q].centre()] = v8[q];
+                __syncthreads();
+            }
+    };
+    sweeps8(a.nu1);
+    // residual of every 8^3 cell, then the level's new cbar
+    double sq = 0.0, sf = 0.0;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        NbT<T> v;
+        tail_gather(o8[q], u8, v);
+        T S, D;
+        const T Q = k8.root(v, g8[q], S, D);
+        d8[o8[q].centre()] = (S - T(6) * v8[q]) * k8.inv_h2 - Q - f8[q] + cb8;
+        sq += Q;
+        sf += f8[q];
+    }
+    sq = wave_total(sq);
+    sf = wave_total(sf);
+    if ((tid & 63) == 0) {
+        red[tid >> 6][0] = sq;
+        red[tid >> 6][1] = sf;
+    }
+    __syncthreads();
+    double SQ = 0.0, SF = 0.0;
+#pragma unroll
+    for (int w = 0; w < T8_NT / 64; ++w) {
+        SQ += red[w][0];
+        SF += red[w][1];
+    }
+    cb8 = (T)((SF + SQ) / 512.0);
+    if (tid < 64) {
+        // 8-child averages of phi, d (and phi~), children summed in a fixed order
+        T su = T(0), sd = T(0), sp = T(0);
+        const int I = tid & 3, J = (tid >> 2) & 3, Z = tid >> 4;
+#pragma unroll
+        for (int m = 0; m < 8; ++m) {
+            const int e = ((2 * Z + (m >> 2)) * 8 + 2 * J + ((m >> 1) & 1)) * 8 + 2 * I + (m & 1);
+            sd += d8[e];
+            su += u8[e];
+            if constexpr (K::BASE) sp += pt8[e];
+        }
+        const T old = T(0.125) * su;
+        T v4 = old;
+        u4[tid] = v4;
+        typename K::Cell g4;
+        if constexpr (K::BASE) pt4[tid] = T(0.125) * sp;
+        wave_sync();
+        if constexpr (K::BASE) {
+            NbT<T> p;
+            tail_gather(o4, pt4, p);
+            K::base_cell(p, g4);
+            g4.t0 = k4.base_t0(p, del4);
+        } else {
+            g4.del = del4;
+        }
+        // coarse rhs f^H = L^H(R phi) - R d
+        NbT<T> v;
+        T S, D;
+        tail_gather(o4, u4, v);
+        T Q = k4.root(v, g4, S, D);
+        const T f4 = (S - T(6) * v4) * k4.inv_h2 - Q - T(0.125) * sd;
+        const double sf4 = wave_total((double)f4);
+        // coarsest sweeps, cbar from the current sum of Q before each
+        const int colour = (I + J + Z) & 1;
         for (int s = 0; s < a.ncoarse; ++s) {
-            double sq = 0.0, SQ;
-            for (int e = tid; e < C.N; e += TAIL_NT) {
-                int i, j, k;
-                ctail_decode(C, e, i, j, k);
-                float Se;
-                sq += ctail_dq(C, cf, i, j, k, e, Se);
+            tail_gather(o4, u4, v);
+            Q = k4.root(v, g4, S, D);
+            const T cb = (T)((sf4 + wave_total((double)Q)) / 64.0);
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                if (colour == q) {
+                    tail_gather(o4, u4, v);
+                    v4 = tail_update(k4, v, g4, v4, f4, cb);
+                }
+                wave_sync();
+                if (colour == q) u4[tid] = v4;
+                wave_sync();
             }
-            tail_sum2(sq, dummy, SQ, D, red);
-            ctail_sweep(C, tmp, cf, (float)((SF + SQ) / (double)C.N));
         }
+        c4[tid] = v4 - old;
     }
-    // ascent: prolongation of the correction's correction, post-smoothing
-    for (int l = last - 1; l >= 0; --l) {
-        const CLev F = ctail_level(a, pool, l);
-        const CLev C = ctail_level(a, pool, l + 1);
-        for (int e = tid; e < F.N; e += TAIL_NT) {
-            int i, j, k;
-            ctail_decode(F, e, i, j, k);
-            const int I = i >> 1, J = j >> 1, K = k >> 1;
-            const int si = (i & 1) ? 1 : -1, sj = (j & 1) ? 1 : -1, sk = (k & 1) ? 1 : -1;
-            float acc = 0.0f;
-            for (int m = 0; m < 8; ++m) {
-                const int ai = m & 1, aj = (m >> 1) & 1, ak = m >> 2;
-                const float w = (ai ? 0.25f : 0.75f) * (aj ? 0.25f : 0.75f) * (ak ? 0.25f : 0.75f);
-                const int ci = ctail_idx(C, I + ai * si, J + aj * sj, K + ak * sk);
-                acc += w * (C.e[ci] - C.old[ci]);
-            }
-            F.e[e] += acc;
+    __syncthreads();
+    // prolongation of the correction, post-smoothing
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const int i = o8[q].x[1];
+        T acc = T(0);
+#pragma unroll
+        for (int m = 0; m < 8; ++m) {
+            const int ai = m & 1, aj = (m >> 1) & 1, ak = m >> 2;
+            const T w = T((ai ? 0.25 : 0.75) * (aj ? 0.25 : 0.75) * (ak ? 0.25 : 0.75));
+            const int ci = ((i >> 1) + (ai ? ((i & 1) ? 1 : -1) : 0)) & 3;
+            const int cj = ((j8 >> 1) + (aj ? ((j8 & 1) ? 1 : -1) : 0)) & 3;
+            const int ck = ((z8 >> 1) + (ak ? ((z8 & 1) ? 1 : -1) : 0)) & 3;
+            acc += w * c4[(ck * 4 + cj) * 4 + ci];
         }
-        __syncthreads();
-        for (int s = 0; s < a.nu2; ++s) ctail_sweep(F, tmp, cf, cbar[l]);
+        v8[q] += acc;
+        u8[o8[q].centre()] = v8[q];
     }
-    {
-        const CLev T = ctail_level(a, pool, 0);
-        for (int e = tid; e < T.N; e += TAIL_NT) a.e[e] = T.e[e];
-    }
-    if (tid == 0) a.sc->cbar = cbar[0];
+    __syncthreads();
+    sweeps8(a.nu2);
+#pragma unroll
+    for (int q = 0; q < 2; ++q) a.u[o8[q].centre()] = v8[q];
+    if (tid == 0) a.sc->cbar = cb8;
 }
 
-hipError_t launch_tail_corr(const TailCorrArgs& a, hipStream_t s) {
-    if (a.nlev < 1 || a.nlev > TAIL_LEVELS) return hipErrorInvalidValue;
-    int64_t need = 0;
-    for (int l = 0; l < a.nlev; ++l) {
-        const int64_t N = (int64_t)a.n[l][0] * a.n[l][1] * a.n[l][2];
-        if (N > TAIL_CELLS || a.n[l][0] < 1 || a.n[l][1] < 1 || a.n[l][2] < 1) return hipErrorInvalidValue;
-        if (l > 0)
-            for (int d = 0; d < 3; ++d)
-                if (2 * a.n[l][d] != a.n[l - 1][d]) return hipErrorInvalidValue;
-        need += (l == 0 ? 4 : 5) * N;
+// One coarsest level of up to 512 cells, any shape: thread t owns cells t and t + NTH.
+template <typename K, int NTH>
+__global__ void __launch_bounds__(NTH) k_tail1(Tail<typename K::T> a) {
+    using T = typename K::T;
+    __shared__ T u[TAIL_CELLS], pt[K::BASE ? TAIL_CELLS : 1];
+    __shared__ double red[2][NTH / 64];
+    const int tid = threadIdx.x;
+    const int n0 = a.n[0], n1 = a.n[1], n2 = a.n[2], N = n0 * n1 * n2;
+    const K k(a.c, a.h);
+    constexpr int NS = NTH >= 256 ? 2 : 1;
+    TNbr o[NS];
+    T val[NS], f[NS];
+    typename K::Cell g[NS];
+    int colour[NS];   // -1: no cell
+    double sf = 0.0;
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+        const int e = tid + s * NTH;
+        const bool ok = e < N;
+        const int i = ok ? e % n0 : 0, r = ok ? e / n0 : 0, j = r % n1, z = r / n1;
+        o[s] = tail_nbr(n0, n1, n2, i, j, z);
+        colour[s] = ok ? (i + j + z) & 1 : -1;
+        const int c = o[s].centre();
+        val[s] = a.u[c];
+        f[s] = a.f ? a.f[c] : T(0);
+        if constexpr (K::BASE) {
+            g[s].t0 = a.t0[c];
+            if (ok) pt[e] = a.pt[c];
+        } else {
+            g[s].del = a.delta[c];
+        }
+        if (ok) {
+            u[e] = val[s];
+            sf += f[s];
+        }
     }
-    if (need > CTAIL_POOL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_tail_corr, dim3(1), dim3(TAIL_NT), 0, s, a);
+    __syncthreads();
+    if constexpr (K::BASE) {
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            NbT<T> p;
+            tail_gather(o[s], pt, p);
+            K::base_cell(p, g[s]);
+        }
+    }
+    int turn = 0;   // the two halves of red alternate, so one barrier per sum is enough
+    auto total = [&](double x) {
+        x = wave_total(x);
+        if (NTH == 64) return x;
+        if ((tid & 63) == 0) red[turn][tid >> 6] = x;
+        __syncthreads();
+        double s = 0.0;
+#pragma unroll
+        for (int w = 0; w < NTH / 64; ++w) s += red[turn][w];
+        turn ^= 1;
+        return s;
+    };
+    const double SF = total(sf);
+    for (int sw = 0; sw < a.ncoarse; ++sw) {
+        double sq = 0.0;
+#pragma unroll
+        for (int s = 0; s < NS; ++s)
+            if (colour[s] >= 0) {
+                NbT<T> v;
+                tail_gather(o[s], u, v);
+                T S, D;
+                sq += k.root(v, g[s], S, D);
+            }
+        const T cb = (T)((SF + total(sq)) / (double)N);
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+#pragma unroll
+            for (int s = 0; s < NS; ++s)
+                if (colour[s] == q) {
+                    NbT<T> v;
+                    tail_gather(o[s], u, v);
+                    val[s] = tail_update(k, v, g[s], val[s], f[s], cb);
+                }
+            __syncthreads();
+#pragma unroll
+            for (int s = 0; s < NS; ++s)
+                if (colour[s] == q) u[o[s].centre()] = val[s];
+            __syncthreads();
+        }
+    }
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+        if (colour[s] >= 0) a.u[o[s].centre()] = val[s];
+}
+
+// nlev levels from the one `a` describes, `next` the cells of the one below it
+template <typename K>
+static hipError_t tail_launch(const Tail<typename K::T>& a, int nlev, const int next[3], hipStream_t s) {
+    const int64_t N = (int64_t)a.n[0] * a.n[1] * a.n[2];
+    if (N < 1 || N > TAIL_CELLS || a.n[0] < 1 || a.n[1] < 1 || a.n[2] < 1) return hipErrorInvalidValue;
+    if (nlev == 2) {
+        for (int d = 0; d < 3; ++d)
+            if (a.n[d] != 8 || next[d] != 4) return hipErrorInvalidValue;
+        hipLaunchKernelGGL((k_tail8<K>), dim3(1), dim3(T8_NT), 0, s, a);
+    } else if (nlev == 1) {
+        if (N <= 64) hipLaunchKernelGGL((k_tail1<K, 64>), dim3(1), dim3(64), 0, s, a);
+        else hipLaunchKernelGGL((k_tail1<K, 256>), dim3(1), dim3(256), 0, s, a);
+    } else {
+        return hipErrorInvalidValue;   // no periodic hierarchy has three levels of <= 512 cells
+    }
     return hipGetLastError();
 }
 
 hipError_t launch_tail(const TailArgs& a, hipStream_t s) {
-    if (a.nlev < 1 || a.nlev > TAIL_LEVELS) return hipErrorInvalidValue;
-    int64_t need = 0;
-    for (int l = 0; l < a.nlev; ++l) {
-        const int64_t N = (int64_t)a.n[l][0] * a.n[l][1] * a.n[l][2];
-        if (N > TAIL_CELLS || a.n[l][0] < 1 || a.n[l][1] < 1 || a.n[l][2] < 1) return hipErrorInvalidValue;
-        if (l > 0)
-            for (int d = 0; d < 3; ++d)
-                if (2 * a.n[l][d] != a.n[l - 1][d]) return hipErrorInvalidValue;
-        need += (l == 0 ? 3 : 4) * N;
-    }
-    if (need > TAIL_POOL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_tail, dim3(1), dim3(TAIL_NT), 0, s, a);
-    return hipGetLastError();
+    Tail<double> t;
+    for (int d = 0; d < 3; ++d) t.n[d] = a.n[0][d];
+    t.h = a.h[0];
+    t.delta = a.delta[0];
+    t.delta_c = a.nlev > 1 ? a.delta[1] : nullptr;
+    t.u = a.phi;
+    t.f = a.f;
+    t.pt = t.t0 = nullptr;
+    t.sc = a.sc;
+    t.c = a.c;
+    t.nu1 = a.nu1; t.nu2 = a.nu2; t.ncoarse = a.ncoarse;
+    return tail_launch<TailK>(t, a.nlev, a.n[1], s);
+}
+
+hipError_t launch_tail_corr(const TailCorrArgs& a, hipStream_t s) {
+    Tail<float> t;
+    for (int d = 0; d < 3; ++d) t.n[d] = a.n[0][d];
+    t.h = a.h[0];
+    t.delta = a.delta[0];
+    t.delta_c = a.nlev > 1 ? a.delta[1] : nullptr;
+    t.u = a.e;
+    t.f = a.r;
+    t.pt = a.pt;
+    t.t0 = a.t0;
+    t.sc = a.sc;
+    t.c = a.c64;
+    t.nu1 = a.nu1; t.nu2 = a.nu2; t.ncoarse = a.ncoarse;
+    return tail_launch<TailCorrK>(t, a.nlev, a.n[1], s);
 }
 
 }  // namespace vmg

@@ -126,9 +126,10 @@ inline SmoothCfg default_march(int n0, int n1, int n2) {
 
 // ---- coarse tail (kernels_tail.hip) ----------------------------------------
 // Periodic levels with at most TAIL_CELLS cells, down to the coarsest, in one
-// single-workgroup launch (all arrays in LDS).
+// single-workgroup launch (all arrays in LDS).  A level coarsens only while every
+// axis keeps 4 cells, so such a tail is 8^3 over 4^3 or one coarsest level.
 constexpr int TAIL_CELLS = 512;
-constexpr int TAIL_LEVELS = 6;
+constexpr int TAIL_LEVELS = 2;
 struct TailArgs {
     int nlev;                           // levels in the tail; [0] is its top level
     int n[TAIL_LEVELS][3];

@@ -1,0 +1,34 @@
+"""The single-launch coarse tail against the level-by-level cycle (which the other
+tests pin to the oracle): 8^3 over 4^3, and one coarsest level of every kind (one
+wave, four waves, odd and uneven sizes), with and without pre- or post-sweeps."""
+import numpy as np
+import pytest
+
+from paper_1303_0008_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+
+# The cycles do the same arithmetic up to the order of sums and fused products.
+# FP64: three cycles of at most 30 coarse updates, each a few eps of |phi|.
+# Mixed: the same count in FP32, three outer iterations of two inner cycles:
+# 180 updates x 2^-24 of the correction, which starts as large as phi.
+@pytest.mark.parametrize("prec,bound", [("fp64", 1e-12), ("mixed", 2e-5)])
+@pytest.mark.parametrize("n", [(8, 8, 8), (16, 16, 16), (20, 24, 28), (14, 12, 10), (16, 12, 8), (64, 64, 64)])
+@pytest.mark.parametrize("nu,coarse", [((2, 2), 4), ((0, 1), 3), ((3, 0), 8)])
+def test_tail_equals_levels(prec, bound, n, nu, coarse):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1303_0008_amd import vmg as V
+    delta = torch.from_numpy(I.lognormal(n, 21, sigma=0.7)).to("cuda")
+    out = []
+    for tail in (1, 0):
+        with V.Plan([V.make_grid(n)], V.make_params(0.1, 1.5, 1e-30, 3, {"fp64": V.FP64, "mixed": V.MIXED}[prec],
+                                                    flags=V.GRAPH)) as p:
+            p.set_cycle(nu1=nu[0], nu2=nu[1], coarse_sweeps=coarse, coarse_tail=tail)
+            phi = torch.zeros_like(delta)
+            p.solve(delta, phi, allow_noconv=True)
+            out.append(phi.cpu().numpy())
+    assert np.abs(out[1]).max() > 0
+    assert np.abs(out[0] - out[1]).max() <= bound * np.abs(out[1]).max()
