@@ -33,29 +33,6 @@ namespace vmg {
 
 namespace {
 
-// Sum over the wave, in every lane (row shifts, then row broadcasts; lane 63
-// holds the total).
-template <int CTRL, int ROWS>
-__device__ __forceinline__ double dpp_add(double v) {
-    const long long b = __builtin_bit_cast(long long, v);
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, ROWS, 0xf, true);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, ROWS, 0xf, true);
-    return v + __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned)lo);
-}
-
-__device__ __forceinline__ double wave_total(double v) {
-    v = dpp_add<0x111, 0xf>(v);   // row_shr:1
-    v = dpp_add<0x112, 0xf>(v);
-    v = dpp_add<0x114, 0xf>(v);
-    v = dpp_add<0x118, 0xf>(v);   // lane 15 of each row: the row's sum
-    v = dpp_add<0x142, 0xa>(v);   // row_bcast:15 into rows 1 and 3
-    v = dpp_add<0x143, 0xc>(v);   // row_bcast:31 into rows 2 and 3
-    const long long b = __builtin_bit_cast(long long, v);
-    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)b, 63);
-    const int hi = __builtin_amdgcn_readlane((int)(b >> 32), 63);
-    return __builtin_bit_cast(double, ((long long)hi << 32) | lo);
-}
-
 // LDS written by a lane of this wave is read by another after this: the LDS
 // serves a wave's accesses in order, so only the compiler has to keep them so.
 __device__ __forceinline__ void wave_sync() {
@@ -271,8 +248,8 @@ __global__ void __launch_bounds__(T8_NT) k_tail8(Tail<typename K::T> a) {
         sq += Q;
         sf += f8[q];
     }
-    sq = wave_total(sq);
-    sf = wave_total(sf);
+    sq = wave_sum(sq);
+    sf = wave_sum(sf);
     if ((tid & 63) == 0) {
         red[tid >> 6][0] = sq;
         red[tid >> 6][1] = sf;
@@ -316,13 +293,13 @@ __global__ void __launch_bounds__(T8_NT) k_tail8(Tail<typename K::T> a) {
         tail_gather(o4, u4, v);
         T Q = k4.root(v, g4, S, D);
         const T f4 = (S - T(6) * v4) * k4.inv_h2 - Q - T(0.125) * sd;
-        const double sf4 = wave_total((double)f4);
+        const double sf4 = wave_sum((double)f4);
         // coarsest sweeps, cbar from the current sum of Q before each
         const int colour = (I + J + Z) & 1;
         for (int s = 0; s < a.ncoarse; ++s) {
             tail_gather(o4, u4, v);
             Q = k4.root(v, g4, S, D);
-            const T cb = (T)((sf4 + wave_total((double)Q)) / 64.0);
+            const T cb = (T)((sf4 + wave_sum((double)Q)) / 64.0);
 #pragma unroll
             for (int q = 0; q < 2; ++q) {
                 if (colour == q) {
@@ -408,7 +385,7 @@ __global__ void __launch_bounds__(NTH) k_tail1(Tail<typename K::T> a) {
     }
     int turn = 0;   // the two halves of red alternate, so one barrier per sum is enough
     auto total = [&](double x) {
-        x = wave_total(x);
+        x = wave_sum(x);
         if (NTH == 64) return x;
         if ((tid & 63) == 0) red[turn][tid >> 6] = x;
         __syncthreads();
