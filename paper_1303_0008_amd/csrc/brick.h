@@ -562,11 +562,6 @@ constexpr int BRICK_WAVES = 4;   // waves per SIMD: two blocks per CU (LDS <= 80
 constexpr int brick_side(int s) { return BB + 4 * s; }          // staged region, per axis
 constexpr int brick_cwin(int s) { return brick_side(s) / 2 + 2; }   // coarse window, per axis
 
-__device__ __forceinline__ int wrap_idx(int i, int n) {
-    i %= n;
-    return i < 0 ? i + n : i;
-}
-
 // whether padded element (x, y, z) of a Dirichlet level is stored (ghost shell included)
 __device__ __forceinline__ bool in_shell(const Geom& g, int x, int y, int z) {
     return x >= -1 && x <= g.n0 && y >= -1 && y <= g.n1 && z >= -1 && z <= g.n2;
@@ -591,7 +586,7 @@ __device__ __forceinline__ void brick_store_ghosts(const K& k, const Geom& g, in
                 if ((dx != 0 && gx >= 0 && gx < g.n0) || (dy != 0 && gy >= 0 && gy < g.n1) ||
                     (dz != 0 && gz >= 0 && gz < g.n2))
                     continue;                         // a step that stays inside: not a ghost of this cell
-                k.store_ghost(cell_index(g, gx, gy, gz), ii, out == 1 ? -1 : 1, v);
+                k.store_ghost(small_index(g, gx, gy, gz), ii, out == 1 ? -1 : 1, v);
             }
 }
 
@@ -625,10 +620,10 @@ __device__ __forceinline__ void brick_sweeps(const K& k, const Geom& g, int bx0,
             const int x = e % RW, y = (e / RW) % RW, z = e / RW2;
             if (DIR) {
                 const int gx = bx0 - R + x, gy = by0 - R + y, gz = bz0 - R + z;
-                u0[q] = in_shell(g, gx, gy, gz) ? k.load_cell(cell_index(g, gx, gy, gz)) : Cell{};
+                u0[q] = in_shell(g, gx, gy, gz) ? k.load_cell(small_index(g, gx, gy, gz)) : Cell{};
             } else {
-                u0[q] = k.load_cell(cell_index(g, wrap_idx(bx0 - R + x, g.n0), wrap_idx(by0 - R + y, g.n1),
-                                               wrap_idx(bz0 - R + z, g.n2)));
+                u0[q] = k.load_cell(small_index(g, wrapi(bx0 - R + x, g.n0), wrapi(by0 - R + y, g.n1),
+                                               wrapi(bz0 - R + z, g.n2)));
             }
         }
     }
@@ -641,10 +636,10 @@ __device__ __forceinline__ void brick_sweeps(const K& k, const Geom& g, int bx0,
             const int x = e % RS, y = (e / RS) % RS, z = e / (RS * RS);
             if (DIR) {
                 const int gx = bx0 - R + 1 + x, gy = by0 - R + 1 + y, gz = bz0 - R + 1 + z;
-                s0[q] = in_shell(g, gx, gy, gz) ? k.load_src(cell_index(g, gx, gy, gz)) : Src{};
+                s0[q] = in_shell(g, gx, gy, gz) ? k.load_src(small_index(g, gx, gy, gz)) : Src{};
             } else {
-                s0[q] = k.load_src(cell_index(g, wrap_idx(bx0 - R + 1 + x, g.n0), wrap_idx(by0 - R + 1 + y, g.n1),
-                                              wrap_idx(bz0 - R + 1 + z, g.n2)));
+                s0[q] = k.load_src(small_index(g, wrapi(bx0 - R + 1 + x, g.n0), wrapi(by0 - R + 1 + y, g.n1),
+                                              wrapi(bz0 - R + 1 + z, g.n2)));
             }
         }
     }
@@ -658,8 +653,8 @@ __device__ __forceinline__ void brick_sweeps(const K& k, const Geom& g, int bx0,
             const int e = tid + q * NTH;
             if (e < NCW) {
                 const int x = e % CW, y = (e / CW) % CW, z = e / (CW * CW);
-                c0[q] = k.load_corr(cell_index(k.gc, wrap_idx(cx0 + x, k.gc.n0), wrap_idx(cy0 + y, k.gc.n1),
-                                               wrap_idx(cz0 + z, k.gc.n2)));
+                c0[q] = k.load_corr(small_index(k.gc, wrapi(cx0 + x, k.gc.n0), wrapi(cy0 + y, k.gc.n1),
+                                               wrapi(cz0 + z, k.gc.n2)));
             }
         }
     }
@@ -756,7 +751,7 @@ __device__ __forceinline__ void brick_sweeps(const K& k, const Geom& g, int bx0,
         const int gx = bx0 + x, gy = by0 + y, gz = bz0 + z;
         if (gx < g.n0 && gy < g.n1 && gz < g.n2) {
             const Cell v = U[((z + R) * RW + (y + R)) * RW + (x + R)];
-            const int64_t ii = cell_index(g, gx, gy, gz);
+            const int64_t ii = small_index(g, gx, gy, gz);
             k.store_cell(ii, v);
             if (GHOSTS) brick_store_ghosts(k, g, gx, gy, gz, ii, v);
         }

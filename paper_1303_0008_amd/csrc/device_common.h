@@ -7,11 +7,16 @@ namespace vmg {
 constexpr int NT = 256;          // threads per block for every kernel here
 constexpr int MAX_RED_BLOCKS = 2048;
 
+// Periodic wrap of an index near [0, n): exact for -n <= i < 2n; beyond that (the
+// columns of a tile or brick past a grid smaller than it, which no stored cell
+// draws on) any index in range.  Compares and adds: a run-time modulo is some 25
+// instructions, quarter-rate multiplies among them, and a block of the small
+// levels' sweeps wraps 14 elements per thread and axis before it can load.
 __device__ __forceinline__ int wrapi(int i, int n) {
-    i %= n;
-    return i < 0 ? i + n : i;
+    i += i < 0 ? n : 0;
+    i -= i >= n ? n : 0;
+    return i < n ? i : 0;
 }
-
 
 // ---------------------------------------------------------------------------
 // Raw buffer access (gfx9 buffer resource).  A load whose byte offset is at or
@@ -279,22 +284,35 @@ __device__ __forceinline__ void decode(const Geom& g, int64_t e, int& i, int& j,
     k = (int)(r / g.n1);
 }
 
+// (a row and a plane hold fewer than 2^31 elements, so each product is one 32 x 32
+// -> 64 multiply)
 __device__ __forceinline__ int64_t cell_index(const Geom& g, int i, int j, int k) {
-    return g.off0 + i + (int64_t)j * g.sy + (int64_t)k * g.sz;
+    return g.off0 + i + (int64_t)j * (int)g.sy + (int64_t)k * (int)g.sz;
+}
+
+// The same for levels of fewer than 2^31 elements with fewer than 2^23 rows (all
+// that bricks run on), by full-rate 24-bit multiplies.
+__device__ __forceinline__ int64_t small_index(const Geom& g, int i, int j, int k) {
+    return g.off0 + (__mul24(__mul24(k, g.n1 + (g.dir ? 2 : 0)) + j, (int)g.sy) + i);
 }
 
 // 18 neighbours of cell (i,j,k) read through global memory (periodic wrap or ghost shell)
 template <int DIR, typename T, typename NB>
 __device__ __forceinline__ T gather_nb(const Geom& g, const T* __restrict__ u, int i, int j, int k, NB& v) {
-    int im, ip, jm, jp, km, kp;
-    if (DIR) {
-        im = i - 1; ip = i + 1; jm = j - 1; jp = j + 1; km = k - 1; kp = k + 1;
-    } else {
-        im = i == 0 ? g.n0 - 1 : i - 1; ip = i == g.n0 - 1 ? 0 : i + 1;
-        jm = j == 0 ? g.n1 - 1 : j - 1; jp = j == g.n1 - 1 ? 0 : j + 1;
-        km = k == 0 ? g.n2 - 1 : k - 1; kp = k == g.n2 - 1 ? 0 : k + 1;
-    }
     const int64_t sy = g.sy, sz = g.sz, o = g.off0;
+    if (DIR) {   // fixed offsets from the cell
+        const T* __restrict__ p = u + cell_index(g, i, j, k);
+        v.xm = p[-1]; v.xp = p[1];
+        v.ym = p[-sy]; v.yp = p[sy];
+        v.zm = p[-sz]; v.zp = p[sz];
+        v.xpyp = p[sy + 1]; v.xmym = p[-sy - 1]; v.xpym = p[-sy + 1]; v.xmyp = p[sy - 1];
+        v.xpzp = p[sz + 1]; v.xmzm = p[-sz - 1]; v.xpzm = p[-sz + 1]; v.xmzp = p[sz - 1];
+        v.ypzp = p[sz + sy]; v.ymzm = p[-sz - sy]; v.ypzm = p[-sz + sy]; v.ymzp = p[sz - sy];
+        return p[0];
+    }
+    const int im = i == 0 ? g.n0 - 1 : i - 1, ip = i == g.n0 - 1 ? 0 : i + 1;
+    const int jm = j == 0 ? g.n1 - 1 : j - 1, jp = j == g.n1 - 1 ? 0 : j + 1;
+    const int km = k == 0 ? g.n2 - 1 : k - 1, kp = k == g.n2 - 1 ? 0 : k + 1;
     auto at = [&](int x, int y, int z) { return u[o + x + y * sy + z * sz]; };
     v.xm = at(im, j, k); v.xp = at(ip, j, k);
     v.ym = at(i, jm, k); v.yp = at(i, jp, k);

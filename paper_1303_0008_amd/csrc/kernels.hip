@@ -854,7 +854,8 @@ __device__ __forceinline__ double parent_trilinear(const double* __restrict__ pa
     for (int d = 0; d < 3; ++d) {
         const double u = (o[d] + c[d] + 0.5) * h / H - 0.5;   // parent index space
         const double fl = floor(u);
-        lo[d] = wrapi((int)fl, np[d]);
+        lo[d] = (int)fl % np[d];   // (any origin)
+        lo[d] += lo[d] < 0 ? np[d] : 0;
         hi[d] = lo[d] + 1 == np[d] ? 0 : lo[d] + 1;
         t[d] = u - fl;
     }
