@@ -555,6 +555,7 @@ __device__ __forceinline__ void fused_sweep(const K& k, const Geom& g, const int
 //   k.load_cell(i), k.load_src(i), k.store_cell(i, v)   element i of the level
 //   k.load_corr(i)                  u^H - u^H_old at element i of the coarse level
 //   k.update_nb(v, centre, src)     the updated cell from its 18 neighbours
+//   k.set_cbar(c)                   the compatibility constant of the updates
 // ---------------------------------------------------------------------------
 constexpr int BB = BB_SIDE;
 constexpr int BRICK_THREADS = 512;
@@ -590,8 +591,27 @@ __device__ __forceinline__ void brick_store_ghosts(const K& k, const Geom& g, in
             }
 }
 
+// The 18 neighbours of element c of a cube of RW cells per axis.
+template <int RW, typename T>
+__device__ __forceinline__ void brick_nb(const T* U, int c, NbT<T>& v) {
+    constexpr int RW2 = RW * RW;
+    v.xm = U[c - 1];                 v.xp = U[c + 1];
+    v.ym = U[c - RW];                v.yp = U[c + RW];
+    v.zm = U[c - RW2];               v.zp = U[c + RW2];
+    v.xmym = U[c - RW - 1];          v.xpym = U[c - RW + 1];
+    v.xmyp = U[c + RW - 1];          v.xpyp = U[c + RW + 1];
+    v.xmzm = U[c - RW2 - 1];         v.xpzm = U[c - RW2 + 1];
+    v.xmzp = U[c + RW2 - 1];         v.xpzp = U[c + RW2 + 1];
+    v.ymzm = U[c - RW2 - RW];        v.ypzm = U[c - RW2 + RW];
+    v.ymzp = U[c + RW2 - RW];        v.ypzp = U[c + RW2 + RW];
+}
+
+// With `pend`, the level's cbar is still in the block sums of the pass that formed
+// its right-hand side (or its residual): every block sums them while its cells
+// are in flight, and block 0 stores the result for the level's later passes.
 template <int S, bool PRO, int DIR = 0, bool GHOSTS = false, typename K>
-__device__ __forceinline__ void brick_sweeps(const K& k, const Geom& g, int bx0, int by0, int bz0) {
+__device__ __forceinline__ void brick_sweeps(K& k, const Geom& g, int bx0, int by0, int bz0,
+                                             const PendingCbar& pend = PendingCbar{}) {
     using Cell = typename K::Cell;
     using Src = typename K::Src;
     using Corr = typename K::Corr;
@@ -607,6 +627,7 @@ __device__ __forceinline__ void brick_sweeps(const K& k, const Geom& g, int bx0,
     static_assert(!GHOSTS || DIR, "only Dirichlet levels have a ghost shell");
     __shared__ Cell U[NU];
     __shared__ Src SR[NS];
+    __shared__ double psum;
     // the coarse window is read before U is written: it borrows U's space
     Corr* CWB = reinterpret_cast<Corr*>(U);
     const int tid = threadIdx.x;
@@ -627,6 +648,9 @@ __device__ __forceinline__ void brick_sweeps(const K& k, const Geom& g, int bx0,
             }
         }
     }
+    const bool pending = !DIR && pend.part;
+    double share = 0.0;
+    if (pending && tid < 64) share = pending_share(pend);
     // every load is issued before the first LDS write (registers, then LDS)
     Src s0[NLS];
 #pragma unroll
@@ -699,7 +723,16 @@ __device__ __forceinline__ void brick_sweeps(const K& k, const Geom& g, int bx0,
         const int e = tid + q * NTH;
         if (e < NU) U[e] = u0[q];
     }
+    if (pending && tid < 64) {
+        share = wave_sum(share);
+        if (tid == 0) psum = share;
+    }
     __syncthreads();
+    if (pending) {
+        const double cbar = psum / (double)g.ncell;
+        k.set_cbar(cbar);
+        if (blockIdx.x == 0 && tid == 0) pend.sc->cbar = cbar;
+    }
 
     // ---- the 2S colour phases on shrinking rings
     const int par0 = (bx0 + by0 + bz0) & 1;   // colour of region cell (0,0,0) is par0 (R even)
@@ -724,15 +757,7 @@ __device__ __forceinline__ void brick_sweeps(const K& k, const Geom& g, int bx0,
                 }
                 const int c = (z * RW + y) * RW + x;
                 NbT<Cell> v;
-                v.xm = U[c - 1];                 v.xp = U[c + 1];
-                v.ym = U[c - RW];                v.yp = U[c + RW];
-                v.zm = U[c - RW2];               v.zp = U[c + RW2];
-                v.xmym = U[c - RW - 1];          v.xpym = U[c - RW + 1];
-                v.xmyp = U[c + RW - 1];          v.xpyp = U[c + RW + 1];
-                v.xmzm = U[c - RW2 - 1];         v.xpzm = U[c - RW2 + 1];
-                v.xmzp = U[c + RW2 - 1];         v.xpzp = U[c + RW2 + 1];
-                v.ymzm = U[c - RW2 - RW];        v.ypzm = U[c - RW2 + RW];
-                v.ymzp = U[c + RW2 - RW];        v.ypzp = U[c + RW2 + RW];
+                brick_nb<RW>(U, c, v);
                 const Src sv = SR[((z - 1) * RS + (y - 1)) * RS + (x - 1)];
                 res[q] = k.update_nb(v, U[c], sv);
                 at[q] = c;

@@ -350,6 +350,22 @@ __device__ __forceinline__ double wave_sum(double v) {
     return __builtin_bit_cast(double, ((long long)hi << 32) | lo);
 }
 
+// Sum of Q and f over a level from the block sums of a head pass: the share of a
+// lane of one wave, to be added up by wave_sum.  One wave and one order whatever
+// the block, so that every taker of the sums forms the same bits; eight loads are
+// in flight at a time.
+__device__ __forceinline__ double pending_share(const PendingCbar& p) {
+    double s = 0.0;
+    for (int b0 = threadIdx.x & 63; b0 < p.rows; b0 += 8 * 64) {
+        double v[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) v[q] = b0 + 64 * q < p.rows ? p.part[b0 + 64 * q] : 0.0;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) s += v[q];
+    }
+    return s;
+}
+
 // Sum R_NSLOT per-thread accumulators over the block (fixed order) and store
 // them in partials[blockIdx.x * R_NSLOT + k].
 __device__ __forceinline__ void block_store_partials(double (&acc)[R_NSLOT], double* partials) {

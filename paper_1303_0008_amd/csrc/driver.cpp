@@ -146,6 +146,13 @@ vmg_status build_plan(Plan* P, const vmg_grid* grids, int n_grids, const vmg_par
                 CKH(launch_fill((double*)L.sc, sizeof(LevelScalars) / sizeof(double), 0.0, stream));
             }
         }
+        for (auto& G : P->grids)
+            for (size_t l = 0; l < G.lev.size(); ++l) {
+                if (!one_launch_head(G, (int)l)) continue;
+                const size_t bytes = sizeof(double) * R_NSLOT * (size_t)head_blocks(G.lev[l].g);
+                if ((st = dalloc(P, (void**)&G.lev[l].sums, bytes)) != VMG_OK) return st;
+                if ((st = dalloc(P, (void**)&G.lev[l + 1].sums_c, bytes)) != VMG_OK) return st;
+            }
         if (P->mixed && (st = alloc_mixed(P)) != VMG_OK) return st;
     }
     for (auto& G : P->grids) {
@@ -243,16 +250,29 @@ static hipError_t collect_levels(Plan* P) {
     return hipSuccess;
 }
 
+hipError_t settle_cbar(Plan* P, LevelBuf& L, LevelScalars* sc) {
+    if (!L.pend) return hipSuccess;
+    const hipError_t e = launch_settle_cbar(PendingCbar{L.pend, L.npend, sc}, L.g.ncell, P->stream);
+    L.pend = nullptr;
+    return e;
+}
+
 // `count` sweeps of level l, the first from phi + the prolonged coarse correction
 // when `pro` is given: one launch per sweep, or per two on the brick schedule
 static hipError_t smooth_level_n(Plan* P, GridState& G, int l, int count, const ProlongIn* pro = nullptr) {
     LevelBuf& L = G.lev[l];
     const SmoothCfg cfg = level_schedule(P, l, L.g);
     const int per = cfg.pipe == PIPE_BRICK ? 2 : 1;
+    if (count > 0 && per == 1) {
+        hipError_t e = settle_cbar(P, L, L.sc);
+        if (e != hipSuccess) return e;
+    }
     for (int s = 0; s < count;) {
         const int n = std::min(per, count - s);
+        const PendingCbar pend{L.pend, L.npend, L.sc};   // taken up by the first launch
+        L.pend = nullptr;
         hipError_t e = launch_smooth(L.g, P->coef, L.phi[L.cur], L.phi[L.cur ^ 1], L.delta, level_f(P, G, l), L.sc,
-                                     cfg, P->stream, s == 0 ? pro : nullptr, n);
+                                     cfg, P->stream, s == 0 ? pro : nullptr, n, &pend);
         L.cur ^= 1;
         P->cell_updates += n * L.g.ncell;
         if (l == 0) P->finest_sweeps += n;
@@ -311,6 +331,8 @@ static hipError_t tail_cycle(Plan* P, GridState& G, int l) {
     a.phi = L.phi[L.cur];
     a.f = level_f(P, G, l);
     a.sc = L.sc;
+    a.pend = PendingCbar{L.pend, L.npend, L.sc};
+    L.pend = nullptr;
     a.c = P->coef;
     a.nu1 = pre_sweeps(P, l); a.nu2 = post_sweeps(P, l); a.ncoarse = P->ncoarse;
     return launch_tail(a, P->stream);
@@ -336,6 +358,26 @@ static hipError_t vcycle_head(Plan* P, GridState& G, int l, NormOut* norm) {
     if (l == 0 && (e = sweep_mark(P, false, nu1)) != hipSuccess) return e;
     LevelBuf& C = G.lev[l + 1];
     C.cur = 0;
+    if ((e = settle_cbar(P, L, L.sc)) != hipSuccess) return e;   // (without pre-sweeps)
+    if (one_launch_head(G, l)) {
+        if ((e = launch_head(L.g, C.g, P->coef, L.phi[L.cur], L.delta, level_f(P, G, l), L.sc, C.delta, C.phi[0],
+                             C.phiold, C.f, norm != nullptr, L.sums, C.sums_c, P->stream)) != hipSuccess)
+            return e;
+        const int nh = head_blocks(L.g);
+        if (norm) {
+            if ((e = launch_finalize_pair(FinJob{L.sums, nh, 1, 0, L.g.ncell, L.sc, norm, nullptr},
+                                          FinJob{C.sums_c, nh, 1, 1, C.g.ncell, C.sc, norm, nullptr},
+                                          P->stream)) != hipSuccess)
+                return e;
+            C.pend = nullptr;
+        } else {
+            L.pend = L.sums;
+            C.pend = C.sums_c;
+            L.npend = C.npend = nh;
+        }
+        return level_mark(P, l, false);
+    }
+    C.pend = nullptr;
     int nb = 0, nbc = 0;
     if ((e = launch_residual_restrict(L.g, C.g, P->coef, L.phi[L.cur], L.delta, level_f(P, G, l), L.sc,
                                       C.phi[0], C.phiold, C.rd, P->partials, &nb, P->stream)) != hipSuccess)
@@ -389,6 +431,7 @@ static hipError_t vcycle(Plan* P, GridState& G, int l) {
     }
     if (l == last) {
         if ((e = level_mark(P, l, true)) != hipSuccess) return e;
+        L.pend = nullptr;   // (forms cbar from its own sums)
         e = launch_coarse_solve(L.g, P->coef, L.phi[L.cur], L.delta, level_f(P, G, l), L.sc,
                                 P->ncoarse, P->stream);
         P->cell_updates += (int64_t)P->ncoarse * L.g.ncell;
@@ -630,6 +673,7 @@ vmg_status solve(Plan* P, const double* delta, const double* ghost, const double
     for (auto& G : P->grids) {
         LevelBuf& L0 = G.lev[0];
         L0.cur = 0;
+        for (auto& L : G.lev) L.pend = nullptr;
         CKH(launch_copy_in(L0.g, delta + G.desc.offset, L0.delta, s));
         CKH(launch_copy_in(L0.g, phi + G.desc.offset, L0.phi[0], s));
         if (source) CKH(launch_copy_in(L0.g, source + G.desc.offset, L0.f, s));

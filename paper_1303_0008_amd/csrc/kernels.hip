@@ -14,6 +14,7 @@
 #include <type_traits>
 
 #include "brick.h"
+#include "head.h"
 
 namespace vmg {
 
@@ -28,6 +29,7 @@ struct SmoothArgs {
     const double* delta;
     const double* f;      // may be null
     const LevelScalars* sc;
+    PendingCbar pend;     // bricks: cbar still in these sums (part null: in sc)
     // prolongation folded into the sweep (periodic): pin += P(uc - oc) first
     Geom gc;
     const double* uc;     // null: no prolongation
@@ -69,8 +71,9 @@ struct SmoothK {
         inv_h4 = 1.0 / (h2 * h2);
         h2_6 = h2 * (1.0 / 6.0);
         kk = kink_k(h2);
-        cb_6 = periodic ? h2_6 * a.sc->cbar : 0.0;
+        cb_6 = periodic && !a.pend.part ? h2_6 * a.sc->cbar : 0.0;
     }
+    __device__ void set_cbar(double cbar) { cb_6 = h2_6 * cbar; }
     static constexpr int EB = 8;
     struct InPlane {
         __amdgpu_buffer_rsrc_t u;
@@ -168,8 +171,8 @@ __global__ void __launch_bounds__(BRICK_THREADS, (S == 2 && PRO) ? 2 : BRICK_WAV
     const int bx = b % nbx;
     b /= nbx;
     const int by = b % nby, bz = b / nby;
-    const SmoothK<HAS_F> k(a, a.g, true);
-    brick_sweeps<S, PRO>(k, a.g, bx * BB, by * BB, bz * BB);
+    SmoothK<HAS_F> k(a, a.g, true);
+    brick_sweeps<S, PRO>(k, a.g, bx * BB, by * BB, bz * BB, a.pend);
 }
 
 // One sweep of every Dirichlet grid of a batch at one level on BB^3 bricks:
@@ -184,7 +187,7 @@ __global__ void __launch_bounds__(BRICK_THREADS, BRICK_WAVES) k_smooth_brick_bat
         const int4 w = items[it];
         SmoothArgs a = proto;
         a.g = geoms[w.x];
-        const SmoothK<HAS_F> k(a, a.g, false);
+        SmoothK<HAS_F> k(a, a.g, false);
         brick_sweeps<1, false, 1, GHOSTS>(k, a.g, w.y * BB, w.z * BB, w.w * BB);
         __syncthreads();   // the next item's staging overwrites the LDS
     }
@@ -433,6 +436,102 @@ int resid_blocks(const Geom& g) {
 }
 
 // ---------------------------------------------------------------------------
+// Head of a cycle on a small periodic level (head.h).
+// ---------------------------------------------------------------------------
+struct HeadArgs {
+    Geom g, gc;
+    Coef c;
+    const double *phi, *delta, *f;   // fine level; f may be null
+    const LevelScalars* sc;
+    const double* delta_c;
+    double *phic, *phiold_c, *f_c;
+    double *part, *part_c;
+};
+
+template <bool HAS_F>
+struct HeadK {
+    using T = double;
+    using Cell = double;
+    struct Src {
+        double dl, f;
+    };
+    struct CSrc {
+        double dl;
+    };
+    const HeadArgs& a;
+    double inv_h2, inv_h4, inv_h2c, inv_h4c, cb;
+    __device__ explicit HeadK(const HeadArgs& args) : a(args) {
+        inv_h2 = 1.0 / (a.g.h * a.g.h);
+        inv_h4 = inv_h2 * inv_h2;
+        inv_h2c = 1.0 / (a.gc.h * a.gc.h);
+        inv_h4c = inv_h2c * inv_h2c;
+        cb = a.sc->cbar;
+    }
+    __device__ double load_cell(int64_t i) const { return a.phi[i]; }
+    __device__ Src load_src(int64_t i) const { return Src{a.delta[i], HAS_F ? a.f[i] : 0.0}; }
+    __device__ CSrc load_csrc(int64_t i) const { return CSrc{a.delta_c[i]}; }
+    __device__ double pair(double p, double q) const { return p + q; }
+    __device__ double eighth(double s) const { return 0.125 * s; }
+    __device__ double residual(const Nb& v, double pc, const Src& s, double (&acc)[R_NSLOT]) const {
+        double S;
+        bool gd;
+        const double Q = nl_root(v, s.dl, a.c, inv_h4, S, gd);
+        const double d = (S - 6.0 * pc) * inv_h2 - Q - s.f + cb;
+        acc[R_D2] += d * d;
+        acc[R_D1] += d;
+        acc[R_Q] += Q;
+        acc[R_F] += s.f;
+        acc[R_PHI] += pc;
+        acc[R_GUARD] += gd ? 1.0 : 0.0;
+        acc[R_NONFIN] += isfinite(d) ? 0.0 : 1.0;
+        return d;
+    }
+    __device__ void coarse(const Nb& v, double pc, double rd, double rf, const CSrc& s, int64_t i,
+                           double (&acc)[R_NSLOT]) const {
+        double S;
+        bool gd;
+        const double Q = nl_root(v, s.dl, a.c, inv_h4c, S, gd);
+        const double fh = (S - 6.0 * pc) * inv_h2c - Q - rd;
+        a.phic[i] = pc;
+        a.phiold_c[i] = pc;
+        a.f_c[i] = fh;
+        acc[R_Q] += Q;
+        acc[R_F] += fh;
+        const double tau = fh - rf;   // f^H - R f^h (see k_resid_tiled)
+        acc[R_D1] += tau;
+        acc[R_D2] += tau * tau;
+    }
+};
+
+template <bool NORM, bool HAS_F>
+__global__ void __launch_bounds__(HEAD_NT) k_head(HeadArgs a) {
+    const int nbx = (a.g.n0 + BB - 1) / BB, nby = (a.g.n1 + BB - 1) / BB;
+    int b = blockIdx.x;
+    const int bx = b % nbx;
+    b /= nbx;
+    const int by = b % nby, bz = b / nby;
+    const HeadK<HAS_F> k(a);
+    head_brick<NORM>(k, a.g, a.gc, bx * BB, by * BB, bz * BB, a.part, a.part_c);
+}
+
+int head_blocks(const Geom& g) { return ((g.n0 + BB - 1) / BB) * ((g.n1 + BB - 1) / BB) * ((g.n2 + BB - 1) / BB); }
+
+hipError_t launch_head(const Geom& gf, const Geom& gc, const Coef& c, const double* phi, const double* delta,
+                       const double* f, const LevelScalars* sc, const double* delta_c, double* phic,
+                       double* phiold_c, double* f_c, bool norm, double* part, double* part_c, hipStream_t s) {
+    if (gf.dir || gc.dir || gf.n0 != 2 * gc.n0 || gf.n1 != 2 * gc.n1 || gf.n2 != 2 * gc.n2 ||
+        gf.ncell > HEAD_CELLS)
+        return hipErrorInvalidValue;
+    const HeadArgs a{gf, gc, c, phi, delta, f, sc, delta_c, phic, phiold_c, f_c, part, part_c};
+    const dim3 nb(head_blocks(gf)), nt(HEAD_NT);
+    if (norm && f) hipLaunchKernelGGL((k_head<true, true>), nb, nt, 0, s, a);
+    else if (norm) hipLaunchKernelGGL((k_head<true, false>), nb, nt, 0, s, a);
+    else if (f) hipLaunchKernelGGL((k_head<false, true>), nb, nt, 0, s, a);
+    else hipLaunchKernelGGL((k_head<false, false>), nb, nt, 0, s, a);
+    return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------
 // residual + restriction (8-child average of phi and d) in one pass
 // ---------------------------------------------------------------------------
 template <int DIR>
@@ -588,6 +687,17 @@ __global__ void __launch_bounds__(NT) k_finalize(FinJobs jobs) {
         out->n_nonfinite = tot[R_NONFIN];
         out->sum_q = tot[R_Q];
     }
+}
+
+// cbar of a level whose next pass cannot take the sums itself (one wave)
+__global__ void __launch_bounds__(64) k_settle_cbar(PendingCbar p, int64_t ncell) {
+    const double s = wave_sum(pending_share(p));
+    if (threadIdx.x == 0) p.sc->cbar = s / (double)ncell;
+}
+
+hipError_t launch_settle_cbar(const PendingCbar& p, int64_t ncell, hipStream_t s) {
+    hipLaunchKernelGGL(k_settle_cbar, dim3(1), dim3(64), 0, s, p, ncell);
+    return hipGetLastError();
 }
 
 // phi^h += P(phi^H - phiold^H): cell-centred trilinear, weights 3/4 and 1/4 per axis
@@ -1259,9 +1369,10 @@ static hipError_t brick_launch(const SmoothArgs& a, hipStream_t s) {
 
 hipError_t launch_smooth(const Geom& g, const Coef& c, const double* pin, double* pout,
                          const double* delta, const double* f, const LevelScalars* sc,
-                         SmoothCfg cfg, hipStream_t s, const ProlongIn* pro, int nsweeps) {
-    SmoothArgs a;
-    std::memset(&a, 0, sizeof(a));
+                         SmoothCfg cfg, hipStream_t s, const ProlongIn* pro, int nsweeps,
+                         const PendingCbar* pend) {
+    SmoothArgs a{};
+    if (pend) a.pend = *pend;
     a.g = g; a.c = c; a.pin = pin; a.pout = pout; a.delta = delta; a.f = f; a.sc = sc;
     if (cfg.pipe == PIPE_BRICK) {
         // periodic levels, one or two sweeps
@@ -1275,7 +1386,7 @@ hipError_t launch_smooth(const Geom& g, const Coef& c, const double* pin, double
         if (f) return nsweeps == 2 ? brick_launch<2, true>(a, s) : brick_launch<1, true>(a, s);
         return nsweeps == 2 ? brick_launch<2, false>(a, s) : brick_launch<1, false>(a, s);
     }
-    if (nsweeps != 1) return hipErrorInvalidValue;
+    if (nsweeps != 1 || a.pend.part) return hipErrorInvalidValue;
     a.zc = cfg.zc > 0 ? cfg.zc : 16;
     if (pro) {
         if (!can_fold_prolong(g, pro->gc, a.zc)) return hipErrorInvalidValue;
@@ -1556,8 +1667,7 @@ hipError_t launch_smooth_batch(const SmoothArgs& proto, const Geom* geoms, const
 hipError_t launch_smooth_batch_args(const Coef& c, const double* pin, double* pout, const double* delta,
                                     const double* f, SmoothCfg cfg, const Geom* geoms, const int4* items,
                                     int nitems, int max_blocks, hipStream_t s, const double* gref) {
-    SmoothArgs a;
-    std::memset(&a, 0, sizeof(a));
+    SmoothArgs a{};
     a.c = c; a.pin = pin; a.pout = pout; a.delta = delta; a.f = f; a.sc = nullptr; a.gref = gref;
     a.zc = cfg.zc > 0 ? cfg.zc : 16;
     return launch_smooth_batch(a, geoms, items, nitems, cfg, max_blocks, s);

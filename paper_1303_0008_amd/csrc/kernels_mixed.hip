@@ -19,6 +19,7 @@
 #include <cstring>
 
 #include "brick.h"
+#include "head.h"
 
 namespace vmg {
 
@@ -34,6 +35,7 @@ struct CorrArgs {
     const float* t0;
     const float* r;
     const LevelScalars* sc;   // inner cbar
+    PendingCbar pend;         // bricks: cbar still in these sums (part null: in sc)
     // prolongation folded into the sweep (periodic): ein += P(uc - oc) first
     Geom gc;
     const float* uc;          // null: no prolongation
@@ -73,8 +75,9 @@ struct CorrK {
           gref(a.gref) {
         h2_6 = c.h2 * (1.0f / 6.0f);
         kk = kink_k(c.h2);
-        cb_6 = periodic ? h2_6 * (float)a.sc->cbar : 0.0f;
+        cb_6 = periodic && !a.pend.part ? h2_6 * (float)a.sc->cbar : 0.0f;
     }
+    __device__ void set_cbar(double cbar) { cb_6 = h2_6 * (float)cbar; }
     static constexpr int EB = 4;
     struct InPlane {
         __amdgpu_buffer_rsrc_t e, p;
@@ -171,8 +174,8 @@ __global__ void __launch_bounds__(BRICK_THREADS, BRICK_WAVES) k_smooth_corr_bric
     const int bx = b % nbx;
     b /= nbx;
     const int by = b % nby, bz = b / nby;
-    const CorrK<ZERO_E> k(a, true);
-    brick_sweeps<S, PRO>(k, a.g, bx * BB, by * BB, bz * BB);
+    CorrK<ZERO_E> k(a, true);
+    brick_sweeps<S, PRO>(k, a.g, bx * BB, by * BB, bz * BB, a.pend);
 }
 
 // persistent sweep over a (grid, tile x, tile y, z chunk) work list (Dirichlet batches)
@@ -204,7 +207,7 @@ __global__ void __launch_bounds__(BRICK_THREADS, BRICK_WAVES) k_smooth_corr_bric
         a.g = geoms[w.x];
         a.c.a_ih4 = proto.c.alpha / (float)(a.g.h * a.g.h * a.g.h * a.g.h);
         a.c.h2 = (float)(a.g.h * a.g.h);
-        const CorrK<false> k(a, false);
+        CorrK<false> k(a, false);
         brick_sweeps<1, false, 1, GHOSTS>(k, a.g, w.y * BB, w.z * BB, w.w * BB);
         __syncthreads();   // the next item's staging overwrites the LDS
     }
@@ -721,6 +724,115 @@ __global__ void __launch_bounds__(NT) k_cast_tiled(CastArgs a) {
     block_store_partials(acc, a.partials);
 }
 
+// ---------------------------------------------------------------------------
+// Head of an inner cycle on a small periodic level (head.h).
+// ---------------------------------------------------------------------------
+struct HeadCorrArgs {
+    Geom g, gc;
+    CoefF c, cc;                        // fine and coarse level
+    Coef c64;
+    const float *e, *pt, *t0, *r;       // fine level
+    const LevelScalars* sc;
+    const double* delta_c;              // FRESH
+    float *ec, *eold_c, *pt_c, *t0_c, *r_c;
+    double *part, *part_c;
+};
+
+// FRESH: the coarse base state phi~ and t0 are formed and stored as well
+template <bool FRESH>
+struct HeadCorrK {
+    using T = float;
+    using Cell = float2;
+    struct Src {
+        float t0, r;
+    };
+    struct CSrc {
+        double dl;
+        float t0;
+    };
+    const HeadCorrArgs& a;
+    float inv_h2, inv_h2c, cb;
+    double inv_h4c;
+    __device__ explicit HeadCorrK(const HeadCorrArgs& args) : a(args) {
+        inv_h2 = 1.0f / a.c.h2;
+        inv_h2c = 1.0f / a.cc.h2;
+        inv_h4c = 1.0 / (a.gc.h * a.gc.h * a.gc.h * a.gc.h);
+        cb = (float)a.sc->cbar;
+    }
+    __device__ float2 load_cell(int64_t i) const { return make_float2(a.e[i], a.pt[i]); }
+    __device__ Src load_src(int64_t i) const { return Src{a.t0[i], a.r[i]}; }
+    __device__ CSrc load_csrc(int64_t i) const { return FRESH ? CSrc{a.delta_c[i], 0.0f} : CSrc{0.0, a.t0_c[i]}; }
+    __device__ float2 pair(float2 p, float2 q) const { return make_float2(p.x + q.x, p.y + q.y); }
+    __device__ float2 eighth(float2 s) const { return make_float2(0.125f * s.x, 0.125f * s.y); }
+    __device__ static void split(const NbT<float2>& v, NbT<float>& e, NbT<float>& p) {
+#define VMG_SPLIT(q) e.q = v.q.x; p.q = v.q.y;
+        VMG_SPLIT(xm) VMG_SPLIT(xp) VMG_SPLIT(ym) VMG_SPLIT(yp) VMG_SPLIT(zm) VMG_SPLIT(zp)
+        VMG_SPLIT(xpyp) VMG_SPLIT(xmym) VMG_SPLIT(xpym) VMG_SPLIT(xmyp)
+        VMG_SPLIT(xpzp) VMG_SPLIT(xmzm) VMG_SPLIT(xpzm) VMG_SPLIT(xmzp)
+        VMG_SPLIT(ypzp) VMG_SPLIT(ymzm) VMG_SPLIT(ypzm) VMG_SPLIT(ymzp)
+#undef VMG_SPLIT
+    }
+    __device__ float residual(const NbT<float2>& v, float2 centre, const Src& s, double (&acc)[R_NSLOT]) const {
+        NbT<float> e, p;
+        split(v, e, p);
+        float Se;
+        const float dQ = dQ_of(dq_corr(e, p, a.c.a_ih4, Se), s.t0, a.c);
+        acc[R_Q] += dQ;
+        acc[R_F] += s.r;
+        return (Se - 6.0f * centre.x) * inv_h2 - dQ - s.r + cb;
+    }
+    __device__ void coarse(const NbT<float2>& v, float2 centre, float rd, float, const CSrc& s, int64_t i,
+                           double (&acc)[R_NSLOT]) const {
+        NbT<float> e, p;
+        split(v, e, p);
+        float t0 = s.t0;
+        if (FRESH) {
+            Nb b;
+            b.xm = p.xm; b.xp = p.xp; b.ym = p.ym; b.yp = p.yp; b.zm = p.zm; b.zp = p.zp;
+            b.xpyp = p.xpyp; b.xmym = p.xmym; b.xpym = p.xpym; b.xmyp = p.xmyp;
+            b.xpzp = p.xpzp; b.xmzm = p.xmzm; b.xpzm = p.xpzm; b.xmzp = p.xmzp;
+            b.ypzp = p.ypzp; b.ymzm = p.ymzm; b.ypzm = p.ypzm; b.ymzp = p.ymzp;
+            const double D0 = base_discriminant(b, s.dl, a.c64, inv_h4c);
+            t0 = (float)(D0 >= 0.0 ? sqrt(D0) : -sqrt(-D0));
+            a.t0_c[i] = t0;
+            a.pt_c[i] = centre.y;
+        }
+        float Se;
+        const float dQ = dQ_of(dq_corr(e, p, a.cc.a_ih4, Se), t0, a.cc);
+        const float rh = (Se - 6.0f * centre.x) * inv_h2c - dQ - rd;
+        a.ec[i] = centre.x;
+        a.eold_c[i] = centre.x;
+        a.r_c[i] = rh;
+        acc[R_Q] += dQ;
+        acc[R_F] += rh;
+    }
+};
+
+template <bool FRESH>
+__global__ void __launch_bounds__(HEAD_NT) k_head_corr(HeadCorrArgs a) {
+    const int nbx = (a.g.n0 + BB - 1) / BB, nby = (a.g.n1 + BB - 1) / BB;
+    int b = blockIdx.x;
+    const int bx = b % nbx;
+    b /= nbx;
+    const int by = b % nby, bz = b / nby;
+    const HeadCorrK<FRESH> k(a);
+    head_brick<false>(k, a.g, a.gc, bx * BB, by * BB, bz * BB, a.part, a.part_c);
+}
+
+hipError_t launch_head_corr(const Geom& gf, const Geom& gc, const CoefF& c, const CoefF& cc, const Coef& c64,
+                            const float* e, const float* pt, const float* t0, const float* r, const LevelScalars* sc,
+                            const double* delta_c, float* ec, float* eold_c, float* pt_c, float* t0_c, float* r_c,
+                            bool fresh_base, double* part, double* part_c, hipStream_t s) {
+    if (gf.dir || gc.dir || gf.n0 != 2 * gc.n0 || gf.n1 != 2 * gc.n1 || gf.n2 != 2 * gc.n2 ||
+        gf.ncell > HEAD_CELLS)
+        return hipErrorInvalidValue;
+    const HeadCorrArgs a{gf, gc, c, cc, c64, e, pt, t0, r, sc, delta_c, ec, eold_c, pt_c, t0_c, r_c, part, part_c};
+    const dim3 nb(head_blocks(gf)), nt(HEAD_NT);
+    if (fresh_base) hipLaunchKernelGGL(k_head_corr<true>, nb, nt, 0, s, a);
+    else hipLaunchKernelGGL(k_head_corr<false>, nb, nt, 0, s, a);
+    return hipGetLastError();
+}
+
 struct CorrResArgs {
     Geom g, gc;
     CoefF c;
@@ -1121,9 +1233,10 @@ static hipError_t corr_launch(const CorrArgs& a, bool zero_in, bool defer, hipSt
 
 hipError_t launch_smooth_corr(const Geom& g, const CoefF& c, const float* ein, float* eout,
                               const float* pt, const float* t0, const float* r, const LevelScalars* sc,
-                              SmoothCfg cfg, hipStream_t s, bool zero_in, const ProlongInF* pro, int nsweeps) {
-    CorrArgs a;
-    std::memset(&a, 0, sizeof(a));
+                              SmoothCfg cfg, hipStream_t s, bool zero_in, const ProlongInF* pro, int nsweeps,
+                              const PendingCbar* pend) {
+    CorrArgs a{};
+    if (pend) a.pend = *pend;
     a.g = g; a.c = c; a.ein = ein; a.eout = eout; a.pt = pt; a.t0 = t0; a.r = r; a.sc = sc;
     if (cfg.pipe == PIPE_BRICK) {
         // periodic levels, one or two sweeps
@@ -1147,7 +1260,7 @@ hipError_t launch_smooth_corr(const Geom& g, const CoefF& c, const float* ein, f
 #undef VMG_CORR_BRICK
         return hipGetLastError();
     }
-    if (nsweeps != 1) return hipErrorInvalidValue;
+    if (nsweeps != 1 || a.pend.part) return hipErrorInvalidValue;
     a.zc = cfg.zc > 0 ? cfg.zc : 16;
     if (pro) {
         if (zero_in || !can_fold_prolong(g, pro->gc, a.zc)) return hipErrorInvalidValue;
@@ -1308,8 +1421,7 @@ hipError_t launch_smooth_corr_batch(const CoefF& c, const float* ein, float* eou
                                     const float* r, SmoothCfg cfg, const Geom* geoms, const int4* items, int nitems,
                                     int max_blocks, hipStream_t s, const float* gref) {
     if (nitems <= 0) return hipSuccess;
-    CorrArgs a;
-    std::memset(&a, 0, sizeof(a));
+    CorrArgs a{};
     a.c = c; a.ein = ein; a.eout = eout; a.pt = pt; a.t0 = t0; a.r = r; a.sc = nullptr;
     a.zc = cfg.zc > 0 ? cfg.zc : 16;
     const dim3 nb(std::min(nitems, max_blocks));

@@ -27,7 +27,7 @@
 // levels and values re-read from LDS it took 23.3 (32.8) and 26.8 us.
 #include <hip/hip_runtime.h>
 
-#include "device_common.h"
+#include "brick.h"
 
 namespace vmg {
 
@@ -176,6 +176,7 @@ struct Tail {
     const T* f;             // its right-hand side (may be null: zero)
     const T *pt, *t0;       // correction problem: base state and +-sqrt|D0|
     LevelScalars* sc;       // its cbar (in/out)
+    PendingCbar pend;       // ... or the sums it is still in
     Coef c;
     int nu1, nu2, ncoarse;
 };
@@ -186,7 +187,7 @@ __global__ void __launch_bounds__(T8_NT) k_tail8(Tail<typename K::T> a) {
     using T = typename K::T;
     __shared__ T u8[512], d8[512], pt8[K::BASE ? 512 : 1];
     __shared__ T u4[64], c4[64], pt4[K::BASE ? 64 : 1];
-    __shared__ double red[T8_NT / 64][2];
+    __shared__ double red[T8_NT / 64][2], psum;
     const int tid = threadIdx.x;
     const K k8(a.c, a.h), k4(a.c, 2.0 * a.h);
     // this thread's cells of the 8^3 level: colour 0 and 1 of one x pair of a row
@@ -211,10 +212,18 @@ __global__ void __launch_bounds__(T8_NT) k_tail8(Tail<typename K::T> a) {
     // the 4^3 level: one cell per lane of the first wave
     const TNbr o4 = tail_nbr(4, 4, 4, tid & 3, (tid >> 2) & 3, (tid >> 4) & 3);
     const double del4 = tid < 64 ? a.delta_c[tid] : 0.0;
-    T cb8 = (T)a.sc->cbar;
+    double share = 0.0;
+    T cb8 = T(0);
+    if (!a.pend.part) cb8 = (T)a.sc->cbar;
+    else if (tid < 64) share = pending_share(a.pend);
 #pragma unroll
     for (int q = 0; q < 2; ++q) u8[o8[q].centre()] = v8[q];
+    if (a.pend.part && tid < 64) {
+        share = wave_sum(share);
+        if (tid == 0) psum = share;
+    }
     __syncthreads();
+    if (a.pend.part) cb8 = (T)(psum / 512.0);
     if constexpr (K::BASE) {
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
@@ -456,6 +465,7 @@ hipError_t launch_tail(const TailArgs& a, hipStream_t s) {
     t.f = a.f;
     t.pt = t.t0 = nullptr;
     t.sc = a.sc;
+    t.pend = a.pend;
     t.c = a.c;
     t.nu1 = a.nu1; t.nu2 = a.nu2; t.ncoarse = a.ncoarse;
     return tail_launch<TailK>(t, a.nlev, a.n[1], s);
@@ -472,6 +482,7 @@ hipError_t launch_tail_corr(const TailCorrArgs& a, hipStream_t s) {
     t.pt = a.pt;
     t.t0 = a.t0;
     t.sc = a.sc;
+    t.pend = a.pend;
     t.c = a.c64;
     t.nu1 = a.nu1; t.nu2 = a.nu2; t.ncoarse = a.ncoarse;
     return tail_launch<TailCorrK>(t, a.nlev, a.n[1], s);

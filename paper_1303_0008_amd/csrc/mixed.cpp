@@ -63,10 +63,16 @@ hipError_t smooth_corr_level_n(Plan* P, GridState& G, int l, int count, bool zer
     const CoefF cf = make_coef_f(P->coef, L.g.h);
     const SmoothCfg cfg = level_schedule(P, l, L.g);
     const int per = cfg.pipe == PIPE_BRICK ? 2 : 1;
+    if (count > 0 && per == 1) {
+        hipError_t e = settle_cbar(P, L, L.scf);
+        if (e != hipSuccess) return e;
+    }
     for (int s = 0; s < count;) {
         const int n = std::min(per, count - s);
+        const PendingCbar pend{L.pend, L.npend, L.scf};   // taken up by the first launch
+        L.pend = nullptr;
         hipError_t e = launch_smooth_corr(L.g, cf, L.e[L.ecur], L.e[L.ecur ^ 1], L.pt, L.t0, L.r, L.scf, cfg,
-                                          P->stream, zero_in && s == 0, s == 0 ? pro : nullptr, n);
+                                          P->stream, zero_in && s == 0, s == 0 ? pro : nullptr, n, &pend);
         L.ecur ^= 1;
         P->cell_updates += n * L.g.ncell;
         if (l == 0) P->finest_sweeps += n;
@@ -117,6 +123,8 @@ static hipError_t inner_tail(Plan* P, GridState& G, int l) {
     a.pt = L.pt;
     a.t0 = L.t0;
     a.sc = L.scf;
+    a.pend = PendingCbar{L.pend, L.npend, L.scf};
+    L.pend = nullptr;
     a.c64 = P->coef;
     a.nu1 = pre_sweeps(P, l); a.nu2 = post_sweeps(P, l); a.ncoarse = P->ncoarse;
     return launch_tail_corr(a, P->stream);
@@ -138,6 +146,7 @@ static hipError_t inner_vcycle(Plan* P, GridState& G, int l, bool zero_e, bool f
     }
     if (l == last) {
         if ((e = level_mark(P, l, true)) != hipSuccess) return e;
+        L.pend = nullptr;   // (forms cbar from its own sums)
         e = launch_coarse_corr(L.g, cf, L.e[L.ecur], L.pt, L.t0, L.r, P->ncoarse, P->stream);
         P->cell_updates += (int64_t)P->ncoarse * L.g.ncell;
         if (e != hipSuccess) return e;
@@ -159,6 +168,21 @@ static hipError_t inner_vcycle(Plan* P, GridState& G, int l, bool zero_e, bool f
     LevelBuf& C = G.lev[l + 1];
     const CoefF cc = make_coef_f(P->coef, C.g.h);
     C.ecur = 0;
+    if ((e = settle_cbar(P, L, L.scf)) != hipSuccess) return e;   // (without pre-sweeps)
+    if (one_launch_head(G, l)) {
+        if ((e = launch_head_corr(L.g, C.g, cf, cc, P->coef, L.e[L.ecur], L.pt, L.t0, L.r, L.scf, C.delta, C.e[0],
+                                  C.eold, C.pt, C.t0, C.r, fresh_base, L.sums, C.sums_c, P->stream)) != hipSuccess)
+            return e;
+        L.pend = L.sums;
+        C.pend = C.sums_c;
+        L.npend = C.npend = head_blocks(L.g);
+        if ((e = level_mark(P, l, false)) != hipSuccess) return e;
+        if ((e = inner_vcycle(P, G, l + 1, false, fresh_base)) != hipSuccess) return e;
+        if ((e = level_mark(P, l, true)) != hipSuccess) return e;
+        if ((e = post_smooth_corr(P, G, l, post_sweeps(P, l))) != hipSuccess) return e;
+        return level_mark(P, l, false);
+    }
+    C.pend = nullptr;
     int nb = 0;
     const int periodic = L.g.dir ? 0 : 1;
     // restriction of e and d_e; the coarse base state phi~ is restricted in the same pass
@@ -198,6 +222,7 @@ static hipError_t cast_pass(Plan* P, GridState& G, bool update) {
                            L.delta, level0_f(P, G), L.sc, L.pt, L.t0, L.r, P->partials, &nb, P->stream);
     if (e != hipSuccess) return e;
     if (update) L.cur ^= 1;
+    L.pend = nullptr;   // the inner problem starts afresh
     if ((e = launch_finalize(P->partials, nb, L.g.ncell, L.g.dir ? 0 : 1, 2, L.sc, G.norm_dev, P->stream,
                              L.scf)) != hipSuccess)
         return e;

@@ -50,6 +50,15 @@ struct LevelScalars {
     double pad[7];
 };
 
+// cbar of a level not yet formed: block sums that add up to N cbar.  The level's
+// next brick sweep or coarse tail adds them up itself instead of a launch of its
+// own doing so.
+struct PendingCbar {
+    const double* part = nullptr;   // null: sc holds the constant
+    int rows = 0;                   // block sums
+    LevelScalars* sc = nullptr;     // receives it
+};
+
 // Host-visible result of a norm pass.
 struct NormOut {
     double rms;       // sqrt(mean d^2) with the updated cbar
@@ -115,6 +124,8 @@ inline SmoothCfg level_cfg(int n0, int n1, int n2, SmoothCfg c) {
 //   (LDS holds one 16-row block per CU): FP64 cycles of 96^3 / 160^3 / 256^3 take
 //   304 / 543 / 939 us so, 347 / 555 / 1051 us on 64 x 8 x 16 tiles everywhere.
 constexpr int64_t BRICK_CELLS = (int64_t)1 << 18;
+// levels whose cycle's head is one launch (timed on both sides in head.h)
+constexpr int64_t HEAD_CELLS = (int64_t)1 << 18;
 inline SmoothCfg default_march(int n0, int n1, int n2) {
     const int64_t xy = (int64_t)((n0 + TX - 1) / TX) * ((n1 + 15) / 16);
     for (int zc = 64; zc > 4; zc >>= 1) {
@@ -138,6 +149,7 @@ struct TailArgs {
     double* phi;                        // top-level state (in/out)
     const double* f;                    // top-level FAS rhs (may be null: zero)
     LevelScalars* sc;                   // top-level cbar (in/out)
+    PendingCbar pend;                   // ... or the sums it is still in
     Coef c;
     int nu1, nu2, ncoarse;
 };
@@ -153,6 +165,7 @@ struct TailCorrArgs {
     const float* pt;                    // top-level base state phi~
     const float* t0;                    // top-level +-sqrt|D0|
     LevelScalars* sc;                   // top-level inner cbar (in/out)
+    PendingCbar pend;                   // ... or the sums it is still in
     Coef c64;                           // FP64 coefficients (alpha, c8, kappa)
     int nu1, nu2, ncoarse;
 };
@@ -182,7 +195,16 @@ inline bool fold_prolong_pays(const Geom& g, int zc) { return zc >= 8 || g.ncell
 // nsweeps: sweeps of this launch (2 only with the brick schedule)
 hipError_t launch_smooth(const Geom& g, const Coef& c, const double* pin, double* pout,
                          const double* delta, const double* f, const LevelScalars* sc,
-                         SmoothCfg cfg, hipStream_t s, const ProlongIn* pro = nullptr, int nsweeps = 1);
+                         SmoothCfg cfg, hipStream_t s, const ProlongIn* pro = nullptr, int nsweeps = 1,
+                         const PendingCbar* pend = nullptr);
+// Head of a cycle on a small periodic level (head.h): residual of phi, its and phi's
+// 8-child averages, the coarse right-hand side f_c.  Block sums into part (fine
+// pass) and part_c (coarse pass), head_blocks(gf) each: rows of R_NSLOT with norm
+// (tau's among them), else the sums of Q + f.
+int head_blocks(const Geom& g);
+hipError_t launch_head(const Geom& gf, const Geom& gc, const Coef& c, const double* phi, const double* delta,
+                       const double* f, const LevelScalars* sc, const double* delta_c, double* phic,
+                       double* phiold_c, double* f_c, bool norm, double* part, double* part_c, hipStream_t s);
 hipError_t launch_residual_restrict(const Geom& gf, const Geom& gc, const Coef& c,
                                     const double* phi, const double* delta, const double* f,
                                     const LevelScalars* sc, double* phic, double* phiold_c,
@@ -212,6 +234,8 @@ struct FinJob {
 struct FinJobs {
     FinJob j[2];
 };
+// cbar of a level from the sums it is still in, by a launch of its own
+hipError_t launch_settle_cbar(const PendingCbar& p, int64_t ncell, hipStream_t s);
 // Two independent reductions in one launch (one block each).
 hipError_t launch_finalize_pair(const FinJob& a, const FinJob& b, hipStream_t s);
 hipError_t launch_prolong(const Geom& gf, const Geom& gc, double* phif, const double* phic,
@@ -280,7 +304,14 @@ hipError_t launch_mass_assign(const double* pos, int64_t np, int n0, int n1, int
 hipError_t launch_smooth_corr(const Geom& g, const CoefF& c, const float* ein, float* eout,
                               const float* pt, const float* t0, const float* r, const LevelScalars* sc,
                               SmoothCfg cfg, hipStream_t s, bool zero_in = false,
-                              const ProlongInF* pro = nullptr, int nsweeps = 1);
+                              const ProlongInF* pro = nullptr, int nsweeps = 1,
+                              const PendingCbar* pend = nullptr);
+// launch_head of the inner problem; fresh_base: also restricts phi~ and forms the
+// coarse t0 (else t0_c is read)
+hipError_t launch_head_corr(const Geom& gf, const Geom& gc, const CoefF& c, const CoefF& cc, const Coef& c64,
+                            const float* e, const float* pt, const float* t0, const float* r, const LevelScalars* sc,
+                            const double* delta_c, float* ec, float* eold_c, float* pt_c, float* t0_c, float* r_c,
+                            bool fresh_base, double* part, double* part_c, hipStream_t s);
 // ptc (may be null): receives the restricted base state phi~ of the coarse level
 hipError_t launch_rr_corr(const Geom& gf, const Geom& gc, const CoefF& c, const float* e, const float* pt,
                           const float* t0, const float* r, const LevelScalars* sc, float* ec, float* eold_c,

@@ -22,6 +22,10 @@ struct LevelBuf {
     double* delta = nullptr;
     double* rd = nullptr;                  // R d^h (coarse levels)
     LevelScalars* sc = nullptr;            // device scalars (cbar)
+    double* sums = nullptr;                // block sums of this level's head (periodic, small levels)
+    double* sums_c = nullptr;              // ... of the finer level's, for this level's right-hand side
+    const double* pend = nullptr;          // cbar still in these sums (null: in sc, or scf of the mixed path)
+    int npend = 0;                         // how many
     int cur = 0;                           // which phi[] holds the current iterate
     // mixed path (FP32 correction problem)
     float* e[2] = {nullptr, nullptr};      // correction, ping-pong
@@ -182,6 +186,12 @@ hipError_t smooth_level_public(Plan* P, GridState& G, int l, int count);
 // whether the first post-sweep of level l (schedule cfg) takes the prolongation
 // from coarse level gc
 bool fold_prolong_here(const Plan* P, const Geom& g, const Geom& gc, const SmoothCfg& cfg);
+// cbar of level L still in block sums: form it with a launch of its own (into sc)
+hipError_t settle_cbar(Plan* P, LevelBuf& L, LevelScalars* sc);
+// whether level l runs its cycle's head in one launch (head.h)
+inline bool one_launch_head(const GridState& G, int l) {
+    return l + 1 < (int)G.lev.size() && !G.lev[l].g.dir && G.lev[l].g.ncell <= HEAD_CELLS;
+}
 // schedule of the fused sweep on level l of a single-grid (periodic) plan
 SmoothCfg level_schedule(const Plan* P, int l, const Geom& g);
 // first level handled by the periodic coarse tail (FP64 plans), or -1
