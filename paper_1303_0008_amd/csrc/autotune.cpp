@@ -161,8 +161,10 @@ hipError_t sweep_level(Plan* P, int l, int n, bool post = false) {
 int swept_level_count(const Plan* P) {
     if (P->batched) {
         int n = 0;
+        // (levels the coarse tails took over keep accepting a schedule)
         for (size_t l = 0; l < P->blev.size(); ++l)
-            if (P->blev[l].nsitems > 0) n = (int)l + 1;
+            for (int c : P->blev[l].coarsest)
+                if (!c) n = (int)l + 1;
         return n;
     }
     const int tl = tail_level(P, P->grids[0]);
@@ -192,6 +194,7 @@ vmg_status autotune(Plan* P) {
         SmoothCfg best;
         // the brick schedule runs on the coarser levels of periodic plans and on
         // every level of Dirichlet batches
+        if (P->batched && P->blev[l].nsitems == 0) continue;   // run by the coarse tails
         if (cached(key, best) && (best.pipe != PIPE_BRICK || l > 0 || P->batched)) {
             P->tuned_from_cache = true;
             if (apply(P, l, best) != hipSuccess) st = fail(VMG_EHIP, "autotune: work list upload failed");

@@ -40,7 +40,7 @@ hipError_t batch_set_level_cfg(Plan* P, int l, SmoothCfg cfg) {
     B.cfg = cfg;
     std::vector<int4> items;
     for (size_t k = 0; k < B.members.size(); ++k) {
-        if (B.coarsest[k]) continue;
+        if (!B.swept[k]) continue;
         const Geom& g = P->grids[B.members[k]].lev[l].g;
         if (cfg.pipe == PIPE_BRICK) {   // (grid, brick x, brick y, brick z)
             const int bx = (g.n0 + BB_SIDE - 1) / BB_SIDE, by = (g.n1 + BB_SIDE - 1) / BB_SIDE;
@@ -76,7 +76,7 @@ hipError_t batch_build_smooth_items(Plan* P) {
         auto count = [&](const SmoothCfg& c) {
             int64_t n = 0;
             for (size_t k = 0; k < B.members.size(); ++k) {
-                if (B.coarsest[k]) continue;
+                if (!B.swept[k]) continue;
                 const Geom& g = P->grids[B.members[k]].lev[l].g;
                 n += (int64_t)((g.n0 + TX - 1) / TX) * ((g.n1 + c.ty - 1) / c.ty) * ((g.n2 + c.zc - 1) / c.zc);
             }
@@ -92,6 +92,65 @@ hipError_t batch_build_smooth_items(Plan* P) {
         CKE(batch_set_level_cfg(P, (int)l, cfg));
     }
     return hipSuccess;
+}
+
+// First level of grid G's coarse tail: the first one below the finest with at most
+// BATCH_TAIL_SIDE cells per axis (plans only hold grids whose coarsest level is
+// that small), or the number of levels for a grid of one level.
+static int tail_top(const GridState& G) {
+    for (size_t l = 1; l < G.lev.size(); ++l) {
+        const Geom& g = G.lev[l].g;
+        if (g.n0 <= BATCH_TAIL_SIDE && g.n1 <= BATCH_TAIL_SIDE && g.n2 <= BATCH_TAIL_SIDE) return (int)l;
+    }
+    return (int)G.lev.size();
+}
+
+// pools of a batch level as the tail of one precision reads them
+static void tail_pools(const BatchLevel& B, int q, TailGrid<double>& t) {
+    if (q == 0) {
+        t.u0 = B.phi[0];
+        t.u1 = B.phi[1];
+        t.f = B.f;
+    }
+    t.old[q] = B.phiold;
+    t.delta[q] = B.delta;
+}
+static void tail_pools(const BatchLevel& B, int q, TailGrid<float>& t) {
+    if (q == 0) {
+        t.u0 = B.e[0];
+        t.u1 = B.e[1];
+        t.f = B.r;
+    }
+    t.old[q] = B.eold;
+    t.pt[q] = B.pt;
+    t.t0[q] = B.t0;
+}
+
+// The coarse tails of the batch, longest first.
+template <typename T>
+static bool upload_tails(Plan* P, TailGrid<T>** dst) {
+    std::vector<TailGrid<T>> tails;
+    P->tail_cells[0] = P->tail_cells[1] = 0;
+    for (const GridState& G : P->grids) {
+        const int top = tail_top(G), nl = (int)G.lev.size() - top;
+        if (nl <= 0) continue;
+        if (nl > BATCH_TAIL_LEVELS) return false;   // (8, 4, 2: cannot happen)
+        TailGrid<T> t{};
+        t.nlev = nl;
+        for (int q = 0; q < BATCH_TAIL_LEVELS; ++q) {
+            t.g[q].n0 = t.g[q].n1 = 1;
+            t.g[q].h = 1.0;
+            if (q >= nl) continue;
+            t.g[q] = G.lev[top + q].g;
+            tail_pools(P->blev[top + q], q, t);
+            P->tail_cells[q == nl - 1 ? 1 : 0] += t.g[q].ncell;
+        }
+        tails.push_back(t);
+    }
+    std::stable_sort(tails.begin(), tails.end(),
+                     [](const TailGrid<T>& a, const TailGrid<T>& b) { return a.nlev > b.nlev; });
+    P->ntails = (int)tails.size();
+    return upload(P, dst, tails) == hipSuccess;
 }
 
 // Pools, per-level geometry lists and work lists.  Called from build_plan for
@@ -155,36 +214,43 @@ vmg_status build_batch(Plan* P) {
         }
         // geometry and work lists
         std::vector<Geom> geom, geom_fine, geomC;
-        std::vector<int2> cells, store, gh;
+        std::vector<int2> cells, store, gh, cycle;
         B.cells_A = B.cells_C = 0;
+        B.swept.assign(nm, 0);
         for (int k = 0; k < nm; ++k) {
             GridState& G = P->grids[B.members[k]];
             const Geom& g = G.lev[l].g;
+            const int top = tail_top(G);
             geom.push_back(g);
             cell_items(cells, k, g.ncell);
-            if (B.coarsest[k]) {
+            B.swept[k] = l < top && !B.coarsest[k];
+            if (B.swept[k]) {
+                B.cells_A += g.ncell;
+            } else if (l == 0) {           // a single level
                 geomC.push_back(g);
                 B.cells_C += g.ncell;
-            } else {
-                B.cells_A += g.ncell;
             }
+            if (l <= top) cell_items(cycle, k, g.ncell);
             if (l > 0) {
                 const Geom& gf = G.lev[l - 1].g;
                 geom_fine.push_back(gf);
                 cell_items(store, k, g.nstore);
-                cell_items(gh, k, ghost_count(g.n0, g.n1, g.n2));
+                if (B.swept[k]) cell_items(gh, k, ghost_count(g.n0, g.n1, g.n2));
             }
         }
+        B.ncycle = (int)cycle.size();
         B.ncells = (int)cells.size();
         B.nstore_items = (int)store.size();
         B.nghost_items = (int)gh.size();
         B.nC = (int)geomC.size();
         if (upload(P, &B.d_geom, geom) != hipSuccess || upload(P, &B.d_geom_fine, geom_fine) != hipSuccess ||
             upload(P, &B.d_geomC, geomC) != hipSuccess || upload(P, &B.d_cells, cells) != hipSuccess ||
-            upload(P, &B.d_store, store) != hipSuccess ||
+            upload(P, &B.d_store, store) != hipSuccess || upload(P, &B.d_cycle, cycle) != hipSuccess ||
             upload(P, &B.d_ghosts, gh) != hipSuccess)
             return fail(VMG_EHIP, "upload of batch work lists failed");
     }
+    if (mixed ? !upload_tails(P, &P->d_tails_f) : !upload_tails(P, &P->d_tails))
+        return fail(VMG_EHIP, "upload of the batch's coarse tails failed");
     // level-0 extras: caller offsets, ghost items, norm block ranges
     BatchLevel& B0 = P->blev[0];
     std::vector<int64_t> uoff, goff;
@@ -255,26 +321,36 @@ static hipError_t bsmooth(Plan* P, int l) {
     return hipSuccess;
 }
 
+// The coarse tails of the whole batch, once the cycle has descended to them (each
+// grid's restriction and right-hand side on its tail's top level are done, the
+// state in the first of the ping-pong buffers).
+static hipError_t btails(Plan* P) {
+    const int nu1 = pre_sweeps(P, 1), nu2 = post_sweeps(P, 1);
+    P->cell_updates += P->tail_cells[0] * (nu1 + nu2) + P->tail_cells[1] * P->ncoarse;
+    return P->mixed ? launch_tail_batch(P->d_tails_f, P->ntails, P->coef, nu1, nu2, P->ncoarse, P->stream)
+                    : launch_tail_batch(P->d_tails, P->ntails, P->coef, nu1, nu2, P->ncoarse, P->stream);
+}
+
 static hipError_t bcycle(Plan* P, int l) {
     BatchLevel& B = P->blev[l];
     hipStream_t s = P->stream;
     if (B.nC) {
-        // grids whose coarsest level is l: relax in place (result in both buffers)
+        // grids of one level (l = 0): relax in place (result in both buffers)
         CKE(launch_coarse_batch(B.d_geomC, B.nC, P->coef, B.phi[B.cur], B.phi[B.cur ^ 1], B.delta, bf(P, l),
-                                P->ncoarse, l > 0 ? B.phiold : nullptr, s));
+                                P->ncoarse, s));
         P->cell_updates += (int64_t)P->ncoarse * B.cells_C;
     }
-    if (l + 1 >= (int)P->blev.size() || B.cells_A == 0) return hipSuccess;
+    if (B.cells_A == 0) return btails(P);   // every grid has reached its tail
     if (l == 0) CKE(sweep_mark(P, true, pre_sweeps(P, l)));
     for (int q = 0; q < pre_sweeps(P, l); ++q) CKE(bsmooth(P, l));
     if (l == 0) CKE(sweep_mark(P, false, pre_sweeps(P, l)));
     BatchLevel& C = P->blev[l + 1];
     C.cur = 0;
-    CKE(launch_rr_batch(C.d_geom_fine, C.d_geom, C.d_cells, C.ncells, P->coef, B.phi[B.cur], B.delta, bf(P, l),
+    CKE(launch_rr_batch(C.d_geom_fine, C.d_geom, C.d_cycle, C.ncycle, P->coef, B.phi[B.cur], B.delta, bf(P, l),
                         C.phi[0], C.phiold, C.rd, s));
-    CKE(launch_fas_batch(C.d_geom, C.d_cells, C.ncells, P->coef, C.phi[0], C.delta, C.rd, C.f, s));
+    CKE(launch_fas_batch(C.d_geom, C.d_cycle, C.ncycle, P->coef, C.phi[0], C.delta, C.rd, C.f, s));
     CKE(bcycle(P, l + 1));
-    CKE(launch_prolong_batch(C.d_geom_fine, C.d_geom, C.d_cells, C.ncells, B.phi[B.cur], C.phi[C.cur],
+    CKE(launch_prolong_batch(C.d_geom_fine, C.d_geom, C.d_cycle, C.ncycle, B.phi[B.cur], C.phi[C.cur],
                              C.phiold, s));
     if (l == 0) CKE(sweep_mark(P, true, post_sweeps(P, l)));
     for (int q = 0; q < post_sweeps(P, l); ++q) CKE(bsmooth(P, l));
@@ -331,20 +407,20 @@ static hipError_t bcycle_corr(Plan* P, int l) {
     const CoefF cf = make_coef_f(P->coef, 1.0);
     if (B.nC) {
         CKE(launch_coarse_corr_batch(B.d_geomC, B.nC, cf, B.e[B.ecur], B.e[B.ecur ^ 1], B.pt, B.t0, B.r,
-                                     P->ncoarse, l > 0 ? B.eold : nullptr, s));
+                                     P->ncoarse, s));
         P->cell_updates += (int64_t)P->ncoarse * B.cells_C;
     }
-    if (l + 1 >= (int)P->blev.size() || B.cells_A == 0) return hipSuccess;
+    if (B.cells_A == 0) return btails(P);   // every grid has reached its tail
     if (l == 0) CKE(sweep_mark(P, true, pre_sweeps(P, l)));
     for (int q = 0; q < pre_sweeps(P, l); ++q) CKE(bsmooth_corr(P, l));
     if (l == 0) CKE(sweep_mark(P, false, pre_sweeps(P, l)));
     BatchLevel& C = P->blev[l + 1];
     C.ecur = 0;
-    CKE(launch_rr_corr_batch(C.d_geom_fine, C.d_geom, C.d_cells, C.ncells, cf, B.e[B.ecur], B.pt, B.t0, B.r,
+    CKE(launch_rr_corr_batch(C.d_geom_fine, C.d_geom, C.d_cycle, C.ncycle, cf, B.e[B.ecur], B.pt, B.t0, B.r,
                              C.e[0], C.eold, C.rdf, s));
-    CKE(launch_fas_corr_batch(C.d_geom, C.d_cells, C.ncells, cf, C.e[0], C.pt, C.t0, C.rdf, C.r, s));
+    CKE(launch_fas_corr_batch(C.d_geom, C.d_cycle, C.ncycle, cf, C.e[0], C.pt, C.t0, C.rdf, C.r, s));
     CKE(bcycle_corr(P, l + 1));
-    CKE(launch_prolong_corr_batch(C.d_geom_fine, C.d_geom, C.d_cells, C.ncells, B.e[B.ecur], C.e[C.ecur],
+    CKE(launch_prolong_corr_batch(C.d_geom_fine, C.d_geom, C.d_cycle, C.ncycle, B.e[B.ecur], C.e[C.ecur],
                                   C.eold, s));
     if (l == 0) CKE(sweep_mark(P, true, post_sweeps(P, l)));
     for (int q = 0; q < post_sweeps(P, l); ++q) CKE(bsmooth_corr(P, l));

@@ -768,44 +768,27 @@ __global__ void __launch_bounds__(NT) k_prolong_tiled(Geom gf, Geom gc, double* 
 // ---------------------------------------------------------------------------
 constexpr int CMAX = 10 * 10 * 10;   // storage of a padded 8^3 grid
 
-// phi (and, if given, phi_also) receive the result; storage starts at g.base.
-// With `old` (coarse Dirichlet levels) the ghosts follow the correction phi - old
-// by mirroring after every colour pass; without it they stay fixed.
+// phi (and, if given, phi_also) receive the result; storage starts at g.base.  On
+// a Dirichlet grid the ghosts are its fixed boundary values.
 template <int DIR>
 __device__ __forceinline__ void coarse_solve_body(Geom g, const Coef& c, double* phi, double* phi_also,
-                                                  const double* delta, const double* f, int sweeps,
-                                                  const double* old = nullptr) {
-    __shared__ double sphi[CMAX], sdel[CMAX], sf[CMAX], sold[CMAX];
+                                                  const double* delta, const double* f, int sweeps) {
+    __shared__ double sphi[CMAX], sdel[CMAX], sf[CMAX];
     __shared__ double red[NT / 64];
     const int tid = threadIdx.x, nt = blockDim.x;
     phi += g.base;
     delta += g.base;
     if (f) f += g.base;
     if (phi_also) phi_also += g.base;
-    if (old) old += g.base;
     for (int64_t e = tid; e < g.nstore; e += nt) {
         sphi[e] = phi[e];
         sdel[e] = delta[e];
         sf[e] = f ? f[e] : 0.0;
-        if (DIR && old) sold[e] = old[e];
     }
     __syncthreads();
     Geom lg = g;   // same indexing on the LDS copy
     lg.off0 -= g.base;
     lg.base = 0;
-    const int64_t nghost = DIR ? ghost_count_dev(g.n0, g.n1, g.n2) : 0;
-    auto refresh_ghosts = [&]() {
-        if (!DIR || !old) return;
-        for (int64_t q = tid; q < nghost; q += nt) {
-            int i, j, k;
-            ghost_coords(g.n0, g.n1, g.n2, q, i, j, k);
-            int sign = 1;
-            const int ir = mirror(i, g.n0, sign), jr = mirror(j, g.n1, sign), kr = mirror(k, g.n2, sign);
-            const int64_t gi = cell_index(lg, i, j, k), ii = cell_index(lg, ir, jr, kr);
-            sphi[gi] = sold[gi] + sign * (sphi[ii] - sold[ii]);
-        }
-        __syncthreads();
-    };
     const double h2 = g.h * g.h, inv_h4 = 1.0 / (h2 * h2);
     double sumf = 0.0;
     if (!DIR) {
@@ -865,7 +848,6 @@ __device__ __forceinline__ void coarse_solve_body(Geom g, const Coef& c, double*
             for (int q = 0; q < per && q < 2; ++q)
                 if (tid + (int64_t)q * nt < g.ncell && ni[q] >= 0) sphi[ni[q]] = nv[q];
             __syncthreads();
-            refresh_ghosts();
         }
     }
     for (int64_t e = tid; e < g.ncell; e += nt) {
@@ -875,14 +857,6 @@ __device__ __forceinline__ void coarse_solve_body(Geom g, const Coef& c, double*
         phi[li] = sphi[li];
         if (phi_also) phi_also[li] = sphi[li];
     }
-    if (DIR && old)
-        for (int64_t q = tid; q < nghost; q += nt) {
-            int i, j, k;
-            ghost_coords(g.n0, g.n1, g.n2, q, i, j, k);
-            const int64_t li = cell_index(lg, i, j, k);
-            phi[li] = sphi[li];
-            if (phi_also) phi_also[li] = sphi[li];
-        }
     __syncthreads();
 }
 
@@ -1220,12 +1194,12 @@ __global__ void __launch_bounds__(NT) k_finalize_batch(const double* __restrict_
     out[k].sum_q = tot[R_Q];
 }
 
-// coarsest levels of several grids, one block per grid; the result goes to both
-// ping-pong buffers so that either parity reads it
+// grids of one level, one block per grid; the result goes to both ping-pong buffers
+// so that either parity reads it
 __global__ void __launch_bounds__(NT) k_coarse_batch(const Geom* __restrict__ gs, Coef c, double* phi0,
                                                      double* phi1, const double* delta, const double* f,
-                                                     int sweeps, const double* old) {
-    coarse_solve_body<1>(gs[blockIdx.x], c, phi0, phi1, delta, f, sweeps, old);
+                                                     int sweeps) {
+    coarse_solve_body<1>(gs[blockIdx.x], c, phi0, phi1, delta, f, sweeps);
 }
 
 __global__ void k_copy_in_batch(const Geom* __restrict__ gs, const int64_t* __restrict__ uoff,
@@ -1722,10 +1696,9 @@ hipError_t launch_finalize_batch(const double* partials, const int* first, const
 }
 
 hipError_t launch_coarse_batch(const Geom* gs, int ngrids, const Coef& c, double* phi0, double* phi1,
-                               const double* delta, const double* f, int sweeps, const double* old,
-                               hipStream_t s) {
+                               const double* delta, const double* f, int sweeps, hipStream_t s) {
     if (ngrids <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_coarse_batch, dim3(ngrids), dim3(NT), 0, s, gs, c, phi0, phi1, delta, f, sweeps, old);
+    hipLaunchKernelGGL(k_coarse_batch, dim3(ngrids), dim3(NT), 0, s, gs, c, phi0, phi1, delta, f, sweeps);
     return hipGetLastError();
 }
 

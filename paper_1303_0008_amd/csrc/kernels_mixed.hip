@@ -323,10 +323,9 @@ __global__ void __launch_bounds__(NT) k_prolong_corr(Geom gf, Geom gc, float* __
 // coarsest inner level, whole grid in LDS
 template <int DIR>
 __device__ __forceinline__ void coarse_corr_body(Geom g, CoefF c, float* e, float* e_also, const float* pt,
-                                                 const float* t0, const float* r, int sweeps,
-                                                 const float* old = nullptr) {
+                                                 const float* t0, const float* r, int sweeps) {
     constexpr int CM = 1000;
-    __shared__ float se[CM], sp[CM], st[CM], sr[CM], so[CM];
+    __shared__ float se[CM], sp[CM], st[CM], sr[CM];
     __shared__ double red[NT / 64];
     const int tid = threadIdx.x, nt = blockDim.x;
     e += g.base;
@@ -334,7 +333,6 @@ __device__ __forceinline__ void coarse_corr_body(Geom g, CoefF c, float* e, floa
     t0 += g.base;
     r += g.base;
     if (e_also) e_also += g.base;
-    if (old) old += g.base;
     c.a_ih4 = c.alpha / (float)(g.h * g.h * g.h * g.h);
     c.h2 = (float)(g.h * g.h);
     g.off0 -= g.base;
@@ -344,22 +342,8 @@ __device__ __forceinline__ void coarse_corr_body(Geom g, CoefF c, float* e, floa
         sp[q] = pt[q];
         st[q] = t0[q];
         sr[q] = r[q];
-        if (DIR && old) so[q] = old[q];
     }
     __syncthreads();
-    const int64_t nghost = DIR ? ghost_count_dev(g.n0, g.n1, g.n2) : 0;
-    auto refresh_ghosts = [&]() {
-        if (!DIR || !old) return;
-        for (int64_t q = tid; q < nghost; q += nt) {
-            int i, j, k;
-            ghost_coords(g.n0, g.n1, g.n2, q, i, j, k);
-            int sign = 1;
-            const int ir = mirror(i, g.n0, sign), jr = mirror(j, g.n1, sign), kr = mirror(k, g.n2, sign);
-            const int64_t gi = cell_index(g, i, j, k), ii = cell_index(g, ir, jr, kr);
-            se[gi] = so[gi] + (float)sign * (se[ii] - so[ii]);
-        }
-        __syncthreads();
-    };
     const float h2 = c.h2;
     double sumr = 0.0;
     if (!DIR) {
@@ -419,7 +403,6 @@ __device__ __forceinline__ void coarse_corr_body(Geom g, CoefF c, float* e, floa
             for (int q = 0; q < 2; ++q)
                 if (ni[q] >= 0) se[ni[q]] = nv[q];
             __syncthreads();
-            refresh_ghosts();
         }
     }
     for (int64_t q = tid; q < g.ncell; q += nt) {
@@ -429,14 +412,6 @@ __device__ __forceinline__ void coarse_corr_body(Geom g, CoefF c, float* e, floa
         e[li] = se[li];
         if (e_also) e_also[li] = se[li];
     }
-    if (DIR && old)
-        for (int64_t q = tid; q < nghost; q += nt) {
-            int i, j, k;
-            ghost_coords(g.n0, g.n1, g.n2, q, i, j, k);
-            const int64_t li = cell_index(g, i, j, k);
-            e[li] = se[li];
-            if (e_also) e_also[li] = se[li];
-        }
     __syncthreads();
 }
 
@@ -446,11 +421,11 @@ __global__ void __launch_bounds__(NT) k_coarse_corr(Geom g, CoefF c, float* e, c
     coarse_corr_body<DIR>(g, c, e, nullptr, pt, t0, r, sweeps);
 }
 
-// coarsest inner levels of several Dirichlet grids, one block per grid; result in both e buffers
+// Dirichlet grids of one level, one block per grid; result in both e buffers
 __global__ void __launch_bounds__(NT) k_coarse_corr_batch(const Geom* __restrict__ gs, CoefF c, float* e0,
                                                           float* e1, const float* pt, const float* t0,
-                                                          const float* r, int sweeps, const float* old) {
-    coarse_corr_body<1>(gs[blockIdx.x], c, e0, e1, pt, t0, r, sweeps, old);
+                                                          const float* r, int sweeps) {
+    coarse_corr_body<1>(gs[blockIdx.x], c, e0, e1, pt, t0, r, sweeps);
 }
 
 // D0 = 1 + (8 alpha/3)(alpha Sigma0 + kappa delta) of the FP64 state (same arithmetic as nl_root)
@@ -1470,10 +1445,9 @@ hipError_t launch_prolong_corr_batch(const Geom* gfs, const Geom* gcs, const int
 }
 
 hipError_t launch_coarse_corr_batch(const Geom* gs, int ngrids, const CoefF& c, float* e0, float* e1,
-                                    const float* pt, const float* t0, const float* r, int sweeps, const float* old,
-                                    hipStream_t s) {
+                                    const float* pt, const float* t0, const float* r, int sweeps, hipStream_t s) {
     if (ngrids <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_coarse_corr_batch, dim3(ngrids), dim3(NT), 0, s, gs, c, e0, e1, pt, t0, r, sweeps, old);
+    hipLaunchKernelGGL(k_coarse_corr_batch, dim3(ngrids), dim3(NT), 0, s, gs, c, e0, e1, pt, t0, r, sweeps);
     return hipGetLastError();
 }
 

@@ -89,6 +89,7 @@ struct TailK {
         inv_h4 = inv_h2 * inv_h2;
         kk = kink_k(h2);
     }
+    __device__ void batch_coefs(double) {}
     // root Q of a cell, its neighbour sum S and discriminant D
     __device__ double root(const NbT<double>& v, const Cell& k, double& S, double& D) const {
         return nl_root_d(v, k.del, c, inv_h4, S, D);
@@ -121,6 +122,8 @@ struct TailCorrK {
         a_ih4 = (float)(c_.alpha * inv_h4);
         kk = kink_k(h2);
     }
+    // the coefficients as the batched passes round them
+    __device__ void batch_coefs(double h) { a_ih4 = c.alpha / (float)(h * h * h * h); }
     __device__ static void base_cell(const NbT<float>& p, Cell& k) {
         const float sx = p.xp + p.xm, sy = p.yp + p.ym, sz = p.zp + p.zm;
         k.dxy = 2.0f * (sx - sy);
@@ -435,6 +438,335 @@ __global__ void __launch_bounds__(NTH) k_tail1(Tail<typename K::T> a) {
 #pragma unroll
     for (int s = 0; s < NS; ++s)
         if (colour[s] >= 0) a.u[o[s].centre()] = val[s];
+}
+
+// ---------------------------------------------------------------------------
+// Coarse tails of a Dirichlet batch: every grid from its first level of at most 8
+// cells per axis down to its coarsest (three levels at most: 8, 4, 2), one
+// workgroup per grid, all grids of the batch in one launch at the bottom of the
+// cycle, whatever level their tails start on.  Level by level these took 7 to 10
+// launches of 5-11 us per level and cycle for a few hundred cells; here a thread
+// owns one pair of cells per level, as above, and everything the three levels read
+// from memory is requested before the first sweep.  96 grids of 16^3-64^3 (V(1,1),
+// FP32 correction): 19 us a cycle, against some 25 launches of 160 us in all.
+// The arithmetic is the level-by-level cycle's: ghosts follow the interior
+// (reference + odd reflection of the correction) after every sweep, on the
+// coarsest level after every colour; the correction prolonged is reflected the
+// same way at the faces.
+// ---------------------------------------------------------------------------
+namespace {
+
+// One level of a tail: cells in an LDS cube of pitch P (ghost shell included),
+// run by 256 threads or (WAVE) by one wave.  NG: ghosts per thread.
+template <typename K, int P, int NG, bool WAVE>
+struct BatchLev {
+    using T = typename K::T;
+    static constexpr int NTH = WAVE ? 64 : T8_NT;
+    K k;
+    T* u;
+    int n0, n1, n2;
+    int i[2], j, z;              // this thread's cells (colour 0 and 1 of a pair)
+    int c[2];                    // their LDS elements (-1: none)
+    T v[2], f[2];
+    typename K::Cell cell[2];
+    int gi[NG], gm[NG];          // ghosts: LDS element (-1: none), mirrored interior element
+    T gs[NG], og[NG], om[NG];    // sign, reference values of both
+
+    __device__ static int at(int x, int y, int z) { return ((z + 1) * P + y + 1) * P + x + 1; }
+    __device__ static void sync() {
+        if (WAVE) wave_sync();
+        else __syncthreads();
+    }
+    // (a level the grid does not have comes as 1 x 1 x 0 cells, h = 1)
+    __device__ BatchLev(const Coef& coef, const Geom& g, T* lds) : k(coef, g.h), u(lds), n0(g.n0), n1(g.n1), n2(g.n2) {
+        k.batch_coefs(g.h);
+        const unsigned t = threadIdx.x, h = (unsigned)(n0 + 1) >> 1, r = t / h;
+        j = (int)(r % (unsigned)n1);
+        z = (int)(r / (unsigned)n1);
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            i[q] = 2 * (int)(t - r * h) + ((j + z + q) & 1);
+            c[q] = z < n2 && i[q] < n0 ? at(i[q], j, z) : -1;
+            v[q] = f[q] = T(0);
+            cell[q] = typename K::Cell{};
+        }
+    }
+    __device__ int64_t element(const Geom& g, int q) const { return small_index(g, i[q], j, z); }
+    // ghosts: places, signs and their references from the pool
+    __device__ void init_ghosts(const Geom& g, const T* __restrict__ old) {
+        const int count = (int)ghost_count_dev(n0, n1, n2);
+#pragma unroll
+        for (int q = 0; q < NG; ++q) {
+            const int e = threadIdx.x + q * NTH;
+            gi[q] = -1;
+            if (e >= count) continue;
+            int x, y, w;
+            ghost_coords_t<unsigned>(n0, n1, n2, e, x, y, w);
+            int sign = 1;
+            const int mx = mirror(x, n0, sign), my = mirror(y, n1, sign), mz = mirror(w, n2, sign);
+            gi[q] = at(x, y, w);
+            gm[q] = at(mx, my, mz);
+            gs[q] = (T)sign;
+            og[q] = old[small_index(g, x, y, w)];
+        }
+    }
+    // the references of the mirrored cells: ref(x, y, z), or a cube of this pitch
+    template <typename R>
+    __device__ void ghost_refs(R&& ref) {
+#pragma unroll
+        for (int q = 0; q < NG; ++q)
+            if (gi[q] >= 0) om[q] = ref(gm[q] % P - 1, (gm[q] / P) % P - 1, gm[q] / (P * P) - 1);
+    }
+    __device__ void ghost_refs_at(const T* cube) {
+#pragma unroll
+        for (int q = 0; q < NG; ++q)
+            if (gi[q] >= 0) om[q] = cube[gm[q]];
+    }
+    // ghosts at their references, interior from v
+    __device__ void store_all() {
+#pragma unroll
+        for (int q = 0; q < NG; ++q)
+            if (gi[q] >= 0) u[gi[q]] = og[q];
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+            if (c[q] >= 0) u[c[q]] = v[q];
+        sync();
+    }
+    __device__ void refresh() {
+#pragma unroll
+        for (int q = 0; q < NG; ++q)
+            if (gi[q] >= 0) u[gi[q]] = og[q] + gs[q] * (u[gm[q]] - om[q]);
+        sync();
+    }
+    __device__ void sweeps(int count, bool every_colour) {
+        for (int s = 0; s < count; ++s)
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                if (c[q] >= 0) {
+                    NbT<T> nb;
+                    brick_nb<P>(u, c[q], nb);
+                    v[q] = tail_update(k, nb, cell[q], v[q], f[q], T(0));
+                }
+                sync();
+                if (c[q] >= 0) u[c[q]] = v[q];
+                sync();
+                if (q == 1 || every_colour) refresh();
+            }
+    }
+    // L(u) - f of this thread's cell q
+    __device__ T residual(int q) const {
+        NbT<T> nb;
+        brick_nb<P>(u, c[q], nb);
+        T S, D;
+        const T Q = k.root(nb, cell[q], S, D);
+        return (S - T(6) * v[q]) * k.inv_h2 - Q - f[q];
+    }
+};
+
+// 8-child average from a fine cube of pitch P, at coarse cell (I, J, Z)
+template <int P, typename T>
+__device__ __forceinline__ T child_average(const T* a, int I, int J, int Z) {
+    T s = T(0);
+#pragma unroll
+    for (int m = 0; m < 8; ++m)
+        s += a[((2 * Z + (m >> 2) + 1) * P + 2 * J + ((m >> 1) & 1) + 1) * P + 2 * I + (m & 1) + 1];
+    return T(0.125) * s;
+}
+
+// trilinear value at fine cell (x, y, z) of the coarse correction d (cube of pitch
+// P), reflected with a sign flip at the faces
+template <int P, typename T>
+__device__ __forceinline__ T prolong_at(const T* d, int n0, int n1, int n2, int x, int y, int z) {
+    T acc = T(0);
+#pragma unroll
+    for (int m = 0; m < 8; ++m) {
+        int sign = 1;
+        const int I = mirror((x >> 1) + ((m & 1) ? ((x & 1) ? 1 : -1) : 0), n0, sign);
+        const int J = mirror((y >> 1) + ((m & 2) ? ((y & 1) ? 1 : -1) : 0), n1, sign);
+        const int Z = mirror((z >> 1) + ((m & 4) ? ((z & 1) ? 1 : -1) : 0), n2, sign);
+        const T w = T(((m & 1) ? 0.25 : 0.75) * ((m & 2) ? 0.25 : 0.75) * ((m & 4) ? 0.25 : 0.75));
+        acc += w * ((T)sign * d[((Z + 1) * P + J + 1) * P + I + 1]);
+    }
+    return acc;
+}
+
+// phi~ of a level (ghosts included) into an LDS cube of pitch P; all loads first
+template <int P, int NTH>
+__device__ __forceinline__ void stage_base(const Geom& g, float* cube, const float* __restrict__ pt) {
+    constexpr int NL = (P * P * P + NTH - 1) / NTH;
+    const int m0 = g.n0 + 2, m1 = g.n1 + 2, n = (int)g.nstore;
+    float v[NL];
+#pragma unroll
+    for (int q = 0; q < NL; ++q) {
+        const int e = threadIdx.x + q * NTH;
+        v[q] = e < n ? pt[g.base + e] : 0.0f;
+    }
+#pragma unroll
+    for (int q = 0; q < NL; ++q) {
+        const int e = threadIdx.x + q * NTH, r = e / m0;
+        if (e < n) cube[((r / m1) * P + r % m1) * P + e % m0] = v[q];
+    }
+}
+
+template <int P, typename L>
+__device__ __forceinline__ void base_cells(L& lev, const float* cube) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+        if (lev.c[q] >= 0) {
+            NbT<float> p;
+            brick_nb<P>(cube, lev.c[q], p);
+            TailCorrK::base_cell(p, lev.cell[q]);
+        }
+}
+
+}  // namespace
+
+template <typename K>
+__global__ void __launch_bounds__(T8_NT) k_tail_batch(const TailGrid<typename K::T>* __restrict__ grids, Coef coef,
+                                                      int nu1, int nu2, int ncoarse) {
+    using T = typename K::T;
+    constexpr int PA = 10, PB = 6, PC = 4;
+    constexpr int CA = PA * PA * PA, CB = PB * PB * PB, CC = PC * PC * PC;
+    __shared__ T uA[CA], dA[CA], oA[CA], uB[CB], dB[CB], uC[CC];
+    __shared__ float pA[K::BASE ? CA : 1], pB[K::BASE ? CB : 1], pC[K::BASE ? CC : 1];
+    const TailGrid<T>& G = grids[blockIdx.x];
+    const int nlev = G.nlev, tid = threadIdx.x;
+    // the lower levels run on the first wave
+    const bool runB = nlev > 1 && tid < 64, runC = nlev > 2 && tid < 64;
+    BatchLev<K, PA, 2, false> A(coef, G.g[0], uA);
+    BatchLev<K, PB, 3, true> B(coef, G.g[1], uB);
+    BatchLev<K, PC, 1, true> C(coef, G.g[2], uC);
+    auto load = [&](auto& lev, int l) {
+        lev.init_ghosts(G.g[l], G.old[l]);
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+            if (lev.c[q] >= 0) {
+                const int64_t e = lev.element(G.g[l], q);
+                if constexpr (K::BASE) lev.cell[q].t0 = G.t0[l][e];
+                else lev.cell[q].del = G.delta[l][e];
+            }
+    };
+    T ref[2] = {T(0), T(0)};
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+        if (A.c[q] >= 0) {
+            const int64_t e = A.element(G.g[0], q);
+            A.v[q] = G.u0[e];
+            A.f[q] = G.f[e];
+            ref[q] = G.old[0][e];
+        }
+    load(A, 0);
+    if (runB) load(B, 1);
+    if (runC) load(C, 2);
+    if constexpr (K::BASE) {
+        stage_base<PA, T8_NT>(G.g[0], pA, G.pt[0]);
+        if (runB) stage_base<PB, 64>(G.g[1], pB, G.pt[1]);
+        if (runC) stage_base<PC, 64>(G.g[2], pC, G.pt[2]);
+    }
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+        if (A.c[q] >= 0) oA[A.c[q]] = ref[q];
+    __syncthreads();
+    A.ghost_refs_at(oA);
+    if constexpr (K::BASE) {
+        base_cells<PA>(A, pA);
+        if (runB) base_cells<PB>(B, pB);
+        if (runC) base_cells<PC>(C, pC);
+    }
+    A.store_all();
+    if (nlev == 1) {
+        A.sweeps(ncoarse, true);
+    } else {
+        A.sweeps(nu1, false);
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+            if (A.c[q] >= 0) dA[A.c[q]] = A.residual(q);
+        __syncthreads();
+        if (tid < 64) {
+            T oldB[2] = {T(0), T(0)};
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+                if (B.c[q] >= 0) {
+                    oldB[q] = child_average<PA>(uA, B.i[q], B.j, B.z);
+                    B.v[q] = oldB[q];
+                    B.f[q] = child_average<PA>(dA, B.i[q], B.j, B.z);   // R d, then f^H
+                }
+            B.ghost_refs([&](int x, int y, int z) { return child_average<PA>(uA, x, y, z); });
+            B.store_all();
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+                if (B.c[q] >= 0) B.f[q] = B.residual(q);
+            if (nlev == 2) {
+                B.sweeps(ncoarse, true);
+            } else {
+                B.sweeps(nu1, false);
+#pragma unroll
+                for (int q = 0; q < 2; ++q)
+                    if (B.c[q] >= 0) dB[B.c[q]] = B.residual(q);
+                wave_sync();
+                T oldC[2] = {T(0), T(0)};
+#pragma unroll
+                for (int q = 0; q < 2; ++q)
+                    if (C.c[q] >= 0) {
+                        oldC[q] = child_average<PB>(uB, C.i[q], C.j, C.z);
+                        C.v[q] = oldC[q];
+                        C.f[q] = child_average<PB>(dB, C.i[q], C.j, C.z);
+                    }
+                C.ghost_refs([&](int x, int y, int z) { return child_average<PB>(uB, x, y, z); });
+                C.store_all();
+#pragma unroll
+                for (int q = 0; q < 2; ++q)
+                    if (C.c[q] >= 0) C.f[q] = C.residual(q);
+                C.sweeps(ncoarse, true);
+#pragma unroll
+                for (int q = 0; q < 2; ++q)
+                    if (C.c[q] >= 0) uC[C.c[q]] = C.v[q] - oldC[q];
+                wave_sync();
+#pragma unroll
+                for (int q = 0; q < 2; ++q)
+                    if (B.c[q] >= 0) {
+                        B.v[q] += prolong_at<PC>(uC, C.n0, C.n1, C.n2, B.i[q], B.j, B.z);
+                        uB[B.c[q]] = B.v[q];
+                    }
+                wave_sync();
+                B.sweeps(nu2, false);
+            }
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+                if (B.c[q] >= 0) uB[B.c[q]] = B.v[q] - oldB[q];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+            if (A.c[q] >= 0) {
+                A.v[q] += prolong_at<PB>(uB, A.n0 >> 1, A.n1 >> 1, A.n2 >> 1, A.i[q], A.j, A.z);
+                uA[A.c[q]] = A.v[q];
+            }
+        __syncthreads();
+        A.sweeps(nu2, false);
+    }
+    // either ping-pong parity reads the result
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+        if (A.c[q] >= 0) {
+            const int64_t e = A.element(G.g[0], q);
+            G.u0[e] = A.v[q];
+            G.u1[e] = A.v[q];
+        }
+}
+
+hipError_t launch_tail_batch(const TailGrid<double>* grids, int ngrids, const Coef& c, int nu1, int nu2, int ncoarse,
+                             hipStream_t s) {
+    if (ngrids <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_tail_batch<TailK>, dim3(ngrids), dim3(T8_NT), 0, s, grids, c, nu1, nu2, ncoarse);
+    return hipGetLastError();
+}
+
+hipError_t launch_tail_batch(const TailGrid<float>* grids, int ngrids, const Coef& c, int nu1, int nu2, int ncoarse,
+                             hipStream_t s) {
+    if (ngrids <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_tail_batch<TailCorrK>, dim3(ngrids), dim3(T8_NT), 0, s, grids, c, nu1, nu2, ncoarse);
+    return hipGetLastError();
 }
 
 // nlev levels from the one `a` describes, `next` the cells of the one below it

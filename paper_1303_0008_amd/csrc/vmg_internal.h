@@ -170,6 +170,24 @@ struct TailCorrArgs {
     int nu1, nu2, ncoarse;
 };
 hipError_t launch_tail_corr(const TailCorrArgs& a, hipStream_t s);
+// Coarse tails of a Dirichlet batch: each grid from its first level (below the
+// finest) of at most BATCH_TAIL_SIDE cells per axis down to its coarsest.
+constexpr int BATCH_TAIL_SIDE = 8;
+constexpr int BATCH_TAIL_LEVELS = 3;    // 8, 4 and 2 cells (a Dirichlet axis keeps 2)
+template <typename T>
+struct TailGrid {
+    Geom g[BATCH_TAIL_LEVELS];          // levels it does not have: 1 x 1 x 0 cells, h = 1
+    int nlev;
+    T *u0, *u1;                         // top level's state: read from u0, written to both
+    const T* f;                         // its right-hand side
+    const T* old[BATCH_TAIL_LEVELS];    // R u of the top level; ghost references of all
+    const double* delta[BATCH_TAIL_LEVELS];                        // FP64 problem
+    const T *pt[BATCH_TAIL_LEVELS], *t0[BATCH_TAIL_LEVELS];        // correction problem
+};
+hipError_t launch_tail_batch(const TailGrid<double>* grids, int ngrids, const Coef& c, int nu1, int nu2, int ncoarse,
+                             hipStream_t s);
+hipError_t launch_tail_batch(const TailGrid<float>* grids, int ngrids, const Coef& c, int nu1, int nu2, int ncoarse,
+                             hipStream_t s);
 
 // ---- launchers (kernels.hip) --------------------------------------------
 // Coarse correction prolonged inside a sweep: the sweep starts from
@@ -368,8 +386,7 @@ hipError_t launch_norm_batch(const Geom* gs, const int2* items, int nitems, cons
 hipError_t launch_finalize_batch(const double* partials, const int* first, const Geom* gs, int ngrids,
                                  NormOut* out, hipStream_t s);
 hipError_t launch_coarse_batch(const Geom* gs, int ngrids, const Coef& c, double* phi0, double* phi1,
-                               const double* delta, const double* f, int sweeps, const double* old,
-                               hipStream_t s);
+                               const double* delta, const double* f, int sweeps, hipStream_t s);
 hipError_t launch_ghost_refresh_batch(const Geom* gs, const int2* items, int nitems, double* u, const double* ref,
                                       hipStream_t s);
 hipError_t launch_ghost_refresh_batch_f(const Geom* gs, const int2* items, int nitems, float* u, const float* ref,
@@ -399,8 +416,7 @@ hipError_t launch_fas_corr_batch(const Geom* gs, const int2* items, int nitems, 
 hipError_t launch_prolong_corr_batch(const Geom* gfs, const Geom* gcs, const int2* items, int nitems, float* ef,
                                      const float* ec, const float* eold_c, hipStream_t s);
 hipError_t launch_coarse_corr_batch(const Geom* gs, int ngrids, const CoefF& c, float* e0, float* e1,
-                                    const float* pt, const float* t0, const float* r, int sweeps, const float* old,
-                                    hipStream_t s);
+                                    const float* pt, const float* t0, const float* r, int sweeps, hipStream_t s);
 hipError_t launch_cast_batch(const Geom* gs, const int2* items, int nitems, const Coef& c, const double* phi,
                              const double* delta, const double* f, float* pt, float* t0, float* r,
                              double* partials, hipStream_t s);

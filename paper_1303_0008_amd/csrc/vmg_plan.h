@@ -69,7 +69,11 @@ struct BatchLevel {
     SmoothCfg cfg{8, 16};            // schedule of the persistent smoother on this level
     int2* d_ghosts = nullptr;        // 256-value blocks of each member's ghost shell (levels >= 1)
     int nghost_items = 0;
-    int64_t cells_A = 0, cells_C = 0;
+    int64_t cells_A = 0, cells_C = 0;   // cells of the members swept here / of the coarsest solves
+    // the cycle's passes cover the members that have not entered their coarse tail
+    std::vector<int> swept;          // per member: smoothed on this level by the batch kernels
+    int2* d_cycle = nullptr;         // 256-cell blocks of the members in the cycle at this level
+    int ncycle = 0;
     int cur = 0, ecur = 0;
 };
 
@@ -138,6 +142,10 @@ struct Plan {
     int64_t* d_uoff = nullptr;       // caller offsets of each grid's cells
     int64_t* d_goff = nullptr;       // caller offsets of each grid's ghosts
     int2* d_gitems = nullptr;        // 256-value blocks of every grid's ghosts
+    TailGrid<double>* d_tails = nullptr;     // coarse tails of the batch (FP64 / mixed path)
+    TailGrid<float>* d_tails_f = nullptr;
+    int ntails = 0;
+    int64_t tail_cells[2] = {0, 0};  // tail cells above the coarsest levels / on them
     int bngitems = 0;
     int* d_first = nullptr;          // first norm block of each grid (+ end)
     int* d_first1 = nullptr;         // the same for level 1 (tau^h), when every grid has it

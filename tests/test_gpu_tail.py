@@ -32,3 +32,48 @@ def test_tail_equals_levels(prec, bound, n, nu, coarse):
             out.append(phi.cpu().numpy())
     assert np.abs(out[1]).max() > 0
     assert np.abs(out[0] - out[1]).max() <= bound * np.abs(out[1]).max()
+
+
+TAIL_GRIDS = [(16, 16, 16), (16, 8, 4), (10, 10, 10), (12, 12, 12), (4, 4, 4), (8, 8, 8), (32, 16, 8), (14, 10, 6),
+              (2, 2, 2), (7, 5, 3), (24, 20, 28), (48, 40, 56)]
+
+
+@pytest.fixture(scope="module")
+def tail_refs():
+    return {}
+
+
+@pytest.mark.parametrize("prec,bound", [("fp64", 1e-10), ("mixed", 1e-8)])
+@pytest.mark.parametrize("nu,coarse", [((2, 2), 8), ((1, 2), 2), ((0, 2), 3), ((2, 0), 4)])
+def test_batch_tails(oracle_mod, tail_refs, prec, bound, nu, coarse):
+    """Coarse tails of one, two and three levels that start one, two and three
+    levels below the finest, odd and uneven coarsest sizes, and grids without one
+    (a single level), in one batch: every grid reaches the oracle's solution."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1303_0008_amd import vmg as V
+    rng = np.random.Generator(np.random.PCG64(5))
+    h, off, goff = 1.0 / 512, 0, 0
+    grids, deltas, ghosts = [], [], []
+    for i, n in enumerate(TAIL_GRIDS):
+        deltas.append(I.lognormal(n, 900 + i, sigma=1.2))
+        ghosts.append(2e-5 * rng.standard_normal(oracle_mod.ghost_count(n)))
+        grids.append(V.make_grid(n, h, V.DIRICHLET, off, goff))
+        off += deltas[-1].size
+        goff += ghosts[-1].size
+    if not tail_refs:
+        for i, (d, g) in enumerate(zip(deltas, ghosts)):
+            tail_refs[i] = oracle_mod.solve(d, 0.1, 1.5, h=h, ghost=g)[0]
+    dt = torch.from_numpy(np.concatenate([d.ravel() for d in deltas])).to("cuda")
+    gt = torch.from_numpy(np.concatenate(ghosts)).to("cuda")
+    with V.Plan(grids, V.make_params(0.1, 1.5, 1e-12, 120, {"fp64": V.FP64, "mixed": V.MIXED}[prec],
+                                     flags=V.GRAPH)) as p:
+        p.set_cycle(nu1=nu[0], nu2=nu[1], coarse_sweeps=coarse)
+        phi = torch.zeros_like(dt)
+        p.solve(dt, phi, ghost=gt, allow_noconv=True)
+    phi = phi.cpu().numpy()
+    for i, g in enumerate(grids):
+        ref = tail_refs[i]
+        got = phi[g.offset:g.offset + ref.size].reshape(ref.shape)
+        assert np.abs(got - ref).max() <= bound * np.abs(ref).max(), TAIL_GRIDS[i]
