@@ -277,8 +277,7 @@ vmg_status vmg_total_force(const double *phi_newton, const double *phi, const in
  * particles.  The previous contents of delta are ignored.
  * workspace: device memory of at least vmg_mass_assign_workspace(n_particles,
  * n) bytes, 256-byte aligned, owned by the caller, contents ignored (it holds
- * the particles binned by 16^3-cell brick of the grid and each brick's
- * boundary sums); calls that share a workspace
+ * the particles binned by brick of the grid and each brick's boundary sums); calls that share a workspace
  * must be ordered on one stream.  Enqueued on `stream`; the caller owns every
  * buffer.  Errors: VMG_EINVAL (null pointer, n_particles outside
  * [1, 2^31 - 1], n < 1, n[1] or n[2] above 65535, unknown scheme, workspace
@@ -317,14 +316,16 @@ vmg_status vmg_mass_assign_region(const double *pos, int64_t n_particles, const 
  * on one GPU share that array: calls that overlap in time on one GPU (on
  * different streams, or from different threads) race and must be ordered by
  * the caller; each call rewrites every part of the array it reads.  Errors:
- * VMG_EINVAL (as vmg_mass_assign, and a call whose workspace,
- * vmg_mass_assign_workspace(n_particles, n), exceeds 64 MiB: e.g. a 128^3 grid
- * with more than about 4.8 M particles), VMG_EHIP. */
+ * VMG_EINVAL (as vmg_mass_assign, and a call whose smallest workspace, about 8
+ * bytes per particle plus 12 per cell, exceeds 64 MiB: e.g. a 128^3 grid with
+ * more than about 4.8 M particles), VMG_EHIP. */
 vmg_status vmg_mass_assign_noalloc(const double *pos, int64_t n_particles, const int32_t n[3], int32_t scheme,
                                    double *delta, hipStream_t stream);
 
-/* Workspace bytes vmg_mass_assign needs (about 8 bytes per particle plus 12
- * per grid cell), or -1 for arguments vmg_mass_assign rejects. */
+/* Workspace bytes vmg_mass_assign can use (about 8 bytes per particle plus 12
+ * per grid cell, 16 on grids below about 2 M cells), or -1 for arguments
+ * vmg_mass_assign rejects.  On those smaller grids a call also accepts 12 bytes
+ * per cell and then takes a slower path with the same result. */
 int64_t vmg_mass_assign_workspace(int64_t n_particles, const int32_t n[3]);
 
 /* Number of ghost values of a Dirichlet grid with n cells per axis. */

@@ -1168,12 +1168,12 @@ vmg_status vmg_mass_assign(const double* pos, int64_t n_particles, const int32_t
         return fail(VMG_EINVAL, "mass assignment needs 1 <= n_particles <= 2^31 - 1");
     if (!assign_args_ok(n_particles, n)) return fail(VMG_EINVAL, "mass assignment needs n >= 1 per axis");
     if (scheme != VMG_ASSIGN_CIC && scheme != VMG_ASSIGN_TSC) return fail(VMG_EINVAL, "unknown assignment scheme");
-    if (workspace_bytes < mass_assign_workspace(n_particles, n[0], n[1], n[2]) ||
+    if (workspace_bytes < mass_assign_workspace_min(n_particles, n[0], n[1], n[2]) ||
         reinterpret_cast<uintptr_t>(workspace) % 256 != 0)
         return fail(VMG_EINVAL, "mass assignment workspace too small or not 256-byte aligned");
     const double mean_count = (double)n_particles / ((double)n[0] * n[1] * n[2]);
     CKH(launch_mass_assign(pos, n_particles, n[0], n[1], n[2], scheme, true, 0.0, nullptr, mean_count, workspace,
-                           delta, stream));
+                           workspace_bytes, delta, stream));
     return VMG_OK;
 }
 
@@ -1185,7 +1185,7 @@ vmg_status vmg_mass_assign_noalloc(const double* pos, int64_t n_particles, const
         return fail(VMG_EINVAL, "mass assignment needs 1 <= n_particles <= 2^31 - 1");
     if (!assign_args_ok(n_particles, n)) return fail(VMG_EINVAL, "mass assignment needs n >= 1 per axis");
     if (scheme != VMG_ASSIGN_CIC && scheme != VMG_ASSIGN_TSC) return fail(VMG_EINVAL, "unknown assignment scheme");
-    const int64_t need = mass_assign_workspace(n_particles, n[0], n[1], n[2]);
+    const int64_t need = mass_assign_workspace_min(n_particles, n[0], n[1], n[2]);
     if (need > NOALLOC_SCRATCH_BYTES)
         return fail(VMG_EINVAL, "vmg_mass_assign_noalloc: the workspace this call needs (" + std::to_string(need) +
                                     " bytes) exceeds the static scratch of " +
@@ -1193,8 +1193,8 @@ vmg_status vmg_mass_assign_noalloc(const double* pos, int64_t n_particles, const
     void* work = nullptr;
     CKH(noalloc_scratch(&work));
     const double mean_count = (double)n_particles / ((double)n[0] * n[1] * n[2]);
-    CKH(launch_mass_assign(pos, n_particles, n[0], n[1], n[2], scheme, true, 0.0, nullptr, mean_count, work, delta,
-                           stream));
+    CKH(launch_mass_assign(pos, n_particles, n[0], n[1], n[2], scheme, true, 0.0, nullptr, mean_count, work,
+                           NOALLOC_SCRATCH_BYTES, delta, stream));
     return VMG_OK;
 }
 
@@ -1214,11 +1214,11 @@ vmg_status vmg_mass_assign_region(const double* pos, int64_t n_particles, const 
             return fail(VMG_EINVAL, "a region must leave at least 4 of its cells of the box uncovered per axis");
     }
     if (scheme != VMG_ASSIGN_CIC && scheme != VMG_ASSIGN_TSC) return fail(VMG_EINVAL, "unknown assignment scheme");
-    if (workspace_bytes < mass_assign_workspace(n_particles, n[0], n[1], n[2]) ||
+    if (workspace_bytes < mass_assign_workspace_min(n_particles, n[0], n[1], n[2]) ||
         reinterpret_cast<uintptr_t>(workspace) % 256 != 0)
         return fail(VMG_EINVAL, "mass assignment workspace too small or not 256-byte aligned");
-    CKH(launch_mass_assign(pos, n_particles, n[0], n[1], n[2], scheme, false, h, corner, mean_count, workspace, delta,
-                           stream));
+    CKH(launch_mass_assign(pos, n_particles, n[0], n[1], n[2], scheme, false, h, corner, mean_count, workspace,
+                           workspace_bytes, delta, stream));
     return VMG_OK;
 }
 

@@ -6,27 +6,31 @@
 // it, and contributions outside it are dropped.
 //
 // Both schemes touch the particle's nearest cell and its 26 neighbours at most,
-// so the grid is cut into bricks of BRICK^3 cells and every particle belongs to
-// the brick of its nearest cell:
-//   1. k_bin<0>       particles per brick: each workgroup takes a chunk of
-//                     particles, counts them per brick in an LDS hash table and
-//                     adds each nonzero count to one of the brick's global
-//                     counters (SUB per brick);
+// so the grid is cut into bricks of 16^3 cells (8^3 on small grids, so that they
+// fill the chip) and every particle belongs to the brick of its nearest cell:
+//   1. k_count        particles per brick: each workgroup counts a contiguous
+//                     range of particles in an LDS table with one counter per
+//                     brick and adds the nonzero ones to one of the brick's
+//                     global counters (SUB per brick); the brick of each particle
+//                     is kept, or (region) the particles that reach it are listed;
 //   2. k_scan_*       exclusive prefix sum of the counters;
-//   3. k_bin<1>       the same chunks again: each nonzero (chunk, brick) count
+//   3. k_place        the same ranges again: each nonzero (range, brick) count
 //                     reserves a range of that brick's slots with one atomic,
 //                     and the particle indices are written sorted by brick;
-//   4. k_bin_assign   one workgroup per brick (heaviest bricks first for the
-//                     triangular-shaped cloud): the brick and a one-cell halo
-//                     are accumulated in LDS and the region is copied to the
-//                     workspace;
+//   4. k_bin_assign   one workgroup per brick, or several where bricks are few
+//                     and full (heaviest bricks first for the triangular-shaped
+//                     cloud): the brick and a one-cell halo are accumulated in LDS
+//                     and the region goes to the workspace;
 //   5. k_gather       every cell sums the staged entries of the bricks that
 //                     reach it (one; up to 8 on the outer layer of a brick, 27
 //                     where bricks are one cell wide) and writes delta.
-// No global atomics touch the density, so the sums are formed in a fixed order.
+// Grids of more bricks than an LDS table holds count and place in chunks of 2048
+// particles with an LDS hash table instead (k_bin).
+// No global atomics touch the density.
 // Masses are 64-bit fixed point (2^-40 of a particle per unit): every
 // contribution is rounded once and all sums are integer, so the result does
 // not depend on the order of particles or of atomics.
+#include <algorithm>
 #include <mutex>
 
 #include "device_common.h"
@@ -37,14 +41,14 @@ namespace {
 
 constexpr double FIX_ONE = 1099511627776.0;           // 2^40
 constexpr double FIX_INV = 1.0 / 1099511627776.0;     // 2^-40
-constexpr int BRICK = 16;                             // cells per brick edge
-constexpr int REG = BRICK + 2;                        // brick + halo, LDS region edge
-constexpr int REGN = REG * REG * REG;
+constexpr int reg_edge(int B) { return B + 2; }        // brick of edge B + halo, LDS region edge
+constexpr int reg_cells(int B) { return reg_edge(B) * reg_edge(B) * reg_edge(B); }
 constexpr uint32_t NO_KEY = 0xffffffffu;
 
 struct AGrid {
     int n0, n1, n2;          // cells
     int b0, b1, b2;          // bricks per axis
+    int shift;               // log2 of the brick edge
     // refinement region (not periodic): cell size, corner of cell (0,0,0) and
     // n h + 2h per axis (offsets beyond it belong to the image below the corner)
     double h, cr[3], far[3];
@@ -97,7 +101,7 @@ __device__ __forceinline__ uint32_t brick_key(const AGrid& g, double x, double y
         c1 = min(max((int)f1, 0), g.n1 - 1);
         c2 = min(max((int)f2, 0), g.n2 - 1);
     }
-    return ((uint32_t)(c2 / BRICK) * g.b1 + (uint32_t)(c1 / BRICK)) * g.b0 + (uint32_t)(c0 / BRICK);
+    return ((uint32_t)(c2 >> g.shift) * g.b1 + (uint32_t)(c1 >> g.shift)) * g.b0 + (uint32_t)(c0 >> g.shift);
 }
 
 // round(a * b) as an integer, for 0 <= a * b < 2^51: the exact product plus
@@ -113,11 +117,159 @@ __global__ void __launch_bounds__(NT) k_fill_u32(uint32_t* __restrict__ p, int64
 }
 
 constexpr int ANT = 512;                              // threads of the brick accumulation
-constexpr int SUB = 16;                               // counters per brick (chunk ch uses ch % SUB)
+constexpr int SUB = 16;                               // counters per brick (range or chunk r uses r % SUB)
 constexpr int CHUNK_PER_THREAD = 8;
 constexpr int CHUNK = CHUNK_PER_THREAD * NT;          // particles per chunk
 constexpr int TAB = 2 * CHUNK;                        // LDS hash table entries (load <= 1/2)
 static_assert(TAB == 1 << 12, "the hash keeps the top 12 bits of the product");
+
+// Counting and placing with a counter per brick in LDS.  Block b takes particles
+// [b * per, (b + 1) * per).  Against the hashed chunks of k_bin a workgroup covers
+// up to 8 times as many particles per table, so unordered particles cost that much
+// fewer global atomics per brick, and no probing; ordered ones are counted a run of
+// equal bricks at a time either way.  Whole calls: 200^3 particles in random order
+// onto 200^3 cells (TSC) 800 -> 505 us, with 4096 ranges instead of 1024 788 us;
+// 256^3 lattice-ordered ones: k_count 104 us (403 MB read at 4.5 TB/s), k_place 39 us
+// against 49.  A region only keeps the particles that reach it: 7 M particles, 64^3
+// cells of a 384^3 box: k_count 28 us, k_place 6 us against 32 and 13 us.
+constexpr int CNT = 512;                              // threads
+constexpr int CNT_BLOCKS = 1024;
+constexpr int TAB_BRICKS = 1 << 14;                   // 64 KB of counters: two workgroups per CU
+
+// Runs of equal keys among the lanes of a wave: whether this lane is the first of
+// its run, that first lane, and (first lanes) the run's length.
+struct Run {
+    bool head;
+    int first, len;
+};
+__device__ __forceinline__ Run key_run(uint32_t key) {
+    const int lane = threadIdx.x & 63;
+    const uint32_t prev = (uint32_t)__shfl_up((int)key, 1);
+    Run r;
+    r.head = lane == 0 || key != prev;
+    const unsigned long long heads = __ballot(r.head), below = (2ull << lane) - 1ull;
+    r.first = 63 - __clzll(heads & below);
+    const unsigned long long after = heads & ~below;
+    r.len = (after ? __ffsll(after) - 1 : 64) - lane;
+    return r;
+}
+
+// PER: keys[p] receives particle p's brick.  Region: the block lists the particles
+// of its range that reach the region (few, as a rule) at the start of its range of
+// keys, and their number in listed[block].
+template <bool PER>
+__global__ void __launch_bounds__(CNT) k_count(AGrid g, const double* __restrict__ pos, int64_t np, int64_t per,
+                                               uint32_t nb, uint32_t* __restrict__ counter,
+                                               uint32_t* __restrict__ keys, uint32_t* __restrict__ listed) {
+    extern __shared__ uint32_t tab[];
+    __shared__ uint32_t n_listed;
+    for (uint32_t e = threadIdx.x; e < nb; e += CNT) tab[e] = 0u;
+    if (threadIdx.x == 0) n_listed = 0u;
+    __syncthreads();
+    const int64_t lo = blockIdx.x * per, hi = min(lo + per, np);
+    constexpr int U = 4;                              // particles in flight per thread
+    for (int64_t p0 = lo; p0 < hi; p0 += U * CNT) {
+        double x[U], y[U], z[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t p = p0 + u * CNT + threadIdx.x;
+            x[u] = y[u] = z[u] = __builtin_nan("");
+            if (p < hi) {
+                x[u] = pos[3 * p];
+                y[u] = pos[3 * p + 1];
+                z[u] = pos[3 * p + 2];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t p = p0 + u * CNT + threadIdx.x;
+            uint32_t key = NO_KEY;
+            if constexpr (PER) {
+                if (finite3(x[u], y[u], z[u])) key = brick_key<PER>(g, x[u], y[u], z[u]);
+                if (p < hi) keys[p] = key;
+            } else {
+                // most waves lie outside along z or y: one division, not three
+                // (a coordinate that is not finite fails the comparisons)
+                const double fz = floor(region_u(z[u], g.cr[2], g.far[2], g.h));
+                if (!__any(fz >= -1.0 && fz <= g.n2)) continue;   // (uniform over the wave)
+                const double fy = floor(region_u(y[u], g.cr[1], g.far[1], g.h));
+                if (!__any(fy >= -1.0 && fy <= g.n1)) continue;
+                if (finite3(x[u], y[u], z[u])) key = brick_key<PER>(g, x[u], y[u], z[u]);
+                const unsigned long long in = __ballot(key != NO_KEY);
+                if (in == 0) continue;
+                const int lane = threadIdx.x & 63;
+                uint32_t base = 0;
+                if (lane == 0) base = atomicAdd(&n_listed, (uint32_t)__popcll(in));
+                base = (uint32_t)__shfl((int)base, 0);
+                if (key != NO_KEY) keys[lo + base + (uint32_t)__popcll(in & ((1ull << lane) - 1ull))] = (uint32_t)p;
+            }
+            const Run r = key_run(key);
+            if (r.head && key != NO_KEY) atomicAdd(&tab[key], (uint32_t)r.len);
+        }
+    }
+    __syncthreads();
+    const uint32_t sub = blockIdx.x % SUB;
+    for (uint32_t e = threadIdx.x; e < nb; e += CNT)
+        if (tab[e]) atomicAdd(counter + (size_t)e * SUB + sub, tab[e]);
+    if (!PER && threadIdx.x == 0) listed[blockIdx.x] = n_listed;
+}
+
+// The particles of this block's range again (PER: their keys; region: the listed
+// ones): count, reserve, write.
+template <bool PER>
+__global__ void __launch_bounds__(CNT) k_place(AGrid g, const double* __restrict__ pos, int64_t np, int64_t per,
+                                               uint32_t nb, uint32_t* __restrict__ cursor,
+                                               const uint32_t* __restrict__ keys,
+                                               const uint32_t* __restrict__ listed, uint32_t* __restrict__ idx) {
+    extern __shared__ uint32_t tab[];
+    for (uint32_t e = threadIdx.x; e < nb; e += CNT) tab[e] = 0u;
+    __syncthreads();
+    const int64_t lo = blockIdx.x * per, hi = PER ? min(lo + per, np) : lo + listed[blockIdx.x];
+    if (!PER && lo == hi) return;
+    constexpr int U = 4;
+    auto load = [&](int64_t p0, uint32_t (&key)[U], uint32_t (&part)[U]) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t p = p0 + u * CNT + threadIdx.x;
+            key[u] = NO_KEY;
+            part[u] = (uint32_t)p;
+            if (p < hi) (PER ? key[u] : part[u]) = keys[p];
+        }
+        if constexpr (!PER) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int64_t q = part[u];
+                if (p0 + u * CNT + threadIdx.x < hi)
+                    key[u] = brick_key<PER>(g, pos[3 * q], pos[3 * q + 1], pos[3 * q + 2]);
+            }
+        }
+    };
+    for (int64_t p0 = lo; p0 < hi; p0 += U * CNT) {
+        uint32_t key[U], part[U];
+        load(p0, key, part);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const Run r = key_run(key[u]);
+            if (r.head && key[u] != NO_KEY) atomicAdd(&tab[key[u]], (uint32_t)r.len);
+        }
+    }
+    __syncthreads();
+    for (uint32_t e = threadIdx.x; e < nb; e += CNT)
+        if (tab[e]) tab[e] = atomicAdd(cursor + (size_t)e * SUB + blockIdx.x % SUB, tab[e]);
+    __syncthreads();
+    for (int64_t p0 = lo; p0 < hi; p0 += U * CNT) {
+        uint32_t key[U], part[U];
+        load(p0, key, part);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const Run r = key_run(key[u]);
+            uint32_t base = 0;
+            if (r.head && key[u] != NO_KEY) base = atomicAdd(&tab[key[u]], (uint32_t)r.len);
+            base = (uint32_t)__shfl((int)base, r.first);
+            if (key[u] != NO_KEY) idx[base + (uint32_t)((threadIdx.x & 63) - r.first)] = part[u];
+        }
+    }
+}
 
 // MODE 0: add every chunk's per-brick counts to counter[] and store each
 // particle's brick key.  MODE 1: reserve each chunk's range of every brick's
@@ -294,11 +446,60 @@ __global__ void __launch_bounds__(NT) k_scan_tiles(const uint32_t* __restrict__ 
     if (base + SCAN_PER_THREAD >= nc && base < nc) start[nc] = run;    // the thread holding the last counter
 }
 
-// Brick-local LDS index of a cell whose brick-local coordinates are l0, l1, l2
-// in [-1, BRICK].
-__device__ __forceinline__ int reg_index(int l0, int l1, int l2) { return ((l2 + 1) * REG + (l1 + 1)) * REG + (l0 + 1); }
+// The same in one launch of one block, for up to SCAN_ONE counters (a launch costs
+// more than one CU's scan of them): thread t takes `per` consecutive counters (a
+// multiple of 4), read twice.
+constexpr int SCAN_NT = 1024;
+constexpr int64_t SCAN_ONE = 1 << 14;
+__global__ void __launch_bounds__(SCAN_NT) k_scan_one(const uint32_t* __restrict__ count, int nc, int per,
+                                                      uint32_t* __restrict__ start, uint32_t* __restrict__ cursor) {
+    __shared__ uint32_t wsum[SCAN_NT / 64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lo = threadIdx.x * per;
+    const uint4* c4 = reinterpret_cast<const uint4*>(count);   // nc is a multiple of SUB
+    uint32_t sum = 0;
+#pragma unroll 4
+    for (int k = 0; k < per; k += 4)
+        if (lo + k < nc) {
+            const uint4 v = c4[(lo + k) >> 2];
+            sum += v.x + v.y + v.z + v.w;
+        }
+    uint32_t incl = sum;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t u = (uint32_t)__shfl_up((int)incl, o);
+        incl += lane >= o ? u : 0u;
+    }
+    if (lane == 63) wsum[wave] = incl;
+    __syncthreads();
+    uint32_t run = incl - sum;
+#pragma unroll
+    for (int q = 0; q < SCAN_NT / 64; ++q) run += q < wave ? wsum[q] : 0u;
+#pragma unroll 4
+    for (int k = 0; k < per; k += 4)
+        if (lo + k < nc) {
+            const uint4 v = c4[(lo + k) >> 2];
+            uint4 o;
+            o.x = run;
+            o.y = o.x + v.x;
+            o.z = o.y + v.y;
+            o.w = o.z + v.z;
+            run = o.w + v.w;
+            reinterpret_cast<uint4*>(start)[(lo + k) >> 2] = o;
+            reinterpret_cast<uint4*>(cursor)[(lo + k) >> 2] = o;
+        }
+    if (lo < nc && lo + per >= nc) start[nc] = run;
+}
+static_assert(SUB % 4 == 0, "counters come in fours");
 
-__device__ __forceinline__ bool in_reg(int l) { return (unsigned)(l + 1) <= (unsigned)(BRICK + 1); }
+// Brick-local LDS index of a cell whose brick-local coordinates are l0, l1, l2
+// in [-1, B].
+template <int B>
+__device__ __forceinline__ int reg_index(int l0, int l1, int l2) {
+    return ((l2 + 1) * reg_edge(B) + (l1 + 1)) * reg_edge(B) + (l0 + 1);
+}
+
+template <int B>
+__device__ __forceinline__ bool in_reg(int l) { return (unsigned)(l + 1) <= (unsigned)(B + 1); }
 
 // Per-axis local cells (brick-local coordinate of the first stencil cell) and
 // weights.  CIC: weights 1 - t, t on cells floor(u - 1/2) and the next; TSC:
@@ -355,19 +556,29 @@ __global__ void __launch_bounds__(ORD_NT) k_brick_order(const uint32_t* __restri
     }
 }
 
-template <int M, bool PER>
+// SPLIT: `split` workgroups share a brick's particles and add their regions to the
+// zeroed staging area; else a workgroup writes its brick's region.
+template <int M, bool PER, int B, bool SPLIT>
 __global__ void __launch_bounds__(ANT) k_bin_assign(AGrid g, const double* __restrict__ pos,
                                                    const uint32_t* __restrict__ start,
                                                    const uint32_t* __restrict__ idx,
-                                                   const uint32_t* __restrict__ order,
+                                                   const uint32_t* __restrict__ order, int split,
                                                    unsigned long long* __restrict__ stage) {
+    constexpr int REGN = reg_cells(B);
     __shared__ unsigned long long acc[REGN];
-    const int key = order ? (int)order[blockIdx.x] : (int)blockIdx.x;
+    const int item = SPLIT ? (int)blockIdx.x / split : (int)blockIdx.x;
+    const int key = order ? (int)order[item] : item;
+    uint32_t lo = start[(size_t)key * SUB], hi = start[(size_t)(key + 1) * SUB];
+    if (SPLIT) {
+        const uint32_t s = blockIdx.x % split, n = hi - lo;
+        hi = lo + (uint32_t)((uint64_t)n * (s + 1) / split);
+        lo += (uint32_t)((uint64_t)n * s / split);
+        if (lo == hi) return;
+    }
     const int bx = key % g.b0, by = (key / g.b0) % g.b1, bz = key / (g.b0 * g.b1);
-    const int o0 = bx * BRICK, o1 = by * BRICK, o2 = bz * BRICK;
+    const int o0 = bx * B, o1 = by * B, o2 = bz * B;
     for (int e = threadIdx.x; e < REGN; e += ANT) acc[e] = 0ull;
     __syncthreads();
-    const uint32_t lo = start[(size_t)key * SUB], hi = start[(size_t)(key + 1) * SUB];
     const int lane = threadIdx.x & 63;
     const int rx = lane % M, ry = (lane >> 4) % M;
     for (uint32_t t = lo + threadIdx.x; t < hi; t += ANT) {
@@ -400,12 +611,12 @@ __global__ void __launch_bounds__(ANT) k_bin_assign(AGrid g, const double* __res
 #pragma unroll
             for (int b = 0; b < M; ++b) {
                 const double wyz = wz[a] * wyr[b] * FIX_ONE;
-                const int r = reg_index(l0, l1 + oyr[b], l2 + a);
+                const int r = reg_index<B>(l0, l1 + oyr[b], l2 + a);
 #pragma unroll
                 for (int c = 0; c < M; ++c) {
                     // region: a stencil cell beyond the LDS halo lies outside
                     // the region; its contribution is dropped
-                    if (!PER && !(in_reg(l0 + oxr[c]) && in_reg(l1 + oyr[b]) && in_reg(l2 + a))) continue;
+                    if (!PER && !(in_reg<B>(l0 + oxr[c]) && in_reg<B>(l1 + oyr[b]) && in_reg<B>(l2 + a))) continue;
                     atomicAdd(&acc[r + oxr[c]], fix_round(wxr[c], wyz));
                 }
             }
@@ -413,7 +624,14 @@ __global__ void __launch_bounds__(ANT) k_bin_assign(AGrid g, const double* __res
     }
     __syncthreads();
     unsigned long long* st = stage + (size_t)key * REGN;
-    for (int e = threadIdx.x; e < REGN; e += ANT) st[e] = acc[e];
+    for (int e = threadIdx.x; e < REGN; e += ANT) {
+        if (!SPLIT) st[e] = acc[e];
+        else if (acc[e]) atomicAdd(st + e, acc[e]);
+    }
+}
+
+__global__ void __launch_bounds__(NT) k_fill_u64(unsigned long long* __restrict__ p, int64_t n) {
+    for (int64_t e = (int64_t)blockIdx.x * NT + threadIdx.x; e < n; e += (int64_t)gridDim.x * NT) p[e] = 0ull;
 }
 
 // The (brick, brick-local coordinate) pairs along one axis whose LDS region
@@ -421,15 +639,16 @@ __global__ void __launch_bounds__(ANT) k_bin_assign(AGrid g, const double* __res
 // of a brick the right (left) halo entry of the previous (next) brick, with
 // periodic wrap (a region has no brick before its first or after its last);
 // returns how many (1 to 3).
+template <int B>
 __device__ __forceinline__ int axis_sources(int i, int n, int nbrick, bool periodic, int (&b)[3], int (&l)[3]) {
-    const int bi = i / BRICK, li = i - bi * BRICK, w = min(BRICK, n - bi * BRICK);
+    const int bi = i / B, li = i - bi * B, w = min(B, n - bi * B);
     int m = 0;
     b[m] = bi;
     l[m++] = li;
     if (li == 0 && (periodic || bi > 0)) {
         const int bp = bi == 0 ? nbrick - 1 : bi - 1;
         b[m] = bp;
-        l[m++] = min(BRICK, n - bp * BRICK);
+        l[m++] = min(B, n - bp * B);
     }
     if (li == w - 1 && (periodic || bi < nbrick - 1)) {
         b[m] = bi == nbrick - 1 ? 0 : bi + 1;
@@ -440,42 +659,81 @@ __device__ __forceinline__ int axis_sources(int i, int n, int nbrick, bool perio
 
 // Every cell: the sum of the staged region entries of the bricks that reach it
 // (its own brick's entry, plus halo entries of neighbours for outer-layer
-// cells), converted to delta = q * scale - 1.  One block per row
-// (blockIdx.x = j, blockIdx.y = k), so the density is written in whole rows.
+// cells), converted to delta = q * scale - 1.  A block writes 64 columns of one
+// plane of a row of bricks (blockIdx.x = brick row and column tile, blockIdx.y =
+// k), so the staged plane of each brick is read through whole lines; a thread
+// takes B/4 rows of its column (that many loads in flight, its sources found
+// once).  256^3 cells: 85 us (325 MB at 3.8 TB/s); with a block per row of cells,
+// which read every line of the staged planes twice and found its sources for one
+// cell per thread, 139 us.
+constexpr int GCOLS = 64, GROUPS = NT / GCOLS;
+template <int B>
 __global__ void __launch_bounds__(NT) k_gather(AGrid g, bool periodic, const unsigned long long* __restrict__ stage,
                                                double scale, double* __restrict__ d) {
-    const int j = blockIdx.x, k = blockIdx.y;
-    int b1[3], l1[3], b2[3], l2[3];
-    const int m1 = axis_sources(j, g.n1, g.b1, periodic, b1, l1);
-    const int m2 = axis_sources(k, g.n2, g.b2, periodic, b2, l2);
-    double* row = d + ((int64_t)k * g.n1 + j) * g.n0;
-    for (int i = threadIdx.x; i < g.n0; i += NT) {
-        int b0[3], l0[3];
-        const int m0 = axis_sources(i, g.n0, g.b0, periodic, b0, l0);
-        unsigned long long q = 0ull;
-        for (int c = 0; c < m2; ++c)
-            for (int b = 0; b < m1; ++b)
-                for (int a = 0; a < m0; ++a) {
-                    const size_t key = ((size_t)b2[c] * g.b1 + b1[b]) * g.b0 + b0[a];
-                    q += stage[key * REGN + reg_index(l0[a], l1[b], l2[c])];
-                }
-        row[i] = (double)q * scale - 1.0;
-    }
+    constexpr int REG = reg_edge(B), REGN = reg_cells(B), RT = B / GROUPS;
+    const int tiles = (g.n0 + GCOLS - 1) / GCOLS;
+    const int by = blockIdx.x / tiles, k = blockIdx.y;
+    const int i = (blockIdx.x % tiles) * GCOLS + threadIdx.x % GCOLS;
+    const int r0 = threadIdx.x / GCOLS * RT;          // first of this thread's rows of the brick row
+    const int w = min(B, g.n1 - by * B);              // rows there are
+    if (i >= g.n0 || r0 >= w) return;
+    int b0[3], l0[3], b2[3], l2[3];
+    const int m0 = axis_sources<B>(i, g.n0, g.b0, periodic, b0, l0);
+    const int m2 = axis_sources<B>(k, g.n2, g.b2, periodic, b2, l2);
+    unsigned long long q[RT];
+#pragma unroll
+    for (int r = 0; r < RT; ++r) q[r] = 0ull;
+    for (int c = 0; c < m2; ++c)
+        for (int a = 0; a < m0; ++a) {
+            const unsigned long long* plane =
+                stage + (((size_t)b2[c] * g.b1) * g.b0 + b0[a]) * REGN + reg_index<B>(l0[a], 0, l2[c]);
+            const unsigned long long* own = plane + (size_t)by * g.b0 * REGN + r0 * REG;
+#pragma unroll
+            for (int r = 0; r < RT; ++r)
+                if (r0 + r < w) q[r] += own[r * REG];
+            // the first and last rows also take halo entries of the brick rows around
+#pragma unroll
+            for (int r = 0; r < RT; ++r) {
+                if (r0 + r >= w || (r0 + r != 0 && r0 + r != w - 1)) continue;
+                int b1[3], l1[3];
+                const int m1 = axis_sources<B>(by * B + r0 + r, g.n1, g.b1, periodic, b1, l1);
+                for (int b = 1; b < m1; ++b) q[r] += plane[(size_t)b1[b] * g.b0 * REGN + l1[b] * REG];
+            }
+        }
+    double* out = d + ((int64_t)k * g.n1 + by * B + r0) * g.n0 + i;
+#pragma unroll
+    for (int r = 0; r < RT; ++r)
+        if (r0 + r < w) out[(int64_t)r * g.n0] = (double)q[r] * scale - 1.0;
 }
 
 inline int64_t align256(int64_t b) { return (b + 255) & ~(int64_t)255; }
 
 }  // namespace
 
-int64_t mass_assign_bricks(int n0, int n1, int n2) {
-    return (int64_t)((n0 + BRICK - 1) / BRICK) * ((n1 + BRICK - 1) / BRICK) * ((n2 + BRICK - 1) / BRICK);
+static int64_t bricks_of(int n0, int n1, int n2, int B) {
+    return (int64_t)((n0 + B - 1) / B) * ((n1 + B - 1) / B) * ((n2 + B - 1) / B);
 }
 
-int64_t mass_assign_workspace(int64_t np, int n0, int n1, int n2) {
-    const int64_t nc = mass_assign_bricks(n0, n1, n2) * SUB;
+int64_t mass_assign_bricks(int n0, int n1, int n2) { return bricks_of(n0, n1, n2, 16); }
+
+static int64_t workspace_of(int64_t np, int n0, int n1, int n2, int B) {
+    const int64_t nb = bricks_of(n0, n1, n2, B), nc = nb * SUB;
     return 2 * align256(nc * 4) + align256((nc + 1) * 4) + align256((nc + SCAN_TILE - 1) / SCAN_TILE * 4) +
-           2 * align256(np * 4) + align256(mass_assign_bricks(n0, n1, n2) * REGN * 8) +
-           align256(mass_assign_bricks(n0, n1, n2) * 4);
+           2 * align256(np * 4) + align256(nb * reg_cells(B) * 8) + align256(nb * 4);
+}
+
+// Grids of fewer than 512 bricks of 16^3 cells (two per CU) are cut into 8^3 ones
+// where the workspace has room for their wider halos: 262144 particles onto 64^3
+// cells (CIC) take 34 us a call so, 51 us with 64 workgroups on 16^3 bricks, whose
+// accumulation alone was 17 us against 8.
+constexpr int64_t SMALL_BRICKS = 512;
+static bool small_grid(int n0, int n1, int n2) { return bricks_of(n0, n1, n2, 16) < SMALL_BRICKS; }
+
+int64_t mass_assign_workspace_min(int64_t np, int n0, int n1, int n2) { return workspace_of(np, n0, n1, n2, 16); }
+
+int64_t mass_assign_workspace(int64_t np, int n0, int n1, int n2) {
+    const int64_t need = workspace_of(np, n0, n1, n2, 16);
+    return small_grid(n0, n1, n2) ? std::max(need, workspace_of(np, n0, n1, n2, 8)) : need;
 }
 
 // Workspace of the allocation-free mass assignment: a file-scope device array
@@ -507,10 +765,25 @@ hipError_t noalloc_scratch(void** ptr) {
     return hipSuccess;
 }
 
+template <int M, bool PER, int B>
+static void assign_launch(const AGrid& g, const double* pos, const uint32_t* start, const uint32_t* idx,
+                          const uint32_t* order, int split, int64_t nb, unsigned long long* stage, hipStream_t s) {
+    if (split > 1) {
+        hipLaunchKernelGGL(k_fill_u64, dim3(grid_for(nb * reg_cells(B), 2048)), dim3(NT), 0, s, stage,
+                           nb * reg_cells(B));
+        hipLaunchKernelGGL((k_bin_assign<M, PER, B, true>), dim3((unsigned)(nb * split)), dim3(ANT), 0, s, g, pos,
+                           start, idx, order, split, stage);
+    } else {
+        hipLaunchKernelGGL((k_bin_assign<M, PER, B, false>), dim3((unsigned)nb), dim3(ANT), 0, s, g, pos, start, idx,
+                           order, split, stage);
+    }
+}
+
 hipError_t launch_mass_assign(const double* pos, int64_t np, int n0, int n1, int n2, int scheme, bool periodic,
-                              double h, const double* corner, double mean_count, void* work, double* delta,
-                              hipStream_t s) {
-    AGrid g{n0, n1, n2, (n0 + BRICK - 1) / BRICK, (n1 + BRICK - 1) / BRICK, (n2 + BRICK - 1) / BRICK, h, {0, 0, 0},
+                              double h, const double* corner, double mean_count, void* work, int64_t work_bytes,
+                              double* delta, hipStream_t s) {
+    const int B = small_grid(n0, n1, n2) && work_bytes >= workspace_of(np, n0, n1, n2, 8) ? 8 : 16;
+    AGrid g{n0, n1, n2, (n0 + B - 1) / B, (n1 + B - 1) / B, (n2 + B - 1) / B, B == 8 ? 3 : 4, h, {0, 0, 0},
             {0, 0, 0}};
     const int nn[3] = {n0, n1, n2};
     if (!periodic)
@@ -534,32 +807,68 @@ hipError_t launch_mass_assign(const double* pos, int64_t np, int n0, int n1, int
     uint32_t* idx = reinterpret_cast<uint32_t*>(w);
     w += align256(np * 4);
     unsigned long long* stage = reinterpret_cast<unsigned long long*>(w);
-    w += align256(nb * REGN * 8);
+    w += align256(nb * reg_cells(B) * 8);
     uint32_t* order = reinterpret_cast<uint32_t*>(w);
     const double scale = FIX_INV / mean_count;
-    const int chunks = grid_for((np + CHUNK - 1) / CHUNK * NT, 8192);
     hipLaunchKernelGGL(k_fill_u32, dim3(grid_for(nc)), dim3(NT), 0, s, count, nc);
-    if (periodic)
+    const bool table = nb <= TAB_BRICKS;
+    const int chunks = grid_for((np + CHUNK - 1) / CHUNK * NT, 8192);
+    // one range per block, whole iterations of four particles per thread
+    const int64_t iter = 4 * CNT, blocks = std::min<int64_t>(CNT_BLOCKS, (np + iter - 1) / iter);
+    const int64_t per = ((np + blocks - 1) / blocks + iter - 1) / iter * iter;
+    const dim3 ranges((unsigned)((np + per - 1) / per));
+    const size_t lds = (size_t)nb * 4;
+    // a region's list lengths wait in the staging area, which is written after them
+    uint32_t* listed = reinterpret_cast<uint32_t*>(stage);
+    static_assert(CNT_BLOCKS * 4 <= reg_cells(8) * 8, "room for the list lengths");
+    if (table && periodic)
+        hipLaunchKernelGGL(k_count<true>, ranges, dim3(CNT), lds, s, g, pos, np, per, (uint32_t)nb, count, keys, listed);
+    else if (table)
+        hipLaunchKernelGGL(k_count<false>, ranges, dim3(CNT), lds, s, g, pos, np, per, (uint32_t)nb, count, keys, listed);
+    else if (periodic)
         hipLaunchKernelGGL((k_bin<0, true>), dim3(chunks), dim3(NT), 0, s, g, pos, np, count, keys, idx);
     else
         hipLaunchKernelGGL((k_bin<0, false>), dim3(chunks), dim3(NT), 0, s, g, pos, np, count, keys, idx);
-    hipLaunchKernelGGL(k_scan_sums, dim3((unsigned)ntile), dim3(NT), 0, s, count, nc, sums);
-    hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(NT), 0, s, sums, ntile);
-    hipLaunchKernelGGL(k_scan_tiles, dim3((unsigned)ntile), dim3(NT), 0, s, count, nc, sums, start, cursor);
-    hipLaunchKernelGGL((k_bin<1, true>), dim3(chunks), dim3(NT), 0, s, g, pos, np, cursor, keys, idx);
-    if (scheme == 2)
+    if (nc <= SCAN_ONE) {
+        const int per4 = (int)((nc + 4 * SCAN_NT - 1) / (4 * SCAN_NT)) * 4;
+        hipLaunchKernelGGL(k_scan_one, dim3(1), dim3(SCAN_NT), 0, s, count, (int)nc, per4, start, cursor);
+    } else {
+        hipLaunchKernelGGL(k_scan_sums, dim3((unsigned)ntile), dim3(NT), 0, s, count, nc, sums);
+        hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(NT), 0, s, sums, ntile);
+        hipLaunchKernelGGL(k_scan_tiles, dim3((unsigned)ntile), dim3(NT), 0, s, count, nc, sums, start, cursor);
+    }
+    if (table && periodic)
+        hipLaunchKernelGGL(k_place<true>, ranges, dim3(CNT), lds, s, g, pos, np, per, (uint32_t)nb, cursor, keys,
+                           listed, idx);
+    else if (table)
+        hipLaunchKernelGGL(k_place<false>, ranges, dim3(CNT), lds, s, g, pos, np, per, (uint32_t)nb, cursor, keys,
+                           listed, idx);
+    else
+        hipLaunchKernelGGL((k_bin<1, true>), dim3(chunks), dim3(NT), 0, s, g, pos, np, cursor, keys, idx);
+    // workgroups per brick: enough for two per CU, each with at least 2048 particles
+    // of a brick of average content (4.3 M particles in random order onto 32 x 131 x
+    // 28 cells, CIC: 172 us a call, 457 us with one workgroup per 16^3 brick)
+    const double content = mean_count * (double)n0 * n1 * n2 / (double)nb;
+    int split = 1;
+    while (nb * split < SMALL_BRICKS && content >= 4096.0 * split) split *= 2;
+    // (an order only matters where bricks queue for the CUs)
+    if (scheme == 2 && nb > SMALL_BRICKS)
         hipLaunchKernelGGL(k_brick_order, dim3(1), dim3(ORD_NT), 0, s, start, nb, order);
     else
         order = nullptr;
-    if (scheme == 1 && periodic)
-        hipLaunchKernelGGL((k_bin_assign<2, true>), dim3((unsigned)nb), dim3(ANT), 0, s, g, pos, start, idx, order, stage);
-    else if (scheme == 1)
-        hipLaunchKernelGGL((k_bin_assign<2, false>), dim3((unsigned)nb), dim3(ANT), 0, s, g, pos, start, idx, order, stage);
-    else if (periodic)
-        hipLaunchKernelGGL((k_bin_assign<3, true>), dim3((unsigned)nb), dim3(ANT), 0, s, g, pos, start, idx, order, stage);
-    else
-        hipLaunchKernelGGL((k_bin_assign<3, false>), dim3((unsigned)nb), dim3(ANT), 0, s, g, pos, start, idx, order, stage);
-    hipLaunchKernelGGL(k_gather, dim3(n1, n2), dim3(NT), 0, s, g, periodic, stage, scale, delta);
+#define VMG_ASSIGN(M, PER)                                                                                  \
+    do {                                                                                                    \
+        if (B == 8) assign_launch<M, PER, 8>(g, pos, start, idx, order, split, nb, stage, s);               \
+        else assign_launch<M, PER, 16>(g, pos, start, idx, order, split, nb, stage, s);                     \
+    } while (0)
+    if (scheme == 1 && periodic) VMG_ASSIGN(2, true);
+    else if (scheme == 1) VMG_ASSIGN(2, false);
+    else if (periodic) VMG_ASSIGN(3, true);
+    else VMG_ASSIGN(3, false);
+#undef VMG_ASSIGN
+    const dim3 gather((unsigned)(g.b1 * ((n0 + GCOLS - 1) / GCOLS)), (unsigned)n2);
+    if (B == 8) hipLaunchKernelGGL(k_gather<8>, gather, dim3(NT), 0, s, g, periodic, stage, scale, delta);
+    else hipLaunchKernelGGL(k_gather<16>, gather, dim3(NT), 0, s, g, periodic, stage, scale, delta);
     return hipGetLastError();
 }
 

@@ -301,8 +301,10 @@ hipError_t launch_total_force(int n0, int n1, int n2, double h, const double* ph
 int64_t total_force_blocks(int n0, int n1, int n2);
 // Particles (np x 3, box units) -> delta on a periodic n0 x n1 x n2 grid;
 // scheme 1 cloud in cell, 2 triangular-shaped cloud (kernels_assign.hip).
-// work: mass_assign_workspace(np, n0, n1, n2) bytes, 256-byte aligned.
+// work: 256-byte aligned, at least mass_assign_workspace_min bytes;
+// mass_assign_workspace is what the fastest path can use.
 int64_t mass_assign_bricks(int n0, int n1, int n2);
+int64_t mass_assign_workspace_min(int64_t np, int n0, int n1, int n2);
 int64_t mass_assign_workspace(int64_t np, int n0, int n1, int n2);
 // The allocation-free variant's workspace: a static device array of
 // NOALLOC_SCRATCH_BYTES per GPU; noalloc_scratch() gives the current device's
@@ -313,8 +315,8 @@ hipError_t noalloc_scratch(void** ptr);
 // periodic: the whole box (h, corner unused); else a region of cells of size h
 // whose cell (0,0,0) corner is at corner[3].  delta = mass / mean_count - 1.
 hipError_t launch_mass_assign(const double* pos, int64_t np, int n0, int n1, int n2, int scheme, bool periodic,
-                              double h, const double* corner, double mean_count, void* work, double* delta,
-                              hipStream_t s);
+                              double h, const double* corner, double mean_count, void* work, int64_t work_bytes,
+                              double* delta, hipStream_t s);
 
 // ---- mixed path (kernels_mixed.hip) ---------------------------------------
 // zero_in: the input correction is identically zero (first sweep of an inner
