@@ -65,28 +65,31 @@ constexpr int sweep_slots(bool defer) { return defer ? 4 : 3; }
 // kernels are built for: as many blocks per CU as that LDS allows (160 KB per
 // CU), at most 4, so that the register budget matches the occupancy the LDS
 // permits.
-// With the prolongation folded in (pro): four coarse correction planes of the
-// tile's window ((TX/2 + 4) x (ty/2 + 4) cells) and two planes of their
-// interpolation onto the tile's ring-2 rows ((ty + 4) x (TX/2 + 4)), counted at
-// 8 bytes.
+// With the prolongation folded in (pro: bytes of one coarse correction, 0
+// without): four coarse correction planes of the tile's window ((TX/2 + 4) x
+// (ty/2 + 4) cells) and two planes of their interpolation onto the tile's ring-2
+// rows ((ty + 4) x (TX/2 + 4)).  In FP32 that leaves room for two 16-row blocks
+// per CU on three-plane rings; the folded sweep is bound by instruction issue and
+// barriers, so a second block pays: 512^3 folded FP32 sweep 962 -> 760 us, even
+// with the 8 registers that the 128 of that occupancy no longer hold.
 constexpr int PRO_SLOTS = 4;
 constexpr int pro_window(int ty) { return (TX / 2 + 4) * (ty / 2 + 4); }
 constexpr int pro_rows(int ty) { return (TX / 2 + 4) * (ty + 4); }
-constexpr int sweep_lds_bytes(int ty, bool defer, bool pro = false) {
+constexpr int sweep_lds_bytes(int ty, bool defer, int pro = 0) {
     return sweep_slots(defer) * ((TX + 4) * (ty + 4) + (TX + 2) * (ty + 2)) * 8 +
-           (pro ? (PRO_SLOTS * pro_window(ty) + 2 * pro_rows(ty)) * 8 : 0);
+           (PRO_SLOTS * pro_window(ty) + 2 * pro_rows(ty)) * pro;
 }
 // (at most 4 blocks; with the folded prolongation, whose extra state would not
 // fit that register budget, at most 3 for tile height 4 and 2 above)
-constexpr int sweep_max_blocks(int ty, bool pro) { return pro ? (ty <= 4 ? 3 : 2) : 4; }
-constexpr int sweep_blocks_per_cu(int ty, bool defer, bool pro = false) {
+constexpr int sweep_max_blocks(int ty, int pro) { return pro ? (ty <= 4 ? 3 : 2) : 4; }
+constexpr int sweep_blocks_per_cu(int ty, bool defer, int pro = 0) {
     return (160 * 1024) / sweep_lds_bytes(ty, defer, pro) >= sweep_max_blocks(ty, pro)
                ? sweep_max_blocks(ty, pro)
                : ((160 * 1024) / sweep_lds_bytes(ty, defer, pro) < 1 ? 1
                                                                      : (160 * 1024) / sweep_lds_bytes(ty, defer, pro));
 }
 // waves per SIMD (the launch bound): the resident blocks' waves over the CU's 4 SIMDs
-constexpr int sweep_waves(int ty, bool defer, bool pro = false) {
+constexpr int sweep_waves(int ty, bool defer, int pro = 0) {
     return (sweep_blocks_per_cu(ty, defer, pro) * (sweep_threads(ty) / 64) + 3) / 4;
 }
 
@@ -177,14 +180,16 @@ __device__ __forceinline__ void fused_sweep(const K& k, const Geom& g, const int
     constexpr int NPB = PRO ? NL2 : 1;
     __shared__ Corr PC[PRO ? PRO_SLOTS * CWH : 1];
     __shared__ Corr EY[PRO ? 2 * EYS : 1];
-    int cob[NCW], cl[NCW];   // byte offset of a window cell in a coarse plane, its LDS word (-1: none)
-    int eyo[NEY], eyd[NEY];  // EY entry: window word of (J, column) (-1: none), y step (+-CW)
-    int pwin[NPB][2];        // ring-2 cell: EY word of (row, I), x step (+-1)
+    int cob[NCW];   // byte offset of a window cell in a coarse plane (its LDS word is its index)
+    int eyo[NEY];   // EY entry: its two window words, J in the low and J +- 1 in the high half
+    int pwin[NPB];  // ring-2 cell: EY word of (row, I)
+    // x step of this thread's ring-2 cells: W2 and NTH are even, so they all have its parity
+    const int pstep = (tid & 1) ? 1 : -1;
+    static_assert(W2 % 2 == 0 && NTH % 2 == 0 && CWH < (1 << 15), "parity and packing of the folded prolongation");
     if (PRO) {
 #pragma unroll
         for (int q = 0; q < NCW; ++q) {
             const int e = tid + q * NTH;
-            cl[q] = e < CWH ? e : -1;
             cob[q] = BUF_OOB;
             if (e < CWH) {
                 const int I = wrapi((x0 >> 1) - 2 + e % CW, k.gc.n0), J = wrapi((y0 >> 1) - 2 + e / CW, k.gc.n1);
@@ -195,15 +200,14 @@ __device__ __forceinline__ void fused_sweep(const K& k, const Geom& g, const int
         for (int q = 0; q < NEY; ++q) {
             const int e = tid + q * NTH;
             const int Y = e / CW, c = e % CW;      // ring-2 row, window column
-            eyo[q] = e < EYS ? (1 + (Y >> 1)) * CW + c : -1;
-            eyd[q] = (Y & 1) ? CW : -CW;
+            const int o = e < EYS ? (1 + (Y >> 1)) * CW + c : CW;
+            eyo[q] = o | ((o + ((Y & 1) ? CW : -CW)) << 16);
         }
 #pragma unroll
         for (int s = 0; s < NPB; ++s) {
             const int e = tid + s * NTH;
             const int X = e < NP2 ? e % W2 : 0, Y = e < NP2 ? e / W2 : 0;
-            pwin[s][0] = Y * CW + 1 + (X >> 1);
-            pwin[s][1] = (X & 1) ? 1 : -1;
+            pwin[s] = Y * CW + 1 + (X >> 1);
         }
     }
     auto coarse_load = [&](int kc, Corr (&v)[NCW]) {
@@ -215,7 +219,7 @@ __device__ __forceinline__ void fused_sweep(const K& k, const Geom& g, const int
         Corr* dst = PC + (kc & (PRO_SLOTS - 1)) * CWH;
 #pragma unroll
         for (int q = 0; q < NCW; ++q)
-            if (cl[q] >= 0) dst[cl[q]] = v[q];
+            if (tid + q * NTH < CWH) dst[tid + q * NTH] = v[q];
     };
     // EY of fine plane p from its two coarse planes (z, then y)
     auto make_ey = [&](int p) {
@@ -226,10 +230,10 @@ __device__ __forceinline__ void fused_sweep(const K& k, const Geom& g, const int
         const Corr a = Corr(0.75), b = Corr(0.25);
 #pragma unroll
         for (int q = 0; q < NEY; ++q) {
-            if (eyo[q] < 0) continue;
-            const int o = eyo[q], dy = eyd[q];
+            if (tid + q * NTH >= EYS) continue;
+            const int o = eyo[q] & 0xFFFF, o1 = eyo[q] >> 16;
             const Corr z0v = a * C0[o] + b * C1[o];
-            const Corr z1v = a * C0[o + dy] + b * C1[o + dy];
+            const Corr z1v = a * C0[o1] + b * C1[o1];
             E[tid + q * NTH] = a * z0v + b * z1v;
         }
     };
@@ -240,8 +244,8 @@ __device__ __forceinline__ void fused_sweep(const K& k, const Geom& g, const int
         const Corr a = Corr(0.75), b = Corr(0.25);
 #pragma unroll
         for (int s = 0; s < NPB; ++s) {
-            const int o = pwin[s][0];
-            v[s] = a * E[o] + b * E[o + pwin[s][1]];
+            const int o = pwin[s];
+            v[s] = a * E[o] + b * E[o + pstep];
         }
     };
     auto add_prolonged = [&](const Corr (&v)[NPB], Cell (&r)[NL2]) {
@@ -473,8 +477,10 @@ __device__ __forceinline__ void fused_sweep(const K& k, const Geom& g, const int
         if (RED && CLOAD) coarse_load((t >> 1) + 2, cq);
         if (RED && PRO) make_ey(t + 2);
         // correction of plane t + 1, read early so that its LDS latency is hidden
+        // (not where two blocks share a CU: they hide it, and registers are short)
+        constexpr bool EARLY = DEFER || sizeof(Corr) == 8;
         Corr pv[NPB];
-        if (RED && PRO) read_prolonged(t + 1, pv);
+        if (RED && PRO && EARLY) read_prolonged(t + 1, pv);
         if (RED) {
             if (K::AHEAD == 2)
                 load_plane(t + 2, t + 2 <= z1 + 1, pq[cur]);
@@ -495,6 +501,7 @@ __device__ __forceinline__ void fused_sweep(const K& k, const Geom& g, const int
             fetch_black(pn, pn >= z0 && pn < z1, BNX(), bq[cur]);
             // commit u^0 plane t+1 (its slot is read by no phase of this step; past
             // the chunk's last red step the slot is never read again)
+            if (PRO && !EARLY) read_prolonged(t + 1, pv);
             if (PRO) add_prolonged(pv, pq[K::AHEAD == 2 ? (b ^ 1) : 0]);
             store_plane(slot(t + 1), pq[K::AHEAD == 2 ? (b ^ 1) : 0]);
             if (CLOAD) coarse_store((t >> 1) + 2, cq);

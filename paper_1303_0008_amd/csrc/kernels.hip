@@ -144,7 +144,7 @@ struct SmoothK {
 // PRO: the sweep starts from pin + P(uc - oc), the coarse correction prolonged
 // as the planes are staged (periodic grids, even z chunks)
 template <int TY, int DIR, bool HAS_F, bool DEFER, bool PRO = false>
-__global__ void __launch_bounds__(sweep_threads(TY), sweep_waves(TY, DEFER, PRO)) k_smooth(SmoothArgs a) {
+__global__ void __launch_bounds__(sweep_threads(TY), sweep_waves(TY, DEFER, PRO ? 8 : 0)) k_smooth(SmoothArgs a) {
     int b = xcd_remap(blockIdx.x, gridDim.x);
     const int tx = b % a.tiles_x;
     b /= a.tiles_x;

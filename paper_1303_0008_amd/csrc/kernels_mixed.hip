@@ -153,7 +153,7 @@ struct CorrK {
 // PRO: the sweep starts from ein + P(uc - oc), the coarse correction prolonged
 // as the planes are staged (periodic grids, even z chunks)
 template <int TY, int DIR, bool ZERO_E, bool DEFER, bool PRO = false>
-__global__ void __launch_bounds__(sweep_threads(TY), sweep_waves(TY, DEFER, PRO)) k_smooth_corr(CorrArgs a) {
+__global__ void __launch_bounds__(sweep_threads(TY), sweep_waves(TY, DEFER, PRO ? 4 : 0)) k_smooth_corr(CorrArgs a) {
     int b = xcd_remap(blockIdx.x, gridDim.x);
     const int tx = b % a.tiles_x;
     b /= a.tiles_x;
@@ -1195,7 +1195,12 @@ template <int TY, int DIR>
 static hipError_t corr_launch(const CorrArgs& a, bool zero_in, bool defer, hipStream_t s) {
     const dim3 nb(a.tiles_x * a.tiles_y * ((a.g.n2 + a.zc - 1) / a.zc));
     if (!DIR && a.uc && !zero_in) {
-        if (defer) hipLaunchKernelGGL((k_smooth_corr<TY, 0, false, true, true>), nb, dim3(sweep_threads(TY)), 0, s, a);
+        // The folded 16-row sweep takes the three-plane rings, with which two of its
+        // blocks share a CU, whatever the schedule's pipe once there are two blocks
+        // for every CU (256^3, 16-plane chunks: 127 us against 140 us on four-plane
+        // rings).  Below that a block has its CU to itself either way, and the ring
+        // with one barrier per step is the faster one (128^3, 256 blocks).
+        if (defer && (TY < 16 || nb.x < 512)) hipLaunchKernelGGL((k_smooth_corr<TY, 0, false, true, true>), nb, dim3(sweep_threads(TY)), 0, s, a);
         else hipLaunchKernelGGL((k_smooth_corr<TY, 0, false, false, true>), nb, dim3(sweep_threads(TY)), 0, s, a);
         return hipGetLastError();
     }
