@@ -55,6 +55,45 @@ __device__ __forceinline__ void buf_st_f32(__amdgpu_buffer_rsrc_t r, int bo, flo
     __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned int, v), r, bo, 0, 0);
 }
 
+// Pairs of neighbouring elements (an x pair of cells) in one access, aligned to
+// one element.
+typedef unsigned int vmg_u32x4 __attribute__((ext_vector_type(4)));
+struct Pair64 {
+    double v[2];
+};
+struct Pair32 {
+    float v[2];
+};
+__device__ __forceinline__ Pair64 buf_ld2_f64(__amdgpu_buffer_rsrc_t r, int bo) {
+    return __builtin_bit_cast(Pair64, __builtin_amdgcn_raw_buffer_load_b128(r, bo, 0, 0));
+}
+__device__ __forceinline__ Pair32 buf_ld2_f32(__amdgpu_buffer_rsrc_t r, int bo) {
+    return __builtin_bit_cast(Pair32, __builtin_amdgcn_raw_buffer_load_b64(r, bo, 0, 0));
+}
+__device__ __forceinline__ void buf_st2_f64(__amdgpu_buffer_rsrc_t r, int bo, const Pair64& p) {
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(vmg_u32x4, p), r, bo, 0, 0);
+}
+__device__ __forceinline__ void buf_st2_f32(__amdgpu_buffer_rsrc_t r, int bo, const Pair32& p) {
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(vmg_u32x2, p), r, bo, 0, 0);
+}
+
+// v plus its value 32 lanes up, in the wave's low half (the high half holds the
+// same sums): one lane swap per word instead of a shuffle through the LDS unit.
+__device__ __forceinline__ float add_high_half(float v) {
+    const unsigned u = __builtin_bit_cast(unsigned, v);
+    const auto w = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    return __builtin_bit_cast(float, (unsigned)w[0]) + __builtin_bit_cast(float, (unsigned)w[1]);
+}
+__device__ __forceinline__ double add_high_half(double v) {
+    const vmg_u32x2 u = __builtin_bit_cast(vmg_u32x2, v);
+    const auto lo = __builtin_amdgcn_permlane32_swap(u.x, u.x, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap(u.y, u.y, false, false);
+    vmg_u32x2 a, b;
+    a.x = lo[0]; a.y = hi[0];
+    b.x = lo[1]; b.y = hi[1];
+    return __builtin_bit_cast(double, a) + __builtin_bit_cast(double, b);
+}
+
 // 18 stencil neighbours of a cell (the centre is not needed by the root).
 template <typename T>
 struct NbT {

@@ -209,10 +209,19 @@ __global__ void __launch_bounds__(sweep_threads(TY), sweep_waves(TY, DEFER)) k_s
 // residual d = L(phi) + cbar - f at one cell; also returns Q and the guard flag
 // ---------------------------------------------------------------------------
 // Tiled residual pass.  A block owns a 64 x 8 x zc brick (zc even) and marches
-// up z with phi staged on a one-cell ring in LDS (3 planes, next plane
+// up z with phi staged on a one-cell ring in LDS (4 planes, next plane
 // prefetched into registers).  Thread (m, r) handles the x pair (2m, 2m+1) of
 // row r; rows 2k and 2k+1 live in the two halves of one wave, so the 2x2x2
-// restriction sums need one cross-half shuffle and one z-pair register.
+// restriction sums need one cross-half swap and one z-pair register.
+// These passes are bound by instruction issue beside the memory they stream
+// (the restriction at 256^3 and its FP32 counterpart at 512^3 kept the vector
+// units 45 and 73 % busy), so what is not arithmetic is kept out of the plane
+// loop: raw buffer accesses that need no branch, an x pair per access (scalar
+// stores of every other element held the mixed path's outer pass at 3.7 TB/s),
+// integer counters for guarded and non-finite cells, a ring of four planes with
+// one barrier per plane instead of three with two.  256^3 restriction 79 -> 67 us
+// (4.0 TB/s; a read-only pass reaches 6.1), right-hand side of the 128^3 level
+// 20 -> 17.6 us, 256^3 norm 70 -> 59 us.
 //   MODE 0 (norm):     d = L(phi) + cbar - f, reductions, optional d_out (caller layout)
 //   MODE 1 (restrict): as 0, and R phi -> phic, phiold_c; R d -> rd_c
 //   MODE 2 (FAS rhs):  fout = L(phi) - rd (rd passed as f), reductions of Q and fout
@@ -238,11 +247,11 @@ struct ResidArgs {
 constexpr int RTY = 8;   // rows per residual tile
 
 template <int DIR, int MODE>
-__global__ void __launch_bounds__(NT) k_resid_tiled(ResidArgs a) {
+__global__ void __launch_bounds__(NT, 4) k_resid_tiled(ResidArgs a) {
     constexpr int W1 = TX + 2, H1 = RTY + 2;
     constexpr int NP1 = W1 * H1;
     constexpr int NL1 = (NP1 + NT - 1) / NT;
-    __shared__ double PH[3][H1][W1];
+    __shared__ double PH[4][H1][W1];
     const Geom& g = a.g;
     const int tid = threadIdx.x;
     int b = xcd_remap(blockIdx.x, gridDim.x);
@@ -253,144 +262,148 @@ __global__ void __launch_bounds__(NT) k_resid_tiled(ResidArgs a) {
     const int x0 = tx * TX, y0 = ty * RTY, z0 = ch * a.zc;
     const int z1 = min(z0 + a.zc, g.n2);
     double acc[R_NSLOT] = {0, 0, 0, 0, 0, 0, 0};
+    int n_guard = 0, n_nonfin = 0;
     const double cb = (DIR || MODE == 2) ? 0.0 : a.sc->cbar;
     const double inv_h2 = 1.0 / (g.h * g.h), inv_h4 = inv_h2 * inv_h2;
     const int m = tid & 31, r = tid >> 5;           // x pair, row
     const int gy = y0 + r;
     const int xa = x0 + 2 * m;                       // first cell of the pair
-    const bool row_ok = gy < g.n1;
+    const bool pair_ok = gy < g.n1 && xa < g.n0;     // (periodic grids: n0 even)
+    const int64_t loff0 = g.off0 - g.base;
 
-    int off1[NL1], lds1[NL1];   // global in-plane offset, LDS word (rows split by parity)
-    bool ok1[NL1];
+    int ob1[NL1], lds1[NL1];   // byte offset in a plane (out of range: zero), LDS word (rows split by parity)
 #pragma unroll
     for (int s = 0; s < NL1; ++s) {
         const int e = tid + s * NT;
-        ok1[s] = false;
-        off1[s] = 0;
+        ob1[s] = BUF_OOB;
         lds1[s] = (e / W1) * W1 + split_col<W1>(e % W1);
         if (e < NP1) {
             int gx = x0 - 1 + e % W1, gyy = y0 - 1 + e / W1;
+            bool ok = true;
             if (DIR) {
-                ok1[s] = gx >= -1 && gx <= g.n0 && gyy >= -1 && gyy <= g.n1;
+                ok = gx >= -1 && gx <= g.n0 && gyy >= -1 && gyy <= g.n1;
             } else {
                 gx = wrapi(gx, g.n0);
                 gyy = wrapi(gyy, g.n1);
-                ok1[s] = true;
             }
-            off1[s] = (int)(g.off0 + gx + (int64_t)gyy * g.sy);
+            if (ok) ob1[s] = (int)(loff0 + gx + (int64_t)gyy * g.sy) * 8;
         }
     }
-    auto plane_off = [&](int t, bool& zok) -> int64_t {
-        int gz;
-        if (DIR) { gz = t; zok = t >= -1 && t <= g.n2; }
-        else { gz = wrapi(t, g.n2); zok = true; }
-        return (int64_t)gz * g.sz;
-    };
+    const int sob = pair_ok ? (int)(loff0 + xa + (int64_t)gy * g.sy) * 8 : BUF_OOB;   // the pair in a plane
     auto load_plane = [&](int t, double (&rr)[NL1]) {
-        bool zok;
-        const int64_t zo = plane_off(t, zok);
+        const bool zok = !DIR || (t >= -1 && t <= g.n2);
+        const auto P = plane_rsrc(a.phi, g.base + (int64_t)(DIR ? t : wrapi(t, g.n2)) * g.sz, 8, zok);
 #pragma unroll
-        for (int s = 0; s < NL1; ++s) rr[s] = (ok1[s] && zok && tid + s * NT < NP1) ? a.phi[zo + off1[s]] : 0.0;
+        for (int s = 0; s < NL1; ++s) rr[s] = buf_ld_f64(P, ob1[s]);
     };
-    auto store_plane = [&](int sl, const double (&rr)[NL1]) {
-        double* dst = &PH[sl][0][0];
+    auto store_plane = [&](int t, const double (&rr)[NL1]) {
+        double* dst = &PH[t & 3][0][0];
 #pragma unroll
         for (int s = 0; s < NL1; ++s)
             if (tid + s * NT < NP1) dst[lds1[s]] = rr[s];
     };
-    auto slot = [](int z) { return (z + 3) % 3; };
-    auto src_fetch = [&](int t, double (&dl)[2], double (&fv)[2]) {
-#pragma unroll
-        for (int c2 = 0; c2 < 2; ++c2) {
-            dl[c2] = 0.0;
-            fv[c2] = 0.0;
-            if (!row_ok || xa + c2 >= g.n0 || t >= z1) continue;
-            const int64_t gi = g.off0 + xa + c2 + (int64_t)gy * g.sy + (int64_t)t * g.sz;
-            dl[c2] = a.delta[gi];
-            if (a.f) fv[c2] = a.f[gi];
-        }
+    // (an odd row's last pair reads the ghost cell beside it, which is not used)
+    auto src_fetch = [&](int t, Pair64& dl, Pair64& fv) {
+        const int64_t zo = g.base + (int64_t)t * g.sz;
+        dl = buf_ld2_f64(plane_rsrc(a.delta, zo, 8, t < z1), sob);
+        fv = Pair64{{0.0, 0.0}};
+        if (a.f) fv = buf_ld2_f64(plane_rsrc(a.f, zo, 8, t < z1), sob);
     };
 
     {
         double rr[NL1];
         for (int t = z0 - 1; t <= z0 + 1; ++t) {
             load_plane(t, rr);
-            store_plane(slot(t), rr);
+            store_plane(t, rr);
         }
     }
-    double cdl[2], cfv[2];
+    Pair64 cdl, cfv;
     src_fetch(z0, cdl, cfv);
     __syncthreads();
     double zsum_phi = 0.0, zsum_d = 0.0;   // restriction partial sums of the even plane
     for (int t = z0; t < z1; ++t) {
         // planes t-1, t, t+1 are in LDS; plane t+2 is fetched while plane t is computed
-        double nxt[NL1], ndl[2], nfv[2];
+        // and goes to the slot of plane t-2, last read before the previous barrier
+        double nxt[NL1];
+        Pair64 ndl, nfv;
         const bool pf = t + 2 <= z1;
         if (pf) load_plane(t + 2, nxt);
         src_fetch(t + 1, ndl, nfv);
-        const int sm = slot(t - 1), sc = slot(t), sp = slot(t + 1);
+        const double* Pm = &PH[(t - 1) & 3][r + 1][0];
+        const double* Pc = &PH[t & 3][r + 1][0];
+        const double* Pp = &PH[(t + 1) & 3][r + 1][0];
         double psum = 0.0, dsum = 0.0;
+        Pair64 fout;
+        if (pair_ok) {
 #pragma unroll
-        for (int c2 = 0; c2 < 2; ++c2) {
-            const int X = 2 * m + c2 + 1, Y = r + 1;
-            if (!row_ok || xa + c2 >= g.n0) continue;
-            Nb v;
-            v.xm = PH[sc][Y][split_col<W1>(X - 1)]; v.xp = PH[sc][Y][split_col<W1>(X + 1)];
-            v.ym = PH[sc][Y - 1][split_col<W1>(X)]; v.yp = PH[sc][Y + 1][split_col<W1>(X)];
-            v.zm = PH[sm][Y][split_col<W1>(X)];     v.zp = PH[sp][Y][split_col<W1>(X)];
-            v.xpyp = PH[sc][Y + 1][split_col<W1>(X + 1)]; v.xmym = PH[sc][Y - 1][split_col<W1>(X - 1)];
-            v.xpym = PH[sc][Y - 1][split_col<W1>(X + 1)]; v.xmyp = PH[sc][Y + 1][split_col<W1>(X - 1)];
-            v.xpzp = PH[sp][Y][split_col<W1>(X + 1)]; v.xmzm = PH[sm][Y][split_col<W1>(X - 1)];
-            v.xpzm = PH[sm][Y][split_col<W1>(X + 1)]; v.xmzp = PH[sp][Y][split_col<W1>(X - 1)];
-            v.ypzp = PH[sp][Y + 1][split_col<W1>(X)]; v.ymzm = PH[sm][Y - 1][split_col<W1>(X)];
-            v.ypzm = PH[sm][Y + 1][split_col<W1>(X)]; v.ymzp = PH[sp][Y - 1][split_col<W1>(X)];
-            const double pc = PH[sc][Y][split_col<W1>(X)];
-            double S;
-            bool gd;
-            const double Q = nl_root(v, cdl[c2], a.c, inv_h4, S, gd);
-            const double L = (S - 6.0 * pc) * inv_h2 - Q;
-            if (MODE == 2) {
-                const double fh = L - cfv[c2];
-                a.fout[g.off0 + xa + c2 + (int64_t)gy * g.sy + (int64_t)t * g.sz] = fh;
-                acc[R_Q] += Q;
-                acc[R_F] += fh;
-                // tau^h = L^H(R phi) - R L^h(phi) = f^H - R f^h + cbar^h (a constant on
-                // periodic grids): its sums give the RMS of tau^h (Sec. III.C)
-                double tau = fh;
-                if (a.f_fine) {
-                    const Geom& gf = a.gfine;
-                    double rf = 0.0;
+            for (int c2 = 0; c2 < 2; ++c2) {
+                if (DIR && xa + c2 >= g.n0) continue;
+                const int X = 2 * m + c2 + 1;
+                const int xl = split_col<W1>(X - 1), xc = split_col<W1>(X), xr = split_col<W1>(X + 1);
+                Nb v;
+                v.xm = Pc[xl];        v.xp = Pc[xr];
+                v.ym = Pc[xc - W1];   v.yp = Pc[xc + W1];
+                v.zm = Pm[xc];        v.zp = Pp[xc];
+                v.xpyp = Pc[xr + W1]; v.xmym = Pc[xl - W1];
+                v.xpym = Pc[xr - W1]; v.xmyp = Pc[xl + W1];
+                v.xpzp = Pp[xr];      v.xmzm = Pm[xl];
+                v.xpzm = Pm[xr];      v.xmzp = Pp[xl];
+                v.ypzp = Pp[xc + W1]; v.ymzm = Pm[xc - W1];
+                v.ypzm = Pm[xc + W1]; v.ymzp = Pp[xc - W1];
+                const double pc = Pc[xc];
+                double S;
+                bool gd;
+                const double Q = nl_root(v, cdl.v[c2], a.c, inv_h4, S, gd);
+                const double L = (S - 6.0 * pc) * inv_h2 - Q;
+                if (MODE == 2) {
+                    const double fh = L - cfv.v[c2];
+                    fout.v[c2] = fh;
+                    acc[R_Q] += Q;
+                    acc[R_F] += fh;
+                    // tau^h = L^H(R phi) - R L^h(phi) = f^H - R f^h + cbar^h (a constant on
+                    // periodic grids): its sums give the RMS of tau^h (Sec. III.C)
+                    double tau = fh;
+                    if (a.f_fine) {
+                        const Geom& gf = a.gfine;
+                        double rf = 0.0;
 #pragma unroll
-                    for (int m = 0; m < 8; ++m)
-                        rf += a.f_fine[cell_index(gf, 2 * (xa + c2) + (m & 1), 2 * gy + ((m >> 1) & 1),
-                                                  2 * t + (m >> 2))];
-                    tau -= 0.125 * rf;
+                        for (int m = 0; m < 8; ++m)
+                            rf += a.f_fine[cell_index(gf, 2 * (xa + c2) + (m & 1), 2 * gy + ((m >> 1) & 1),
+                                                      2 * t + (m >> 2))];
+                        tau -= 0.125 * rf;
+                    }
+                    acc[R_D1] += tau;
+                    acc[R_D2] += tau * tau;
+                } else {
+                    const double d = L - cfv.v[c2] + cb;
+                    acc[R_D2] += d * d;
+                    acc[R_D1] += d;
+                    acc[R_Q] += Q;
+                    acc[R_F] += cfv.v[c2];
+                    acc[R_PHI] += pc;
+                    n_guard += gd ? 1 : 0;
+                    n_nonfin += isfinite(d) ? 0 : 1;
+                    if (MODE == 0 && a.d_out)
+                        a.d_out[xa + c2 + ((int64_t)t * g.n1 + gy) * g.n0] = d;
+                    psum += pc;
+                    dsum += d;
                 }
-                acc[R_D1] += tau;
-                acc[R_D2] += tau * tau;
-            } else {
-                const double d = L - cfv[c2] + cb;
-                acc[R_D2] += d * d;
-                acc[R_D1] += d;
-                acc[R_Q] += Q;
-                acc[R_F] += cfv[c2];
-                acc[R_PHI] += pc;
-                acc[R_GUARD] += gd ? 1.0 : 0.0;
-                acc[R_NONFIN] += isfinite(d) ? 0.0 : 1.0;
-                if (MODE == 0 && a.d_out)
-                    a.d_out[xa + c2 + ((int64_t)t * g.n1 + gy) * g.n0] = d;
-                psum += pc;
-                dsum += d;
             }
+        }
+        if (MODE == 2) {
+            const auto F = plane_rsrc(a.fout, g.base + (int64_t)t * g.sz, 8, true);
+            const bool half = DIR && xa + 1 >= g.n0;   // an odd row's last cell
+            buf_st2_f64(F, half ? BUF_OOB : sob, fout);
+            if (DIR) buf_st_f64(F, half ? sob : BUF_OOB, fout.v[0]);
         }
         if (MODE == 1) {
             // y pair: rows 2k and 2k+1 are lanes l and l+32 of one wave
-            psum += __shfl_down(psum, 32, 64);
-            dsum += __shfl_down(dsum, 32, 64);
+            psum = add_high_half(psum);
+            dsum = add_high_half(dsum);
             if ((t & 1) == 0) {
                 zsum_phi = psum;
                 zsum_d = dsum;
-            } else if ((r & 1) == 0 && row_ok && xa < g.n0) {
+            } else if ((r & 1) == 0 && pair_ok) {
                 const Geom& gc = a.gc;
                 const int64_t co = gc.off0 + (xa >> 1) + (int64_t)(gy >> 1) * gc.sy + (int64_t)(t >> 1) * gc.sz;
                 const double rp = 0.125 * (zsum_phi + psum);
@@ -399,17 +412,13 @@ __global__ void __launch_bounds__(NT) k_resid_tiled(ResidArgs a) {
                 a.rd_c[co] = 0.125 * (zsum_d + dsum);
             }
         }
-        __syncthreads();
-        if (pf) {
-            double* dst = &PH[slot(t + 2)][0][0];   // slot of plane t-1: no longer read
-#pragma unroll
-            for (int s = 0; s < NL1; ++s)
-                if (tid + s * NT < NP1) dst[lds1[s]] = nxt[s];
-        }
-        cdl[0] = ndl[0]; cdl[1] = ndl[1];
-        cfv[0] = nfv[0]; cfv[1] = nfv[1];
+        if (pf) store_plane(t + 2, nxt);
+        cdl = ndl;
+        cfv = nfv;
         __syncthreads();
     }
+    acc[R_GUARD] = (double)n_guard;
+    acc[R_NONFIN] = (double)n_nonfin;
     block_store_partials(acc, a.partials);
 }
 

@@ -547,7 +547,10 @@ __global__ void k_cast_all(const double* src, float* dst, int64_t n) {
 
 // ---------------------------------------------------------------------------
 // Tiled passes of the mixed path (same brick / z-march layout as the FP64
-// residual pass: 64 x 8 x 16 bricks, one-cell LDS ring, thread = x pair of a row)
+// residual pass: 64 x 8 x 16 bricks, one-cell LDS ring, thread = x pair of a row;
+// k_resid_tiled says what bounds them).  At 512^3: outer pass 1445 -> 1082 us (40 B
+// per cell at 5.0 TB/s), inner residual and restriction 632 -> 551 us; at 256^3 the
+// coarse right-hand side 96 -> 74 us with t0 read, 158 -> 102 us with t0 formed.
 // ---------------------------------------------------------------------------
 constexpr int MTY = 8, MZC = 16;
 
@@ -568,9 +571,9 @@ struct CastArgs {
 // Outer FP64 pass: phi_new = phi (+ e), d = L(phi_new) + cbar - f, norm partials,
 // and the inner problem's inputs phi~ = fp32(phi_new), t0 = +-sqrt|D0|, r = -d.
 template <int DIR, bool UPDATE>
-__global__ void __launch_bounds__(NT) k_cast_tiled(CastArgs a) {
+__global__ void __launch_bounds__(NT, 4) k_cast_tiled(CastArgs a) {
     constexpr int W1 = TX + 2, H1 = MTY + 2, NP1 = W1 * H1, NL1 = (NP1 + NT - 1) / NT;
-    __shared__ double PH[3][H1][W1];
+    __shared__ double PH[4][H1][W1];
     const Geom& g = a.g;
     const int tid = threadIdx.x;
     int b = xcd_remap(blockIdx.x, gridDim.x);
@@ -581,121 +584,139 @@ __global__ void __launch_bounds__(NT) k_cast_tiled(CastArgs a) {
     const int x0 = tx * TX, y0 = ty * MTY, z0 = ch * a.zc;
     const int z1 = min(z0 + a.zc, g.n2);
     double acc[R_NSLOT] = {0, 0, 0, 0, 0, 0, 0};
+    int n_guard = 0, n_nonfin = 0;
     const double cb = DIR ? 0.0 : a.sc->cbar;
     const double inv_h2 = 1.0 / (g.h * g.h), inv_h4 = inv_h2 * inv_h2;
     const int m = tid & 31, r = tid >> 5;
     const int gy = y0 + r, xa = x0 + 2 * m;
-    const bool row_ok = gy < g.n1;
-    int off1[NL1], lds1[NL1];   // global in-plane offset, LDS word (rows split by parity)
-    bool ok1[NL1];
+    const bool pair_ok = gy < g.n1 && xa < g.n0;   // (periodic grids: n0 even)
+    const int64_t loff0 = g.off0 - g.base;
+    int oe1[NL1], lds1[NL1];   // element offset in a plane (-1: zero), LDS word (rows split by parity)
 #pragma unroll
     for (int s2 = 0; s2 < NL1; ++s2) {
         const int e = tid + s2 * NT;
-        ok1[s2] = false;
-        off1[s2] = 0;
+        oe1[s2] = -1;
         lds1[s2] = (e / W1) * W1 + split_col<W1>(e % W1);
         if (e < NP1) {
             int gx = x0 - 1 + e % W1, gyy = y0 - 1 + e / W1;
+            bool ok = true;
             if (DIR) {
-                ok1[s2] = gx >= -1 && gx <= g.n0 && gyy >= -1 && gyy <= g.n1;
+                ok = gx >= -1 && gx <= g.n0 && gyy >= -1 && gyy <= g.n1;
             } else {
                 gx = wrapi(gx, g.n0);
                 gyy = wrapi(gyy, g.n1);
-                ok1[s2] = true;
             }
-            off1[s2] = (int)(g.off0 + gx + (int64_t)gyy * g.sy);
+            if (ok) oe1[s2] = (int)(loff0 + gx + (int64_t)gyy * g.sy);
         }
     }
-    auto plane_off = [&](int t, bool& zok) -> int64_t {
-        int gz;
-        if (DIR) { gz = t; zok = t >= -1 && t <= g.n2; }
-        else { gz = t < 0 ? t + g.n2 : (t >= g.n2 ? t - g.n2 : t); zok = true; }
-        return (int64_t)gz * g.sz;
-    };
-    auto load_plane = [&](int t, double (&rr)[NL1]) {
-        bool zok;
-        const int64_t zo = plane_off(t, zok);
+    const int soe = (int)(loff0 + xa + (int64_t)gy * g.sy);   // the pair in a plane
+    // plane t of phi (+ e; e is zero on ghosts), at most NL1 cells per thread
+    auto load_plane = [&](int t, double (&rr)[NL1], float (&re)[NL1]) {
+        const bool zok = !DIR || (t >= -1 && t <= g.n2);
+        const int64_t zo = g.base + (int64_t)(DIR ? t : wrapi(t, g.n2)) * g.sz;
+        const auto P = plane_rsrc(a.phi, zo, 8, zok), E = plane_rsrc(UPDATE ? a.e : a.pt, zo, 4, zok && UPDATE);
 #pragma unroll
         for (int s2 = 0; s2 < NL1; ++s2) {
-            const bool ok = ok1[s2] && zok && tid + s2 * NT < NP1;
-            double v = ok ? a.phi[zo + off1[s2]] : 0.0;
-            if (UPDATE && ok) v += (double)a.e[zo + off1[s2]];   // e is zero on ghosts
-            rr[s2] = v;
+            rr[s2] = buf_ld_f64(P, oe1[s2] >= 0 ? oe1[s2] * 8 : BUF_OOB);
+            if (UPDATE) re[s2] = buf_ld_f32(E, oe1[s2] >= 0 ? oe1[s2] * 4 : BUF_OOB);
         }
     };
-    auto store_plane = [&](int sl, const double (&rr)[NL1]) {
-        double* dst = &PH[sl][0][0];
+    auto store_plane = [&](int t, const double (&rr)[NL1], const float (&re)[NL1]) {
+        double* dst = &PH[t & 3][0][0];
 #pragma unroll
         for (int s2 = 0; s2 < NL1; ++s2)
-            if (tid + s2 * NT < NP1) dst[lds1[s2]] = rr[s2];
+            if (tid + s2 * NT < NP1) dst[lds1[s2]] = UPDATE ? rr[s2] + (double)re[s2] : rr[s2];
     };
-    auto slot = [](int z) { return (z + 3) % 3; };
-    auto src_fetch = [&](int t, double (&dl)[2], double (&fv)[2]) {
-#pragma unroll
-        for (int c2 = 0; c2 < 2; ++c2) {
-            dl[c2] = 0.0;
-            fv[c2] = 0.0;
-            if (!row_ok || xa + c2 >= g.n0 || t >= z1) continue;
-            const int64_t gi = g.off0 + xa + c2 + (int64_t)gy * g.sy + (int64_t)t * g.sz;
-            dl[c2] = a.delta[gi];
-            if (a.f) fv[c2] = a.f[gi];
-        }
+    auto src_fetch = [&](int t, Pair64& dl, Pair64& fv) {
+        const int64_t zo = g.base + (int64_t)t * g.sz;
+        dl = buf_ld2_f64(plane_rsrc(a.delta, zo, 8, t < z1), pair_ok ? soe * 8 : BUF_OOB);
+        fv = Pair64{{0.0, 0.0}};
+        if (a.f) fv = buf_ld2_f64(plane_rsrc(a.f, zo, 8, t < z1), pair_ok ? soe * 8 : BUF_OOB);
+    };
+    // the x pair of an output array: one store, or its first cell in an odd row's end
+    const bool half = DIR && xa + 1 >= g.n0;
+    const int so2 = pair_ok && !half ? soe : -1, so1 = pair_ok && half ? soe : -1;
+    auto out64 = [&](double* p, int64_t zo, const Pair64& v) {
+        const auto O = plane_rsrc(p, zo, 8, true);
+        buf_st2_f64(O, so2 >= 0 ? so2 * 8 : BUF_OOB, v);
+        if (DIR) buf_st_f64(O, so1 >= 0 ? so1 * 8 : BUF_OOB, v.v[0]);
+    };
+    auto out32 = [&](float* p, int64_t zo, const Pair32& v) {
+        const auto O = plane_rsrc(p, zo, 4, true);
+        buf_st2_f32(O, so2 >= 0 ? so2 * 4 : BUF_OOB, v);
+        if (DIR) buf_st_f32(O, so1 >= 0 ? so1 * 4 : BUF_OOB, v.v[0]);
     };
     {
         double rr[NL1];
+        float re[NL1];
         for (int t = z0 - 1; t <= z0 + 1; ++t) {
-            load_plane(t, rr);
-            store_plane(slot(t), rr);
+            load_plane(t, rr, re);
+            store_plane(t, rr, re);
         }
     }
-    double cdl[2], cfv[2];
+    Pair64 cdl, cfv;
     src_fetch(z0, cdl, cfv);
     __syncthreads();
     for (int t = z0; t < z1; ++t) {
-        double nxt[NL1], ndl[2], nfv[2];
+        // (rings of four planes, one barrier per plane: see k_resid_tiled)
+        double nxt[NL1];
+        float nxe[NL1];
+        Pair64 ndl, nfv;
         const bool pf = t + 2 <= z1;
-        if (pf) load_plane(t + 2, nxt);
+        if (pf) load_plane(t + 2, nxt, nxe);
         src_fetch(t + 1, ndl, nfv);
-        const int sm = slot(t - 1), sc = slot(t), sp = slot(t + 1);
+        const double* Pm = &PH[(t - 1) & 3][r + 1][0];
+        const double* Pc = &PH[t & 3][r + 1][0];
+        const double* Pp = &PH[(t + 1) & 3][r + 1][0];
+        Pair64 po{{0.0, 0.0}};
+        Pair32 pto{{0.0f, 0.0f}}, t0o{{0.0f, 0.0f}}, ro{{0.0f, 0.0f}};
+        if (pair_ok) {
 #pragma unroll
-        for (int c2 = 0; c2 < 2; ++c2) {
-            const int X = 2 * m + c2 + 1, Y = r + 1;
-            if (!row_ok || xa + c2 >= g.n0) continue;
-            Nb v;
-            v.xm = PH[sc][Y][split_col<W1>(X - 1)]; v.xp = PH[sc][Y][split_col<W1>(X + 1)];
-            v.ym = PH[sc][Y - 1][split_col<W1>(X)]; v.yp = PH[sc][Y + 1][split_col<W1>(X)];
-            v.zm = PH[sm][Y][split_col<W1>(X)];     v.zp = PH[sp][Y][split_col<W1>(X)];
-            v.xpyp = PH[sc][Y + 1][split_col<W1>(X + 1)]; v.xmym = PH[sc][Y - 1][split_col<W1>(X - 1)];
-            v.xpym = PH[sc][Y - 1][split_col<W1>(X + 1)]; v.xmyp = PH[sc][Y + 1][split_col<W1>(X - 1)];
-            v.xpzp = PH[sp][Y][split_col<W1>(X + 1)]; v.xmzm = PH[sm][Y][split_col<W1>(X - 1)];
-            v.xpzm = PH[sm][Y][split_col<W1>(X + 1)]; v.xmzp = PH[sp][Y][split_col<W1>(X - 1)];
-            v.ypzp = PH[sp][Y + 1][split_col<W1>(X)]; v.ymzm = PH[sm][Y - 1][split_col<W1>(X)];
-            v.ypzm = PH[sm][Y + 1][split_col<W1>(X)]; v.ymzp = PH[sp][Y - 1][split_col<W1>(X)];
-            const double pc = PH[sc][Y][split_col<W1>(X)];
-            double S;
-            bool gd;
-            double t0;
-            const double Q = nl_root_t0(v, cdl[c2], a.c, inv_h4, S, gd, t0);
-            const double d = (S - 6.0 * pc) * inv_h2 - Q - cfv[c2] + cb;
-            const int64_t gi = g.off0 + xa + c2 + (int64_t)gy * g.sy + (int64_t)t * g.sz;
-            if (UPDATE) a.phi_out[gi] = pc;
-            a.pt[gi] = (float)pc;
-            a.t0[gi] = (float)t0;
-            a.r[gi] = (float)(-d);
-            acc[R_D2] += d * d;
-            acc[R_D1] += d;
-            acc[R_Q] += Q;
-            acc[R_F] += cfv[c2];
-            acc[R_PHI] += pc;
-            acc[R_GUARD] += gd ? 1.0 : 0.0;
-            acc[R_NONFIN] += isfinite(d) ? 0.0 : 1.0;
+            for (int c2 = 0; c2 < 2; ++c2) {
+                if (DIR && xa + c2 >= g.n0) continue;
+                const int X = 2 * m + c2 + 1;
+                const int xl = split_col<W1>(X - 1), xc = split_col<W1>(X), xr = split_col<W1>(X + 1);
+                Nb v;
+                v.xm = Pc[xl];        v.xp = Pc[xr];
+                v.ym = Pc[xc - W1];   v.yp = Pc[xc + W1];
+                v.zm = Pm[xc];        v.zp = Pp[xc];
+                v.xpyp = Pc[xr + W1]; v.xmym = Pc[xl - W1];
+                v.xpym = Pc[xr - W1]; v.xmyp = Pc[xl + W1];
+                v.xpzp = Pp[xr];      v.xmzm = Pm[xl];
+                v.xpzm = Pm[xr];      v.xmzp = Pp[xl];
+                v.ypzp = Pp[xc + W1]; v.ymzm = Pm[xc - W1];
+                v.ypzm = Pm[xc + W1]; v.ymzp = Pp[xc - W1];
+                const double pc = Pc[xc];
+                double S;
+                bool gd;
+                double t0;
+                const double Q = nl_root_t0(v, cdl.v[c2], a.c, inv_h4, S, gd, t0);
+                const double d = (S - 6.0 * pc) * inv_h2 - Q - cfv.v[c2] + cb;
+                po.v[c2] = pc;
+                pto.v[c2] = (float)pc;
+                t0o.v[c2] = (float)t0;
+                ro.v[c2] = (float)(-d);
+                acc[R_D2] += d * d;
+                acc[R_D1] += d;
+                acc[R_Q] += Q;
+                acc[R_F] += cfv.v[c2];
+                acc[R_PHI] += pc;
+                n_guard += gd ? 1 : 0;
+                n_nonfin += isfinite(d) ? 0 : 1;
+            }
         }
-        __syncthreads();
-        if (pf) store_plane(slot(t + 2), nxt);
-        cdl[0] = ndl[0]; cdl[1] = ndl[1];
-        cfv[0] = nfv[0]; cfv[1] = nfv[1];
+        const int64_t zo = g.base + (int64_t)t * g.sz;
+        if (UPDATE) out64(a.phi_out, zo, po);
+        out32(a.pt, zo, pto);
+        out32(a.t0, zo, t0o);
+        out32(a.r, zo, ro);
+        if (pf) store_plane(t + 2, nxt, nxe);
+        cdl = ndl;
+        cfv = nfv;
         __syncthreads();
     }
+    acc[R_GUARD] = (double)n_guard;
+    acc[R_NONFIN] = (double)n_nonfin;
     block_store_partials(acc, a.partials);
 }
 
@@ -833,9 +854,9 @@ struct CorrResArgs {
 // MODE 3: as MODE 2, with the level's t0 read instead (its base state has not
 //         changed since a MODE 2 pass set it)
 template <int DIR, int MODE>
-__global__ void __launch_bounds__(NT) k_corr_tiled(CorrResArgs a) {
+__global__ void __launch_bounds__(NT, MODE == 2 ? 2 : 4) k_corr_tiled(CorrResArgs a) {
     constexpr int W1 = TX + 2, H1 = MTY + 2, NP1 = W1 * H1, NL1 = (NP1 + NT - 1) / NT;
-    __shared__ float2 EP[3][H1][W1];   // (e, phi~): one 8-byte read per neighbour
+    __shared__ float2 EP[4][H1][W1];   // (e, phi~): one 8-byte read per neighbour
     const Geom& g = a.g;
     const int tid = threadIdx.x;
     int b = xcd_remap(blockIdx.x, gridDim.x);
@@ -846,149 +867,161 @@ __global__ void __launch_bounds__(NT) k_corr_tiled(CorrResArgs a) {
     const int x0 = tx * TX, y0 = ty * MTY, z0 = ch * a.zc;
     const int z1 = min(z0 + a.zc, g.n2);
     double acc[R_NSLOT] = {0, 0, 0, 0, 0, 0, 0};
+    int n_nonfin = 0;
     const float cb = (DIR || MODE >= 2) ? 0.0f : (float)a.sc->cbar;
     const float inv_h2 = 1.0f / a.c.h2;
     const int m = tid & 31, r = tid >> 5;
     const int gy = y0 + r, xa = x0 + 2 * m;
-    const bool row_ok = gy < g.n1;
-    int off1[NL1], lds1[NL1];   // global in-plane offset, LDS word (rows split by parity)
-    bool ok1[NL1];
+    const bool pair_ok = gy < g.n1 && xa < g.n0;   // (periodic grids: n0 even)
+    const int64_t loff0 = g.off0 - g.base;
+    int ob1[NL1], lds1[NL1];   // byte offset in a plane (out of range: zero), LDS word (rows split by parity)
 #pragma unroll
     for (int s2 = 0; s2 < NL1; ++s2) {
         const int e = tid + s2 * NT;
-        ok1[s2] = false;
-        off1[s2] = 0;
+        ob1[s2] = BUF_OOB;
         lds1[s2] = (e / W1) * W1 + split_col<W1>(e % W1);
         if (e < NP1) {
             int gx = x0 - 1 + e % W1, gyy = y0 - 1 + e / W1;
+            bool ok = true;
             if (DIR) {
-                ok1[s2] = gx >= -1 && gx <= g.n0 && gyy >= -1 && gyy <= g.n1;
+                ok = gx >= -1 && gx <= g.n0 && gyy >= -1 && gyy <= g.n1;
             } else {
                 gx = wrapi(gx, g.n0);
                 gyy = wrapi(gyy, g.n1);
-                ok1[s2] = true;
             }
-            off1[s2] = (int)(g.off0 + gx + (int64_t)gyy * g.sy);
+            if (ok) ob1[s2] = (int)(loff0 + gx + (int64_t)gyy * g.sy) * 4;
         }
     }
-    auto plane_off = [&](int t, bool& zok) -> int64_t {
-        int gz;
-        if (DIR) { gz = t; zok = t >= -1 && t <= g.n2; }
-        else { gz = t < 0 ? t + g.n2 : (t >= g.n2 ? t - g.n2 : t); zok = true; }
-        return (int64_t)gz * g.sz;
-    };
+    const int soe = (int)(loff0 + xa + (int64_t)gy * g.sy);   // the pair in a plane
+    const int sob = pair_ok ? soe * 4 : BUF_OOB;
     auto load_planes = [&](int t, float (&re)[NL1], float (&rp)[NL1]) {
-        bool zok;
-        const int64_t zo = plane_off(t, zok);
+        const bool zok = !DIR || (t >= -1 && t <= g.n2);
+        const int64_t zo = g.base + (int64_t)(DIR ? t : wrapi(t, g.n2)) * g.sz;
+        const auto E = plane_rsrc(a.e, zo, 4, zok), P = plane_rsrc(a.pt, zo, 4, zok);
 #pragma unroll
         for (int s2 = 0; s2 < NL1; ++s2) {
-            const bool ok = ok1[s2] && zok && tid + s2 * NT < NP1;
-            re[s2] = ok ? a.e[zo + off1[s2]] : 0.0f;
-            rp[s2] = ok ? a.pt[zo + off1[s2]] : 0.0f;
+            re[s2] = buf_ld_f32(E, ob1[s2]);
+            rp[s2] = buf_ld_f32(P, ob1[s2]);
         }
     };
-    auto store_planes = [&](int sl, const float (&re)[NL1], const float (&rp)[NL1]) {
-        float2* d = &EP[sl][0][0];
+    auto store_planes = [&](int t, const float (&re)[NL1], const float (&rp)[NL1]) {
+        float2* d = &EP[t & 3][0][0];
 #pragma unroll
         for (int s2 = 0; s2 < NL1; ++s2)
             if (tid + s2 * NT < NP1) d[lds1[s2]] = make_float2(re[s2], rp[s2]);
     };
-    auto slot = [](int z) { return (z + 3) % 3; };
     const double inv_h4_64 = 1.0 / (g.h * g.h * g.h * g.h);
-    auto src_fetch = [&](int t, float (&tt)[2], double (&dl)[2], float (&rv)[2]) {
-#pragma unroll
-        for (int c2 = 0; c2 < 2; ++c2) {
-            tt[c2] = 1.0f;
-            dl[c2] = 0.0;
-            rv[c2] = 0.0f;
-            if (!row_ok || xa + c2 >= g.n0 || t >= z1) continue;
-            const int64_t gi = g.off0 + xa + c2 + (int64_t)gy * g.sy + (int64_t)t * g.sz;
-            if (MODE == 2) dl[c2] = a.delta[gi];
-            else tt[c2] = a.t0[gi];   // MODE 1, and MODE 3 (t0 of this level already set)
-            rv[c2] = a.r[gi];
-        }
+    // (an odd row's last pair reads the ghost cell beside it, which is not used)
+    auto src_fetch = [&](int t, Pair32& tt, Pair64& dl, Pair32& rv) {
+        const int64_t zo = g.base + (int64_t)t * g.sz;
+        if (MODE == 2) dl = buf_ld2_f64(plane_rsrc(a.delta, zo, 8, t < z1), pair_ok ? soe * 8 : BUF_OOB);
+        else tt = buf_ld2_f32(plane_rsrc(a.t0, zo, 4, t < z1), sob);   // MODE 1, and MODE 3 (t0 already set)
+        rv = buf_ld2_f32(plane_rsrc(a.r, zo, 4, t < z1), sob);
     };
     {
         float re[NL1], rp[NL1];
         for (int t = z0 - 1; t <= z0 + 1; ++t) {
             load_planes(t, re, rp);
-            store_planes(slot(t), re, rp);
+            store_planes(t, re, rp);
         }
     }
-    float ctt[2], crv[2];
-    double cdl[2];
+    Pair32 ctt{{1.0f, 1.0f}}, crv;
+    Pair64 cdl{{0.0, 0.0}};
     src_fetch(z0, ctt, cdl, crv);
     __syncthreads();
     float zs_e = 0.0f, zs_d = 0.0f, zs_p = 0.0f;
     for (int t = z0; t < z1; ++t) {
-        float ne[NL1], np[NL1], ntt[2], nrv[2];
-        double ndl[2];
+        // (rings of four planes, one barrier per plane: see k_resid_tiled)
+        float ne[NL1], np[NL1];
+        Pair32 ntt{{1.0f, 1.0f}}, nrv;
+        Pair64 ndl{{0.0, 0.0}};
         const bool pf = t + 2 <= z1;
         if (pf) load_planes(t + 2, ne, np);
         src_fetch(t + 1, ntt, ndl, nrv);
-        const int sm = slot(t - 1), sc = slot(t), sp = slot(t + 1);
+        const float2* Pm = &EP[(t - 1) & 3][r + 1][0];
+        const float2* Pc = &EP[t & 3][r + 1][0];
+        const float2* Pp = &EP[(t + 1) & 3][r + 1][0];
         float esum = 0.0f, dsum = 0.0f, psum = 0.0f;
+        Pair32 rout{{0.0f, 0.0f}}, tout{{0.0f, 0.0f}};
+        if (pair_ok) {
 #pragma unroll
-        for (int c2 = 0; c2 < 2; ++c2) {
-            const int X = 2 * m + c2 + 1, Y = r + 1;
-            if (!row_ok || xa + c2 >= g.n0) continue;
-            NbT<float2> v2;
-            v2.xm = EP[sc][Y][split_col<W1>(X - 1)]; v2.xp = EP[sc][Y][split_col<W1>(X + 1)]; v2.ym = EP[sc][Y - 1][split_col<W1>(X)]; v2.yp = EP[sc][Y + 1][split_col<W1>(X)];
-            v2.zm = EP[sm][Y][split_col<W1>(X)]; v2.zp = EP[sp][Y][split_col<W1>(X)];
-            v2.xpyp = EP[sc][Y + 1][split_col<W1>(X + 1)]; v2.xmym = EP[sc][Y - 1][split_col<W1>(X - 1)];
-            v2.xpym = EP[sc][Y - 1][split_col<W1>(X + 1)]; v2.xmyp = EP[sc][Y + 1][split_col<W1>(X - 1)];
-            v2.xpzp = EP[sp][Y][split_col<W1>(X + 1)]; v2.xmzm = EP[sm][Y][split_col<W1>(X - 1)]; v2.xpzm = EP[sm][Y][split_col<W1>(X + 1)]; v2.xmzp = EP[sp][Y][split_col<W1>(X - 1)];
-            v2.ypzp = EP[sp][Y + 1][split_col<W1>(X)]; v2.ymzm = EP[sm][Y - 1][split_col<W1>(X)]; v2.ypzm = EP[sm][Y + 1][split_col<W1>(X)]; v2.ymzp = EP[sp][Y - 1][split_col<W1>(X)];
-            NbT<float> ve, vp;
+            for (int c2 = 0; c2 < 2; ++c2) {
+                if (DIR && xa + c2 >= g.n0) continue;
+                const int X = 2 * m + c2 + 1;
+                const int xl = split_col<W1>(X - 1), xc = split_col<W1>(X), xr = split_col<W1>(X + 1);
+                NbT<float2> v2;
+                v2.xm = Pc[xl];        v2.xp = Pc[xr];
+                v2.ym = Pc[xc - W1];   v2.yp = Pc[xc + W1];
+                v2.zm = Pm[xc];        v2.zp = Pp[xc];
+                v2.xpyp = Pc[xr + W1]; v2.xmym = Pc[xl - W1];
+                v2.xpym = Pc[xr - W1]; v2.xmyp = Pc[xl + W1];
+                v2.xpzp = Pp[xr];      v2.xmzm = Pm[xl];
+                v2.xpzm = Pm[xr];      v2.xmzp = Pp[xl];
+                v2.ypzp = Pp[xc + W1]; v2.ymzm = Pm[xc - W1];
+                v2.ypzm = Pm[xc + W1]; v2.ymzp = Pp[xc - W1];
+                NbT<float> ve, vp;
 #define VMG_SPLIT(q) ve.q = v2.q.x; vp.q = v2.q.y;
-            VMG_SPLIT(xm) VMG_SPLIT(xp) VMG_SPLIT(ym) VMG_SPLIT(yp) VMG_SPLIT(zm) VMG_SPLIT(zp)
-            VMG_SPLIT(xpyp) VMG_SPLIT(xmym) VMG_SPLIT(xpym) VMG_SPLIT(xmyp)
-            VMG_SPLIT(xpzp) VMG_SPLIT(xmzm) VMG_SPLIT(xpzm) VMG_SPLIT(xmzp)
-            VMG_SPLIT(ypzp) VMG_SPLIT(ymzm) VMG_SPLIT(ypzm) VMG_SPLIT(ymzp)
+                VMG_SPLIT(xm) VMG_SPLIT(xp) VMG_SPLIT(ym) VMG_SPLIT(yp) VMG_SPLIT(zm) VMG_SPLIT(zp)
+                VMG_SPLIT(xpyp) VMG_SPLIT(xmym) VMG_SPLIT(xpym) VMG_SPLIT(xmyp)
+                VMG_SPLIT(xpzp) VMG_SPLIT(xmzm) VMG_SPLIT(xpzm) VMG_SPLIT(xmzp)
+                VMG_SPLIT(ypzp) VMG_SPLIT(ymzm) VMG_SPLIT(ypzm) VMG_SPLIT(ymzp)
 #undef VMG_SPLIT
-            const float2 cc = EP[sc][Y][split_col<W1>(X)];
-            const float ecv = cc.x;
-            float t0c = ctt[c2];
-            if (MODE == 2) {
-                Nb vb;
-                vb.xm = vp.xm; vb.xp = vp.xp; vb.ym = vp.ym; vb.yp = vp.yp; vb.zm = vp.zm; vb.zp = vp.zp;
-                vb.xpyp = vp.xpyp; vb.xmym = vp.xmym; vb.xpym = vp.xpym; vb.xmyp = vp.xmyp;
-                vb.xpzp = vp.xpzp; vb.xmzm = vp.xmzm; vb.xpzm = vp.xpzm; vb.xmzp = vp.xmzp;
-                vb.ypzp = vp.ypzp; vb.ymzm = vp.ymzm; vb.ypzm = vp.ypzm; vb.ymzp = vp.ymzp;
-                const double D0 = base_discriminant(vb, cdl[c2], a.c64, inv_h4_64);
-                t0c = (float)(D0 >= 0.0 ? sqrt(D0) : -sqrt(-D0));
-                a.t0out[g.off0 + xa + c2 + (int64_t)gy * g.sy + (int64_t)t * g.sz] = t0c;
+                const float2 cc = Pc[xc];
+                const float ecv = cc.x;
+                float t0c = ctt.v[c2];
+                if (MODE == 2) {
+                    Nb vb;
+                    vb.xm = vp.xm; vb.xp = vp.xp; vb.ym = vp.ym; vb.yp = vp.yp; vb.zm = vp.zm; vb.zp = vp.zp;
+                    vb.xpyp = vp.xpyp; vb.xmym = vp.xmym; vb.xpym = vp.xpym; vb.xmyp = vp.xmyp;
+                    vb.xpzp = vp.xpzp; vb.xmzm = vp.xmzm; vb.xpzm = vp.xpzm; vb.xmzp = vp.xmzp;
+                    vb.ypzp = vp.ypzp; vb.ymzm = vp.ymzm; vb.ypzm = vp.ypzm; vb.ymzp = vp.ymzp;
+                    const double D0 = base_discriminant(vb, cdl.v[c2], a.c64, inv_h4_64);
+                    t0c = (float)(D0 >= 0.0 ? sqrt(D0) : -sqrt(-D0));
+                    tout.v[c2] = t0c;
+                }
+                float Se;
+                const float dq = dq_corr(ve, vp, a.c.a_ih4, Se);
+                const float dQ = dQ_of(dq, t0c, a.c);
+                const float L = (Se - 6.0f * ecv) * inv_h2 - dQ;
+                if (MODE >= 2) {
+                    const float rh = L - crv.v[c2];
+                    rout.v[c2] = rh;
+                    acc[R_Q] += dQ;
+                    acc[R_F] += rh;
+                } else {
+                    const float d = L - crv.v[c2] + cb;
+                    acc[R_D2] += (double)d * d;
+                    acc[R_D1] += d;
+                    acc[R_Q] += dQ;
+                    acc[R_F] += crv.v[c2];
+                    n_nonfin += isfinite(d) ? 0 : 1;
+                    esum += ecv;
+                    dsum += d;
+                    psum += cc.y;
+                }
             }
-            float Se;
-            const float dq = dq_corr(ve, vp, a.c.a_ih4, Se);
-            const float dQ = dQ_of(dq, t0c, a.c);
-            const float L = (Se - 6.0f * ecv) * inv_h2 - dQ;
-            if (MODE >= 2) {
-                const float rh = L - crv[c2];
-                a.rout[g.off0 + xa + c2 + (int64_t)gy * g.sy + (int64_t)t * g.sz] = rh;
-                acc[R_Q] += dQ;
-                acc[R_F] += rh;
-            } else {
-                const float d = L - crv[c2] + cb;
-                acc[R_D2] += (double)d * d;
-                acc[R_D1] += d;
-                acc[R_Q] += dQ;
-                acc[R_F] += crv[c2];
-                acc[R_NONFIN] += isfinite(d) ? 0.0 : 1.0;
-                esum += ecv;
-                dsum += d;
-                psum += cc.y;
+        }
+        if (MODE >= 2) {
+            const int64_t zo = g.base + (int64_t)t * g.sz;
+            const bool half = DIR && xa + 1 >= g.n0;   // an odd row's last cell
+            const auto O = plane_rsrc(a.rout, zo, 4, true);
+            buf_st2_f32(O, half ? BUF_OOB : sob, rout);
+            if (DIR) buf_st_f32(O, half ? sob : BUF_OOB, rout.v[0]);
+            if (MODE == 2) {
+                const auto T = plane_rsrc(a.t0out, zo, 4, true);
+                buf_st2_f32(T, half ? BUF_OOB : sob, tout);
+                if (DIR) buf_st_f32(T, half ? sob : BUF_OOB, tout.v[0]);
             }
         }
         if (MODE == 1) {
-            esum += __shfl_down(esum, 32, 64);
-            dsum += __shfl_down(dsum, 32, 64);
-            psum += __shfl_down(psum, 32, 64);
+            esum = add_high_half(esum);
+            dsum = add_high_half(dsum);
+            psum = add_high_half(psum);
             if ((t & 1) == 0) {
                 zs_e = esum;
                 zs_d = dsum;
                 zs_p = psum;
-            } else if ((r & 1) == 0 && row_ok && xa < g.n0) {
+            } else if ((r & 1) == 0 && pair_ok) {
                 const Geom& gc = a.gc;
                 const int64_t co = gc.off0 + (xa >> 1) + (int64_t)(gy >> 1) * gc.sy + (int64_t)(t >> 1) * gc.sz;
                 const float re = 0.125f * (zs_e + esum);
@@ -998,13 +1031,13 @@ __global__ void __launch_bounds__(NT) k_corr_tiled(CorrResArgs a) {
                 if (a.ptc) a.ptc[co] = 0.125f * (zs_p + psum);
             }
         }
-        __syncthreads();
-        if (pf) store_planes(slot(t + 2), ne, np);
-        ctt[0] = ntt[0]; ctt[1] = ntt[1];
-        cdl[0] = ndl[0]; cdl[1] = ndl[1];
-        crv[0] = nrv[0]; crv[1] = nrv[1];
+        if (pf) store_planes(t + 2, ne, np);
+        ctt = ntt;
+        cdl = ndl;
+        crv = nrv;
         __syncthreads();
     }
+    acc[R_NONFIN] = (double)n_nonfin;
     block_store_partials(acc, a.partials);
 }
 
