@@ -323,7 +323,7 @@ vmg_status vmg_mass_assign_noalloc(const double *pos, int64_t n_particles, const
                                    double *delta, hipStream_t stream);
 
 /* Workspace bytes vmg_mass_assign can use (about 8 bytes per particle plus 12
- * per grid cell, 16 on grids below about 2 M cells), or -1 for arguments
+ * per grid cell, 16 on grids below about 0.5 M cells), or -1 for arguments
  * vmg_mass_assign rejects.  On those smaller grids a call also accepts 12 bytes
  * per cell and then takes a slower path with the same result. */
 int64_t vmg_mass_assign_workspace(int64_t n_particles, const int32_t n[3]);

@@ -722,11 +722,16 @@ static int64_t workspace_of(int64_t np, int n0, int n1, int n2, int B) {
            2 * align256(np * 4) + align256(nb * reg_cells(B) * 8) + align256(nb * 4);
 }
 
-// Grids of fewer than 512 bricks of 16^3 cells (two per CU) are cut into 8^3 ones
-// where the workspace has room for their wider halos: 262144 particles onto 64^3
-// cells (CIC) take 34 us a call so, 51 us with 64 workgroups on 16^3 bricks, whose
-// accumulation alone was 17 us against 8.
-constexpr int64_t SMALL_BRICKS = 512;
+// Grids of fewer than 128 bricks of 16^3 cells are cut into 8^3 ones where the
+// workspace has room for their wider halos: 262144 particles onto 64^3 cells (CIC)
+// take 34 us a call so, 51 us with 64 workgroups on 16^3 bricks, whose accumulation
+// alone was 17 us against 8.  Above that the eightfold number of bricks costs
+// unordered particles more global counter updates than the shorter workgroups save:
+// 152 x 76 x 128 cells (400 bricks), 4.7 M particles in random order, TSC: 207 us,
+// 352 us on 8^3 bricks; 96^3 cells, 1 M particles: 83 us against 126 us (ordered: 64
+// against 66 us).
+constexpr int64_t SMALL_BRICKS = 128;
+constexpr int64_t SPLIT_BRICKS = 1024;
 static bool small_grid(int n0, int n1, int n2) { return bricks_of(n0, n1, n2, 16) < SMALL_BRICKS; }
 
 int64_t mass_assign_workspace_min(int64_t np, int n0, int n1, int n2) { return workspace_of(np, n0, n1, n2, 16); }
@@ -845,12 +850,13 @@ hipError_t launch_mass_assign(const double* pos, int64_t np, int n0, int n1, int
                            listed, idx);
     else
         hipLaunchKernelGGL((k_bin<1, true>), dim3(chunks), dim3(NT), 0, s, g, pos, np, cursor, keys, idx);
-    // workgroups per brick: enough for two per CU, each with at least 2048 particles
-    // of a brick of average content (4.3 M particles in random order onto 32 x 131 x
-    // 28 cells, CIC: 172 us a call, 457 us with one workgroup per 16^3 brick)
+    // workgroups per brick: up to four per CU, each with at least 2048 particles of a
+    // brick of average content (4.3 M particles in random order onto 32 x 131 x 28
+    // cells, CIC: 172 us a call, 457 us with one workgroup per 16^3 brick; the 400
+    // bricks above with ordered particles: 149 us, 222 us with one workgroup each)
     const double content = mean_count * (double)n0 * n1 * n2 / (double)nb;
     int split = 1;
-    while (nb * split < SMALL_BRICKS && content >= 4096.0 * split) split *= 2;
+    while (nb * split < SPLIT_BRICKS && content >= 4096.0 * split) split *= 2;
     // (an order only matters where bricks queue for the CUs)
     if (scheme == 2 && nb > SMALL_BRICKS)
         hipLaunchKernelGGL(k_brick_order, dim3(1), dim3(ORD_NT), 0, s, start, nb, order);
