@@ -70,6 +70,13 @@ __device__ __forceinline__ Pair64 buf_ld2_f64(__amdgpu_buffer_rsrc_t r, int bo) 
 __device__ __forceinline__ Pair32 buf_ld2_f32(__amdgpu_buffer_rsrc_t r, int bo) {
     return __builtin_bit_cast(Pair32, __builtin_amdgcn_raw_buffer_load_b64(r, bo, 0, 0));
 }
+// ... of which only the first one exists where `half`
+__device__ __forceinline__ Pair64 buf_ld2_f64(__amdgpu_buffer_rsrc_t r, int bo, bool half) {
+    Pair64 p = buf_ld2_f64(r, half ? BUF_OOB : bo);
+    const double first = buf_ld_f64(r, half ? bo : BUF_OOB);
+    p.v[0] = half ? first : p.v[0];
+    return p;
+}
 __device__ __forceinline__ void buf_st2_f64(__amdgpu_buffer_rsrc_t r, int bo, const Pair64& p) {
     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(vmg_u32x4, p), r, bo, 0, 0);
 }

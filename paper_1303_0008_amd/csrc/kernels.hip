@@ -246,7 +246,11 @@ struct ResidArgs {
 
 constexpr int RTY = 8;   // rows per residual tile
 
-template <int DIR, int MODE>
+// ODD: rows may have an odd number of cells and end in half a pair (any Dirichlet
+// grid; the coarsest periodic level, whose n0 may be 5 or 7: every level that is
+// coarsened further has an even one).  The cell past such a row is another row's, or
+// past the array: it is not computed, summed, loaded or stored.
+template <int DIR, int MODE, bool ODD = DIR != 0>
 __global__ void __launch_bounds__(NT, 4) k_resid_tiled(ResidArgs a) {
     constexpr int W1 = TX + 2, H1 = RTY + 2;
     constexpr int NP1 = W1 * H1;
@@ -268,7 +272,8 @@ __global__ void __launch_bounds__(NT, 4) k_resid_tiled(ResidArgs a) {
     const int m = tid & 31, r = tid >> 5;           // x pair, row
     const int gy = y0 + r;
     const int xa = x0 + 2 * m;                       // first cell of the pair
-    const bool pair_ok = gy < g.n1 && xa < g.n0;     // (periodic grids: n0 even)
+    const bool pair_ok = gy < g.n1 && xa < g.n0;
+    const bool half = ODD && xa + 1 >= g.n0;         // an odd row's last cell
     const int64_t loff0 = g.off0 - g.base;
 
     int ob1[NL1], lds1[NL1];   // byte offset in a plane (out of range: zero), LDS word (rows split by parity)
@@ -302,12 +307,13 @@ __global__ void __launch_bounds__(NT, 4) k_resid_tiled(ResidArgs a) {
         for (int s = 0; s < NL1; ++s)
             if (tid + s * NT < NP1) dst[lds1[s]] = rr[s];
     };
-    // (an odd row's last pair reads the ghost cell beside it, which is not used)
+    // (a Dirichlet row's half pair reads the ghost cell beside it, which is not used)
+    auto ld_pair = [&](__amdgpu_buffer_rsrc_t p) { return DIR || !ODD ? buf_ld2_f64(p, sob) : buf_ld2_f64(p, sob, half); };
     auto src_fetch = [&](int t, Pair64& dl, Pair64& fv) {
         const int64_t zo = g.base + (int64_t)t * g.sz;
-        dl = buf_ld2_f64(plane_rsrc(a.delta, zo, 8, t < z1), sob);
+        dl = ld_pair(plane_rsrc(a.delta, zo, 8, t < z1));
         fv = Pair64{{0.0, 0.0}};
-        if (a.f) fv = buf_ld2_f64(plane_rsrc(a.f, zo, 8, t < z1), sob);
+        if (a.f) fv = ld_pair(plane_rsrc(a.f, zo, 8, t < z1));
     };
 
     {
@@ -337,7 +343,7 @@ __global__ void __launch_bounds__(NT, 4) k_resid_tiled(ResidArgs a) {
         if (pair_ok) {
 #pragma unroll
             for (int c2 = 0; c2 < 2; ++c2) {
-                if (DIR && xa + c2 >= g.n0) continue;
+                if (ODD && xa + c2 >= g.n0) continue;
                 const int X = 2 * m + c2 + 1;
                 const int xl = split_col<W1>(X - 1), xc = split_col<W1>(X), xr = split_col<W1>(X + 1);
                 Nb v;
@@ -392,9 +398,8 @@ __global__ void __launch_bounds__(NT, 4) k_resid_tiled(ResidArgs a) {
         }
         if (MODE == 2) {
             const auto F = plane_rsrc(a.fout, g.base + (int64_t)t * g.sz, 8, true);
-            const bool half = DIR && xa + 1 >= g.n0;   // an odd row's last cell
             buf_st2_f64(F, half ? BUF_OOB : sob, fout);
-            if (DIR) buf_st_f64(F, half ? sob : BUF_OOB, fout.v[0]);
+            if (ODD) buf_st_f64(F, half ? sob : BUF_OOB, fout.v[0]);
         }
         if (MODE == 1) {
             // y pair: rows 2k and 2k+1 are lanes l and l+32 of one wave
@@ -428,11 +433,14 @@ static hipError_t resid_launch(ResidArgs& a, int mode, int* nblocks_out, hipStre
     a.zc = level_zc((int64_t)a.tiles_x * a.tiles_y, a.g.n2, 32);
     const int nb = a.tiles_x * a.tiles_y * ((a.g.n2 + a.zc - 1) / a.zc);
     *nblocks_out = nb;
-#define RL(D, M) hipLaunchKernelGGL((k_resid_tiled<D, M>), dim3(nb), dim3(NT), 0, s, a)
+#define RL(D, M, O) hipLaunchKernelGGL((k_resid_tiled<D, M, O>), dim3(nb), dim3(NT), 0, s, a)
     if (a.g.dir) {
-        if (mode == 0) RL(1, 0); else if (mode == 1) RL(1, 1); else RL(1, 2);
+        if (mode == 0) RL(1, 0, true); else if (mode == 1) RL(1, 1, true); else RL(1, 2, true);
+    } else if (a.g.n0 & 1) {
+        // a coarsest level: nothing is restricted from it
+        if (mode == 0) RL(0, 0, true); else if (mode == 2) RL(0, 2, true); else return hipErrorInvalidValue;
     } else {
-        if (mode == 0) RL(0, 0); else if (mode == 1) RL(0, 1); else RL(0, 2);
+        if (mode == 0) RL(0, 0, false); else if (mode == 1) RL(0, 1, false); else RL(0, 2, false);
     }
 #undef RL
     return hipGetLastError();

@@ -570,7 +570,8 @@ struct CastArgs {
 
 // Outer FP64 pass: phi_new = phi (+ e), d = L(phi_new) + cbar - f, norm partials,
 // and the inner problem's inputs phi~ = fp32(phi_new), t0 = +-sqrt|D0|, r = -d.
-template <int DIR, bool UPDATE>
+// ODD: rows may end in half a pair (see k_resid_tiled).
+template <int DIR, bool UPDATE, bool ODD = DIR != 0>
 __global__ void __launch_bounds__(NT, 4) k_cast_tiled(CastArgs a) {
     constexpr int W1 = TX + 2, H1 = MTY + 2, NP1 = W1 * H1, NL1 = (NP1 + NT - 1) / NT;
     __shared__ double PH[4][H1][W1];
@@ -589,7 +590,8 @@ __global__ void __launch_bounds__(NT, 4) k_cast_tiled(CastArgs a) {
     const double inv_h2 = 1.0 / (g.h * g.h), inv_h4 = inv_h2 * inv_h2;
     const int m = tid & 31, r = tid >> 5;
     const int gy = y0 + r, xa = x0 + 2 * m;
-    const bool pair_ok = gy < g.n1 && xa < g.n0;   // (periodic grids: n0 even)
+    const bool pair_ok = gy < g.n1 && xa < g.n0;
+    const bool half = ODD && xa + 1 >= g.n0;   // an odd row's last cell
     const int64_t loff0 = g.off0 - g.base;
     int oe1[NL1], lds1[NL1];   // element offset in a plane (-1: zero), LDS word (rows split by parity)
 #pragma unroll
@@ -627,24 +629,27 @@ __global__ void __launch_bounds__(NT, 4) k_cast_tiled(CastArgs a) {
         for (int s2 = 0; s2 < NL1; ++s2)
             if (tid + s2 * NT < NP1) dst[lds1[s2]] = UPDATE ? rr[s2] + (double)re[s2] : rr[s2];
     };
+    auto ld_pair = [&](__amdgpu_buffer_rsrc_t p) {
+        const int sob = pair_ok ? soe * 8 : BUF_OOB;
+        return DIR || !ODD ? buf_ld2_f64(p, sob) : buf_ld2_f64(p, sob, half);
+    };
     auto src_fetch = [&](int t, Pair64& dl, Pair64& fv) {
         const int64_t zo = g.base + (int64_t)t * g.sz;
-        dl = buf_ld2_f64(plane_rsrc(a.delta, zo, 8, t < z1), pair_ok ? soe * 8 : BUF_OOB);
+        dl = ld_pair(plane_rsrc(a.delta, zo, 8, t < z1));
         fv = Pair64{{0.0, 0.0}};
-        if (a.f) fv = buf_ld2_f64(plane_rsrc(a.f, zo, 8, t < z1), pair_ok ? soe * 8 : BUF_OOB);
+        if (a.f) fv = ld_pair(plane_rsrc(a.f, zo, 8, t < z1));
     };
     // the x pair of an output array: one store, or its first cell in an odd row's end
-    const bool half = DIR && xa + 1 >= g.n0;
     const int so2 = pair_ok && !half ? soe : -1, so1 = pair_ok && half ? soe : -1;
     auto out64 = [&](double* p, int64_t zo, const Pair64& v) {
         const auto O = plane_rsrc(p, zo, 8, true);
         buf_st2_f64(O, so2 >= 0 ? so2 * 8 : BUF_OOB, v);
-        if (DIR) buf_st_f64(O, so1 >= 0 ? so1 * 8 : BUF_OOB, v.v[0]);
+        if (ODD) buf_st_f64(O, so1 >= 0 ? so1 * 8 : BUF_OOB, v.v[0]);
     };
     auto out32 = [&](float* p, int64_t zo, const Pair32& v) {
         const auto O = plane_rsrc(p, zo, 4, true);
         buf_st2_f32(O, so2 >= 0 ? so2 * 4 : BUF_OOB, v);
-        if (DIR) buf_st_f32(O, so1 >= 0 ? so1 * 4 : BUF_OOB, v.v[0]);
+        if (ODD) buf_st_f32(O, so1 >= 0 ? so1 * 4 : BUF_OOB, v.v[0]);
     };
     {
         double rr[NL1];
@@ -673,7 +678,7 @@ __global__ void __launch_bounds__(NT, 4) k_cast_tiled(CastArgs a) {
         if (pair_ok) {
 #pragma unroll
             for (int c2 = 0; c2 < 2; ++c2) {
-                if (DIR && xa + c2 >= g.n0) continue;
+                if (ODD && xa + c2 >= g.n0) continue;
                 const int X = 2 * m + c2 + 1;
                 const int xl = split_col<W1>(X - 1), xc = split_col<W1>(X), xr = split_col<W1>(X + 1);
                 Nb v;
@@ -872,7 +877,7 @@ __global__ void __launch_bounds__(NT, MODE == 2 ? 2 : 4) k_corr_tiled(CorrResArg
     const float inv_h2 = 1.0f / a.c.h2;
     const int m = tid & 31, r = tid >> 5;
     const int gy = y0 + r, xa = x0 + 2 * m;
-    const bool pair_ok = gy < g.n1 && xa < g.n0;   // (periodic grids: n0 even)
+    const bool pair_ok = gy < g.n1 && xa < g.n0;   // (periodic: n0 even, checked at launch)
     const int64_t loff0 = g.off0 - g.base;
     int ob1[NL1], lds1[NL1];   // byte offset in a plane (out of range: zero), LDS word (rows split by parity)
 #pragma unroll
@@ -1310,6 +1315,7 @@ hipError_t launch_rr_corr(const Geom& gf, const Geom& gc, const CoefF& c, const 
     std::memset(&a, 0, sizeof(a));
     a.g = gf; a.gc = gc; a.c = c; a.e = e; a.pt = pt; a.t0 = t0; a.r = r; a.sc = sc;
     a.ec = ec; a.eold_c = eold_c; a.rd_c = rd_c; a.ptc = ptc; a.partials = partials;
+    if (!gf.dir && (gf.n0 & 1)) return hipErrorInvalidValue;   // no level below it
     int nb;
     corr_tiles(gf, a.tiles_x, a.tiles_y, a.zc, nb);
     *nblocks_out = nb;
@@ -1328,6 +1334,9 @@ hipError_t launch_fas_corr(const Geom& g, const CoefF& c, const Coef& c64, const
     a.g = g; a.c = c; a.c64 = c64; a.delta = delta; a.e = e; a.pt = pt; a.t0out = t0; a.r = rd; a.rout = r;
     a.t0 = t0;
     a.partials = partials;
+    // a periodic level of odd n0 is a coarsest one of at most 8^3 cells: the head of
+    // the level above forms its right-hand side (launch_head_corr)
+    if (!g.dir && (g.n0 & 1)) return hipErrorInvalidValue;
     int nb;
     corr_tiles(g, a.tiles_x, a.tiles_y, a.zc, nb);
     *nblocks_out = nb;
@@ -1367,6 +1376,9 @@ hipError_t launch_cast_update(const Geom& g, const Coef& c, const double* phi, c
     if (g.dir) {
         if (up) hipLaunchKernelGGL((k_cast_tiled<1, true>), dim3(nb), dim3(NT), 0, s, a);
         else hipLaunchKernelGGL((k_cast_tiled<1, false>), dim3(nb), dim3(NT), 0, s, a);
+    } else if (g.n0 & 1) {
+        if (up) hipLaunchKernelGGL((k_cast_tiled<0, true, true>), dim3(nb), dim3(NT), 0, s, a);
+        else hipLaunchKernelGGL((k_cast_tiled<0, false, true>), dim3(nb), dim3(NT), 0, s, a);
     } else {
         if (up) hipLaunchKernelGGL((k_cast_tiled<0, true>), dim3(nb), dim3(NT), 0, s, a);
         else hipLaunchKernelGGL((k_cast_tiled<0, false>), dim3(nb), dim3(NT), 0, s, a);
