@@ -594,7 +594,7 @@ __device__ __forceinline__ void brick_store_ghosts(const K& k, const Geom& g, in
                 if ((dx != 0 && gx >= 0 && gx < g.n0) || (dy != 0 && gy >= 0 && gy < g.n1) ||
                     (dz != 0 && gz >= 0 && gz < g.n2))
                     continue;                         // a step that stays inside: not a ghost of this cell
-                k.store_ghost(small_index(g, gx, gy, gz), ii, out == 1 ? -1 : 1, v);
+                k.store_ghost(small_index<1>(g, gx, gy, gz), ii, out == 1 ? -1 : 1, v);
             }
 }
 
@@ -648,10 +648,10 @@ __device__ __forceinline__ void brick_sweeps(K& k, const Geom& g, int bx0, int b
             const int x = e % RW, y = (e / RW) % RW, z = e / RW2;
             if (DIR) {
                 const int gx = bx0 - R + x, gy = by0 - R + y, gz = bz0 - R + z;
-                u0[q] = in_shell(g, gx, gy, gz) ? k.load_cell(small_index(g, gx, gy, gz)) : Cell{};
+                u0[q] = in_shell(g, gx, gy, gz) ? k.load_cell(small_index<1>(g, gx, gy, gz)) : Cell{};
             } else {
-                u0[q] = k.load_cell(small_index(g, wrapi(bx0 - R + x, g.n0), wrapi(by0 - R + y, g.n1),
-                                               wrapi(bz0 - R + z, g.n2)));
+                u0[q] = k.load_cell(small_index<0>(g, wrapi(bx0 - R + x, g.n0), wrapi(by0 - R + y, g.n1),
+                                                  wrapi(bz0 - R + z, g.n2)));
             }
         }
     }
@@ -667,10 +667,10 @@ __device__ __forceinline__ void brick_sweeps(K& k, const Geom& g, int bx0, int b
             const int x = e % RS, y = (e / RS) % RS, z = e / (RS * RS);
             if (DIR) {
                 const int gx = bx0 - R + 1 + x, gy = by0 - R + 1 + y, gz = bz0 - R + 1 + z;
-                s0[q] = in_shell(g, gx, gy, gz) ? k.load_src(small_index(g, gx, gy, gz)) : Src{};
+                s0[q] = in_shell(g, gx, gy, gz) ? k.load_src(small_index<1>(g, gx, gy, gz)) : Src{};
             } else {
-                s0[q] = k.load_src(small_index(g, wrapi(bx0 - R + 1 + x, g.n0), wrapi(by0 - R + 1 + y, g.n1),
-                                              wrapi(bz0 - R + 1 + z, g.n2)));
+                s0[q] = k.load_src(small_index<0>(g, wrapi(bx0 - R + 1 + x, g.n0), wrapi(by0 - R + 1 + y, g.n1),
+                                                 wrapi(bz0 - R + 1 + z, g.n2)));
             }
         }
     }
@@ -684,8 +684,8 @@ __device__ __forceinline__ void brick_sweeps(K& k, const Geom& g, int bx0, int b
             const int e = tid + q * NTH;
             if (e < NCW) {
                 const int x = e % CW, y = (e / CW) % CW, z = e / (CW * CW);
-                c0[q] = k.load_corr(small_index(k.gc, wrapi(cx0 + x, k.gc.n0), wrapi(cy0 + y, k.gc.n1),
-                                               wrapi(cz0 + z, k.gc.n2)));
+                c0[q] = k.load_corr(small_index<0>(k.gc, wrapi(cx0 + x, k.gc.n0), wrapi(cy0 + y, k.gc.n1),
+                                                  wrapi(cz0 + z, k.gc.n2)));
             }
         }
     }
@@ -783,7 +783,7 @@ __device__ __forceinline__ void brick_sweeps(K& k, const Geom& g, int bx0, int b
         const int gx = bx0 + x, gy = by0 + y, gz = bz0 + z;
         if (gx < g.n0 && gy < g.n1 && gz < g.n2) {
             const Cell v = U[((z + R) * RW + (y + R)) * RW + (x + R)];
-            const int64_t ii = small_index(g, gx, gy, gz);
+            const int64_t ii = small_index<DIR>(g, gx, gy, gz);
             k.store_cell(ii, v);
             if (GHOSTS) brick_store_ghosts(k, g, gx, gy, gz, ii, v);
         }

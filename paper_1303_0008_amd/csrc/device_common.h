@@ -336,10 +336,16 @@ __device__ __forceinline__ int64_t cell_index(const Geom& g, int i, int j, int k
     return g.off0 + i + (int64_t)j * (int)g.sy + (int64_t)k * (int)g.sz;
 }
 
-// The same for levels of fewer than 2^31 elements with fewer than 2^23 rows (all
-// that bricks run on), by full-rate 24-bit multiplies.
-__device__ __forceinline__ int64_t small_index(const Geom& g, int i, int j, int k) {
-    return g.off0 + (__mul24(__mul24(k, g.n1 + (g.dir ? 2 : 0)) + j, (int)g.sy) + i);
+// The same for levels of fewer than 2^32 elements with fewer than 2^24 rows, by
+// full-rate 24-bit multiplies: all that bricks run on.  (A Dirichlet grid of 2^31
+// cells, the most its work items can count, has 2 % more elements than that, so
+// the offset from the storage's start, ghost shell included, is kept unsigned.)
+template <int DIR>
+__host__ __device__ __forceinline__ int64_t small_index(const Geom& g, int i, int j, int k) {
+    auto mul24 = [](unsigned a, unsigned b) { return (a & 0xffffffu) * (b & 0xffffffu); };
+    constexpr int s = DIR ? 1 : 0;   // cells of the shell before the first
+    const unsigned row = mul24(k + s, g.n1 + 2 * s) + (unsigned)(j + s);
+    return g.base + (int64_t)(mul24(row, (unsigned)g.sy) + (unsigned)(i + s));
 }
 
 // 18 neighbours of cell (i,j,k) read through global memory (periodic wrap or ghost shell)

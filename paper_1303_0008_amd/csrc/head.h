@@ -56,13 +56,13 @@ __device__ __forceinline__ void head_brick(const K& k, const Geom& g, const Geom
     for (int q = 0; q < NL; ++q) {
         const int e = tid + q * HEAD_NT;
         if (e < NU)
-            u0[q] = k.load_cell(small_index(g, wrapi(bx0 - 2 + e % RW, g.n0), wrapi(by0 - 2 + (e / RW) % RW, g.n1),
-                                            wrapi(bz0 - 2 + e / RW2, g.n2)));
+            u0[q] = k.load_cell(small_index<0>(g, wrapi(bx0 - 2 + e % RW, g.n0), wrapi(by0 - 2 + (e / RW) % RW, g.n1),
+                                               wrapi(bz0 - 2 + e / RW2, g.n2)));
     }
     typename K::Src src{};
-    if (ok) src = k.load_src(small_index(g, bx0 + x, by0 + y, bz0 + z));
+    if (ok) src = k.load_src(small_index<0>(g, bx0 + x, by0 + y, bz0 + z));
     typename K::CSrc csrc{};
-    const int64_t ci = cok ? small_index(gc, cx, cy, cz) : 0;
+    const int64_t ci = cok ? small_index<0>(gc, cx, cy, cz) : 0;
     if (cok) csrc = k.load_csrc(ci);
 #pragma unroll
     for (int q = 0; q < NL; ++q) {

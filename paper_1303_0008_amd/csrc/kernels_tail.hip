@@ -491,7 +491,7 @@ struct BatchLev {
             cell[q] = typename K::Cell{};
         }
     }
-    __device__ int64_t element(const Geom& g, int q) const { return small_index(g, i[q], j, z); }
+    __device__ int64_t element(const Geom& g, int q) const { return small_index<1>(g, i[q], j, z); }
     // ghosts: places, signs and their references from the pool
     __device__ void init_ghosts(const Geom& g, const T* __restrict__ old) {
         const int count = (int)ghost_count_dev(n0, n1, n2);
@@ -507,7 +507,7 @@ struct BatchLev {
             gi[q] = at(x, y, w);
             gm[q] = at(mx, my, mz);
             gs[q] = (T)sign;
-            og[q] = old[small_index(g, x, y, w)];
+            og[q] = old[small_index<1>(g, x, y, w)];
         }
     }
     // the references of the mirrored cells: ref(x, y, z), or a cube of this pitch
