@@ -341,7 +341,10 @@ vmg_status vmg_smooth(vmg_plan *plan, int32_t sweeps);
 /* Measurement hook: with enable != 0, every finest-level sweep that later
  * solves launch is bracketed by HIP events on the plan's stream, and
  * vmg_plan_sweep_time returns the summed duration (microseconds) and the number
- * of those launches since this call.  While it is enabled a VMG_GRAPH plan
+ * of those launches since this call.  (A launch holds one sweep, or up to two
+ * where the finest periodic level runs bricks; the launches that also prolong the
+ * coarse correction, or start the mixed path's inner problem from zero, are
+ * other kernels and not counted.)  While it is enabled a VMG_GRAPH plan
  * issues its iterations directly instead of replaying graphs (event nodes of a
  * graph carry no timestamps on this runtime): the same kernels on the same
  * data, launched one by one.  enable = 0 stops it and records the graphs again.
@@ -381,7 +384,7 @@ vmg_status vmg_plan_history(const vmg_plan *plan, int32_t grid, vmg_history *out
 
 /* Counters of the last vmg_solve (host pointers, each may be NULL):
  * cell_updates  = smoother cell updates over all levels and sweeps,
- * finest_sweeps = finest-level smoother sweeps (launches of that kernel),
+ * finest_sweeps = finest-level smoother sweeps,
  * finest_cells  = cells of the finest level(s) per sweep. */
 vmg_status vmg_plan_stats(const vmg_plan *plan, int64_t *cell_updates, int64_t *finest_sweeps,
                           int64_t *finest_cells);

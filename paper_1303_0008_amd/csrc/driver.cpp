@@ -262,7 +262,7 @@ hipError_t settle_cbar(Plan* P, LevelBuf& L, LevelScalars* sc) {
 static hipError_t smooth_level_n(Plan* P, GridState& G, int l, int count, const ProlongIn* pro = nullptr) {
     LevelBuf& L = G.lev[l];
     const SmoothCfg cfg = level_schedule(P, l, L.g);
-    const int per = cfg.pipe == PIPE_BRICK ? 2 : 1;
+    const int per = sweeps_per_launch(cfg);
     if (count > 0 && per == 1) {
         hipError_t e = settle_cbar(P, L, L.sc);
         if (e != hipSuccess) return e;
@@ -280,10 +280,6 @@ static hipError_t smooth_level_n(Plan* P, GridState& G, int l, int count, const 
         s += n;
     }
     return hipSuccess;
-}
-
-static hipError_t smooth_level(Plan* P, GridState& G, int l, const ProlongIn* pro = nullptr) {
-    return smooth_level_n(P, G, l, 1, pro);
 }
 
 hipError_t smooth_level_public(Plan* P, GridState& G, int l, int count) { return smooth_level_n(P, G, l, count); }
@@ -352,10 +348,10 @@ static hipError_t vcycle_head(Plan* P, GridState& G, int l, NormOut* norm) {
     LevelBuf& L = G.lev[l];
     hipError_t e;
     if ((e = level_mark(P, l, true)) != hipSuccess) return e;
-    const int nu1 = pre_sweeps(P, l);
-    if (l == 0 && (e = sweep_mark(P, true, nu1)) != hipSuccess) return e;
+    const int nu1 = pre_sweeps(P, l), launches = sweep_launches(level_schedule(P, l, L.g), nu1);
+    if (l == 0 && (e = sweep_mark(P, true, launches)) != hipSuccess) return e;
     if ((e = smooth_level_n(P, G, l, nu1)) != hipSuccess) return e;
-    if (l == 0 && (e = sweep_mark(P, false, nu1)) != hipSuccess) return e;
+    if (l == 0 && (e = sweep_mark(P, false, launches)) != hipSuccess) return e;
     LevelBuf& C = G.lev[l + 1];
     C.cur = 0;
     if ((e = settle_cbar(P, L, L.sc)) != hipSuccess) return e;   // (without pre-sweeps)
@@ -396,21 +392,23 @@ static hipError_t vcycle_head(Plan* P, GridState& G, int l, NormOut* norm) {
 }
 
 // phi^h += P(phi^H - phi^H_old), then nu2 sweeps of level l: on periodic grids
-// the prolongation is folded into the first sweep where that pays (on the
-// finest level that sweep is not timed with the plain ones)
+// the prolongation is folded into the first launch of sweeps where that pays (on
+// the finest level that launch is not timed with the plain ones)
 hipError_t post_smooth(Plan* P, GridState& G, int l, int nu2) {
     LevelBuf& L = G.lev[l];
     LevelBuf& C = G.lev[l + 1];
     hipError_t e;
-    const int s0 = nu2 > 0 && fold_prolong_here(P, L.g, C.g, level_schedule(P, l, L.g)) ? 1 : 0;
+    const SmoothCfg cfg = level_schedule(P, l, L.g);
+    const bool fold = nu2 > 0 && fold_prolong_here(P, L.g, C.g, cfg);
+    const int n0 = fold ? std::min(nu2, sweeps_per_launch(cfg)) : 0;   // sweeps of that launch
     const ProlongIn pro{C.g, C.phi[C.cur], C.phiold};
-    if (!s0 && (e = launch_prolong(L.g, C.g, L.phi[L.cur], C.phi[C.cur], C.phiold, P->stream)) != hipSuccess)
-        return e;
-    if (l > 0 || !P->time_sweeps) return smooth_level_n(P, G, l, nu2, s0 ? &pro : nullptr);
-    if (s0 && (e = smooth_level(P, G, l, &pro)) != hipSuccess) return e;
-    if ((e = sweep_mark(P, true, nu2 - s0)) != hipSuccess) return e;
-    if ((e = smooth_level_n(P, G, l, nu2 - s0)) != hipSuccess) return e;
-    return sweep_mark(P, false, nu2 - s0);
+    if (fold) e = smooth_level_n(P, G, l, n0, &pro);
+    else e = launch_prolong(L.g, C.g, L.phi[L.cur], C.phi[C.cur], C.phiold, P->stream);
+    if (e != hipSuccess) return e;
+    const int launches = l == 0 ? sweep_launches(cfg, nu2 - n0) : 0;
+    if ((e = sweep_mark(P, true, launches)) != hipSuccess) return e;
+    if ((e = smooth_level_n(P, G, l, nu2 - n0)) != hipSuccess) return e;
+    return sweep_mark(P, false, launches);
 }
 
 static hipError_t vcycle_tail(Plan* P, GridState& G, int l) {
@@ -1232,7 +1230,7 @@ vmg_status vmg_smooth(vmg_plan* plan, int32_t sweeps) {
             CKH(batch_smooth_finest(P));
             continue;
         }
-        for (auto& G : P->grids) CKH(P->mixed ? smooth_corr_level(P, G, 0) : smooth_level(P, G, 0));
+        for (auto& G : P->grids) CKH(P->mixed ? smooth_corr_level_n(P, G, 0, 1) : smooth_level_n(P, G, 0, 1));
     }
     return VMG_OK;
 }

@@ -62,7 +62,7 @@ hipError_t smooth_corr_level_n(Plan* P, GridState& G, int l, int count, bool zer
     LevelBuf& L = G.lev[l];
     const CoefF cf = make_coef_f(P->coef, L.g.h);
     const SmoothCfg cfg = level_schedule(P, l, L.g);
-    const int per = cfg.pipe == PIPE_BRICK ? 2 : 1;
+    const int per = sweeps_per_launch(cfg);
     if (count > 0 && per == 1) {
         hipError_t e = settle_cbar(P, L, L.scf);
         if (e != hipSuccess) return e;
@@ -82,26 +82,24 @@ hipError_t smooth_corr_level_n(Plan* P, GridState& G, int l, int count, bool zer
     return hipSuccess;
 }
 
-hipError_t smooth_corr_level(Plan* P, GridState& G, int l, bool zero_in, const ProlongInF* pro) {
-    return smooth_corr_level_n(P, G, l, 1, zero_in, pro);
-}
-
 // e^h += P(e^H - e^H_old), then nu2 correction sweeps of level l: on periodic
-// grids the prolongation is folded into the first sweep where that pays (on the
-// finest level that sweep is not timed with the plain ones)
+// grids the prolongation is folded into the first launch of sweeps where that pays
+// (on the finest level that launch is not timed with the plain ones)
 hipError_t post_smooth_corr(Plan* P, GridState& G, int l, int nu2) {
     LevelBuf& L = G.lev[l];
     LevelBuf& C = G.lev[l + 1];
     hipError_t e;
-    const int s0 = nu2 > 0 && fold_prolong_here(P, L.g, C.g, level_schedule(P, l, L.g)) ? 1 : 0;
+    const SmoothCfg cfg = level_schedule(P, l, L.g);
+    const bool fold = nu2 > 0 && fold_prolong_here(P, L.g, C.g, cfg);
+    const int n0 = fold ? std::min(nu2, sweeps_per_launch(cfg)) : 0;   // sweeps of that launch
     const ProlongInF pro{C.g, C.e[C.ecur], C.eold};
-    if (!s0 && (e = launch_prolong_corr(L.g, C.g, L.e[L.ecur], C.e[C.ecur], C.eold, P->stream)) != hipSuccess)
-        return e;
-    if (l > 0 || !P->time_sweeps) return smooth_corr_level_n(P, G, l, nu2, false, s0 ? &pro : nullptr);
-    if (s0 && (e = smooth_corr_level(P, G, l, false, &pro)) != hipSuccess) return e;
-    if ((e = sweep_mark(P, true, nu2 - s0)) != hipSuccess) return e;
-    if ((e = smooth_corr_level_n(P, G, l, nu2 - s0, false, nullptr)) != hipSuccess) return e;
-    return sweep_mark(P, false, nu2 - s0);
+    if (fold) e = smooth_corr_level_n(P, G, l, n0, false, &pro);
+    else e = launch_prolong_corr(L.g, C.g, L.e[L.ecur], C.e[C.ecur], C.eold, P->stream);
+    if (e != hipSuccess) return e;
+    const int launches = l == 0 ? sweep_launches(cfg, nu2 - n0) : 0;
+    if ((e = sweep_mark(P, true, launches)) != hipSuccess) return e;
+    if ((e = smooth_corr_level_n(P, G, l, nu2 - n0)) != hipSuccess) return e;
+    return sweep_mark(P, false, launches);
 }
 
 // The periodic coarse tail of the inner cycle: levels l..last in one launch.
@@ -153,18 +151,15 @@ static hipError_t inner_vcycle(Plan* P, GridState& G, int l, bool zero_e, bool f
         return level_mark(P, l, false);
     }
     if ((e = level_mark(P, l, true)) != hipSuccess) return e;
-    // the sweep that reads no correction (zero_e) is another kernel: it is not timed
+    // the launch that reads no correction (zero_e) is another kernel: it is not timed
+    const SmoothCfg cfg = level_schedule(P, l, L.g);
     const int nu1 = pre_sweeps(P, l);
-    const int t1 = zero_e ? nu1 - 1 : nu1;
-    if (l > 0 || !P->time_sweeps) {
-        if ((e = smooth_corr_level_n(P, G, l, nu1, zero_e)) != hipSuccess) return e;
-    } else {
-        for (int s = 0; s < nu1; ++s) {
-            if (s == nu1 - t1 && (e = sweep_mark(P, true, t1)) != hipSuccess) return e;
-            if ((e = smooth_corr_level(P, G, l, zero_e && s == 0)) != hipSuccess) return e;
-        }
-        if (t1 > 0 && (e = sweep_mark(P, false, t1)) != hipSuccess) return e;
-    }
+    const int n0 = zero_e ? std::min(nu1, sweeps_per_launch(cfg)) : 0;   // its sweeps
+    if (zero_e && (e = smooth_corr_level_n(P, G, l, n0, true)) != hipSuccess) return e;
+    const int launches = l == 0 ? sweep_launches(cfg, nu1 - n0) : 0;
+    if ((e = sweep_mark(P, true, launches)) != hipSuccess) return e;
+    if ((e = smooth_corr_level_n(P, G, l, nu1 - n0)) != hipSuccess) return e;
+    if ((e = sweep_mark(P, false, launches)) != hipSuccess) return e;
     LevelBuf& C = G.lev[l + 1];
     const CoefF cc = make_coef_f(P->coef, C.g.h);
     C.ecur = 0;

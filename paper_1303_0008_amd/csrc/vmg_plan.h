@@ -167,7 +167,6 @@ vmg_status alloc_mixed(Plan* P);
 hipError_t enqueue_outer(Plan* P);          // one mixed-precision outer iteration (+ norms to host)
 hipError_t mixed_initial_pass(Plan* P);     // cast pass of the initial guess (+ norms to host)
 hipError_t mixed_prepare(Plan* P);          // per-solve set-up of the FP32 ghost shells
-hipError_t smooth_corr_level(Plan* P, GridState& G, int l, bool zero_in = false, const ProlongInF* pro = nullptr);
 hipError_t smooth_corr_level_n(Plan* P, GridState& G, int l, int count, bool zero_in = false,
                                const ProlongInF* pro = nullptr);
 // coarse-correction prolongation + nu2 post-sweeps of level l (FP64 / correction)
@@ -202,6 +201,11 @@ inline bool one_launch_head(const GridState& G, int l) {
 }
 // schedule of the fused sweep on level l of a single-grid (periodic) plan
 SmoothCfg level_schedule(const Plan* P, int l, const Geom& g);
+// sweeps one launch of such a level holds at most, and launches of `count` sweeps
+inline int sweeps_per_launch(const SmoothCfg& cfg) { return cfg.pipe == PIPE_BRICK ? 2 : 1; }
+inline int sweep_launches(const SmoothCfg& cfg, int count) {
+    return (count + sweeps_per_launch(cfg) - 1) / sweeps_per_launch(cfg);
+}
 // first level handled by the periodic coarse tail (FP64 plans), or -1
 int tail_level(const Plan* P, const GridState& G);
 // batched plans: rebuild the persistent smoother's work list of level l for cfg;
