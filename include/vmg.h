@@ -393,8 +393,8 @@ vmg_status vmg_plan_stats(const vmg_plan *plan, int64_t *cell_updates, int64_t *
  * z-chunk of the finest level's fused sweep (chosen by the autotuner with
  * VMG_AUTOTUNE, which times every swept level's smoother for tile heights
  * {4,8,12,16} x z chunks x pipeline shapes, plus the brick schedule on the
- * coarser levels of a periodic plan and on every level of a Dirichlet batch,
- * at plan creation, and installs a
+ * coarser levels of a periodic plan, on its finest one below 2^18 cells and on
+ * every level of a Dirichlet batch, at plan creation, and installs a
  * cached cycle schedule of vmg_plan_tune_cycle; Sec. V of the paper notes the
  * code needed more tuning), pre/post sweeps and coarsest-level sweeps.
  * Errors: VMG_EINVAL. */
@@ -461,18 +461,24 @@ int32_t vmg_plan_level_count(const vmg_plan *plan);
  * step, three-plane LDS rings), 1 = two planes behind (one barrier, four-plane
  * rings); or, with pipe 2, the brick schedule: no z march, 8^3 bricks whose
  * rings are recomputed by every block, up to two sweeps per launch on a
- * coarser level of a periodic plan, one sweep per launch (the ghost shell as
- * the boundary) on any level of a Dirichlet batch (tile_y and z_chunk are then
- * only validated).
+ * periodic level, one sweep per launch (the ghost shell as the boundary) on any
+ * level of a Dirichlet batch (tile_y and z_chunk are then only validated).  On
+ * the finest level of a periodic plan pipe 2 is accepted only as tile_y 8,
+ * z_chunk 8, which is what vmg_plan_schedule reports for it, and only where that
+ * level has at most 2^18 cells and a coarser one below it; untuned plans run it
+ * there.  A Dirichlet batch runs every grid's levels of at most 8 cells per axis
+ * in one launch per cycle; a schedule of such a level is accepted and reported,
+ * and not used.
  * The schedule changes only the blocking of the same red-black update, not the
  * result's definition.  With VMG_GRAPH the iteration graphs are recorded again
  * (allocates).  Errors: VMG_EINVAL (null plan, level outside [0,
  * vmg_plan_level_count), tile_y not in {4, 8, 12, 16}, z_chunk odd or outside
- * [2, 1024], pipe not 0, 1 or 2, pipe 2 on the finest level of a periodic
- * plan), VMG_EHIP. */
+ * [2, 1024], pipe not 0, 1 or 2, any other pipe 2 on the finest level of a
+ * periodic plan), VMG_EHIP. */
 vmg_status vmg_plan_set_schedule(vmg_plan *plan, int32_t level, int32_t tile_y, int32_t z_chunk, int32_t pipe);
 
-/* The sweep schedule a level runs (host pointers, each may be NULL).
+/* The sweep schedule a level runs (host pointers, each may be NULL); installing
+ * it again changes nothing.
  * Errors: VMG_EINVAL (null plan, level outside [0, vmg_plan_level_count)). */
 vmg_status vmg_plan_schedule(const vmg_plan *plan, int32_t level, int32_t *tile_y, int32_t *z_chunk,
                              int32_t *pipe);

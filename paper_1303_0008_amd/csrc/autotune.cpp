@@ -6,8 +6,9 @@
 //    heights {8,4,16,12} x z chunks ({16,8,32,64} on the finest level,
 //    {16,8,4,2} below, since short chunks spread small grids over the chip) x
 //    both pipeline shapes, plus the brick schedule (without the z march: two
-//    sweeps per launch on the coarser levels of a periodic plan, one on every
-//    level of a Dirichlet batch), and keep the fastest.
+//    sweeps per launch on the coarser levels of a periodic plan and on a finest
+//    level of fewer than 2^18 cells, one on every level of a Dirichlet batch), and
+//    keep the fastest.
 //  * The cycle schedule, on request (vmg_plan_tune_cycle): time complete
 //    solves of a given input (from the caller's initial guess) to the plan's
 //    tolerance for candidate nu1/nu2,
@@ -192,10 +193,11 @@ vmg_status autotune(Plan* P) {
     for (int l = 0; l < nlev && st == VMG_OK; ++l) {
         const std::string key = tune_key(P, l);
         SmoothCfg best;
-        // the brick schedule runs on the coarser levels of periodic plans and on
-        // every level of Dirichlet batches
+        // the brick schedule runs on the coarser levels of periodic plans, on a small
+        // finest one, and on every level of Dirichlet batches
+        const bool bricks = l > 0 || P->batched || finest_may_run_bricks(P);
         if (P->batched && P->blev[l].nsitems == 0) continue;   // run by the coarse tails
-        if (cached(key, best) && (best.pipe != PIPE_BRICK || l > 0 || P->batched)) {
+        if (cached(key, best) && (best.pipe != PIPE_BRICK || bricks)) {
             P->tuned_from_cache = true;
             if (apply(P, l, best) != hipSuccess) st = fail(VMG_EHIP, "autotune: work list upload failed");
             continue;
@@ -210,9 +212,12 @@ vmg_status autotune(Plan* P) {
                 else
                     for (int b = 0; b < 4; ++b) cands.push_back(SmoothCfg{tys[a], zcoarse[b], pipe});
             }
-        // coarser periodic levels may also run their sweeps in pairs on bricks, and
-        // Dirichlet batches one at a time on every level
-        if (l > 0 || P->batched) cands.push_back(SmoothCfg{8, 8, PIPE_BRICK});
+        // periodic levels may also run their sweeps in pairs on bricks, and Dirichlet
+        // batches one at a time on every level; on a finest level of BRICK_CELLS cells
+        // a whole cycle is faster on the best march (default_march has the figures),
+        // which sweeps timed by themselves do not show
+        if (bricks && (l > 0 || P->batched || P->grids[0].lev[0].g.ncell < BRICK_CELLS))
+            cands.push_back(SmoothCfg{8, 8, PIPE_BRICK});
         double best_us = 1e300;
         // the finest level: plain sweeps; below it, a V(2,2) cycle's smoothing (two
         // sweeps, the coarse correction, two sweeps) per repetition

@@ -116,6 +116,7 @@ vmg_status build_plan(Plan* P, const vmg_grid* grids, int n_grids, const vmg_par
         max_cells = std::max<int64_t>(max_cells, G.lev[0].g.ncell);
         P->grids.push_back(G);
     }
+    if (finest_may_run_bricks(P)) P->cfg = SmoothCfg{8, 8, PIPE_BRICK};
     P->mixed = p->prec == VMG_MIXED;
     P->batched = !P->periodic;
     vmg_status st;
@@ -173,8 +174,6 @@ vmg_status build_plan(Plan* P, const vmg_grid* grids, int n_grids, const vmg_par
         if ((st = autotune(P)) != VMG_OK) return st;
         CKH(hipStreamSynchronize(stream));
     }
-    // (after the tuner, which times marches on the finest level)
-    P->small_finest = P->periodic && P->grids[0].lev.size() > 1 && P->grids[0].lev[0].g.ncell <= BRICK_CELLS;
     return VMG_OK;
 }
 
@@ -291,13 +290,11 @@ bool fold_prolong_here(const Plan* P, const Geom& g, const Geom& gc, const Smoot
     return can_fold_prolong(g, gc, zc) && fold_prolong_pays(g, zc);
 }
 
-// The finest level runs the plan's schedule (bricks if it is small and no
-// schedule was installed on it); a coarser level its tuned one, else the default
-// rule, or the plan's installed schedule shortened by level_cfg.
+// The finest level runs the plan's schedule (default, tuned or installed); a
+// coarser level its tuned or installed one, else the default rule.
 SmoothCfg level_schedule(const Plan* P, int l, const Geom& g) {
-    if (l == 0) return P->small_finest && !P->user_cfg ? SmoothCfg{8, 8, PIPE_BRICK} : P->cfg;
+    if (l == 0) return P->cfg;
     if ((int)P->lcfg.size() > l && P->lcfg[l].ty > 0) return P->lcfg[l];
-    if (P->user_cfg) return level_cfg(g.n0, g.n1, g.n2, P->cfg);
     return g.ncell <= BRICK_CELLS ? SmoothCfg{8, 8, PIPE_BRICK} : default_march(g.n0, g.n1, g.n2);
 }
 
@@ -1245,14 +1242,14 @@ vmg_status vmg_plan_set_schedule(vmg_plan* plan, int32_t level, int32_t tile_y, 
     if (pipe != 0 && pipe != 1 && pipe != PIPE_BRICK) return fail(VMG_EINVAL, "pipe must be 0, 1 or 2");
     if (level < 0 || level >= swept_level_count(P))
         return fail(VMG_EINVAL, "level " + std::to_string(level) + " has no fused sweep in this plan");
-    if (pipe == PIPE_BRICK && level == 0 && !P->batched)
-        return fail(VMG_EINVAL, "pipe 2 (bricks) runs on the coarser levels of a periodic plan or on any level of "
-                                "a Dirichlet batch");
+    // (on a small finest periodic level in the one form vmg_plan_schedule reports, so
+    // that a schedule read from a plan can be installed again)
+    if (pipe == PIPE_BRICK && level == 0 && !P->batched &&
+        !(finest_may_run_bricks(P) && tile_y == 8 && z_chunk == 8))
+        return fail(VMG_EINVAL, "pipe 2 (bricks) runs on the coarser levels of a periodic plan, on any level of "
+                                "a Dirichlet batch, and as 8, 8, 2 on a finest periodic level of at most 2^18 cells");
     const SmoothCfg c{tile_y, z_chunk, pipe};
-    if (level == 0) {
-        P->cfg = c;
-        P->user_cfg = true;
-    }
+    if (level == 0) P->cfg = c;
     if (P->batched) {
         CKH(batch_set_level_cfg(P, level, c));
     } else if (level > 0) {
@@ -1269,9 +1266,7 @@ vmg_status vmg_plan_schedule(const vmg_plan* plan, int32_t level, int32_t* tile_
     const Plan* P = reinterpret_cast<const Plan*>(plan);
     if (level < 0 || level >= swept_level_count(P))
         return fail(VMG_EINVAL, "level " + std::to_string(level) + " has no fused sweep in this plan");
-    // (the finest periodic level reports its march, the only schedule it accepts)
-    const SmoothCfg c = P->batched ? P->blev[level].cfg
-                                   : (level == 0 ? P->cfg : level_schedule(P, level, P->grids[0].lev[level].g));
+    const SmoothCfg c = P->batched ? P->blev[level].cfg : level_schedule(P, level, P->grids[0].lev[level].g);
     if (tile_y) *tile_y = c.ty;
     if (z_chunk) *z_chunk = c.zc;
     if (pipe) *pipe = c.pipe;

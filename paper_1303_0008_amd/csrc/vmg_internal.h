@@ -80,8 +80,8 @@ struct SmoothCfg {
     int pipe = 1;   // 0: black one plane behind red, two barriers per plane step;
                     // 1: black two planes behind, one barrier (four-plane rings);
                     // PIPE_BRICK: no z march, BB_SIDE^3 bricks (ty, zc unused): up
-                    // to two sweeps per launch on periodic levels below the finest,
-                    // one on any level of a Dirichlet batch
+                    // to two sweeps per launch on periodic levels, one on any level
+                    // of a Dirichlet batch
 };
 constexpr int PIPE_BRICK = 2;
 constexpr int BB_SIDE = 8;   // brick side of PIPE_BRICK
@@ -99,20 +99,7 @@ inline int level_zc(int64_t xy_tiles, int n2, int zc0 = 16) {
     return zc;
 }
 
-// Fused-sweep schedule of one level: the plan's (tuned) schedule, with the
-// z chunk shortened and then the tile height lowered to 4 on small grids.
-inline SmoothCfg level_cfg(int n0, int n1, int n2, SmoothCfg c) {
-    const int64_t tx = (n0 + 63) / 64;
-    auto blocks = [&](int ty, int zc) { return tx * ((n1 + ty - 1) / ty) * ((n2 + zc - 1) / zc); };
-    c.zc = level_zc(tx * ((n1 + c.ty - 1) / c.ty), n2, c.zc);
-    if (blocks(c.ty, c.zc) < MIN_TILED_BLOCKS && c.ty > 4) {
-        c.ty = 4;
-        c.zc = level_zc(tx * ((n1 + 3) / 4), n2, c.zc);
-    }
-    return c;
-}
-
-// Schedules of plans that neither tuned nor installed one.  Timed as whole
+// Schedules of levels for which none was tuned or installed.  Timed as whole
 // V(2,2) cycles over 32^3..384^3 cubes and ragged grids, both precisions:
 // * periodic levels of at most BRICK_CELLS cells run bricks, the finest one
 //   included: the march's pipeline fill dominates there (FP64 cycle of a 32^3 /

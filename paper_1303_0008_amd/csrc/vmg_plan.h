@@ -84,10 +84,7 @@ struct Plan {
     hipStream_t stream = nullptr;
     hipStream_t own_stream = nullptr;      // created when the caller passes stream 0
     SmoothCfg cfg;                         // finest-level schedule of the fused sweep
-    bool user_cfg = false;                 // cfg was installed by vmg_plan_set_schedule
-    bool small_finest = false;             // periodic finest level of <= BRICK_CELLS cells: runs bricks
-                                           // unless a schedule was installed on it
-    std::vector<SmoothCfg> lcfg;           // tuned schedules of levels >= 1 (empty: level_schedule's rule)
+    std::vector<SmoothCfg> lcfg;           // tuned or installed ones of levels >= 1 (empty: level_schedule's rule)
     int nu1 = 2, nu2 = 2, ncoarse = 40;
     int inner = 2;                         // mixed: FP32 inner V-cycles per outer iteration
     int nu1c = 0, nu2c = 0;                // sweeps below the finest level (0, 0: nu1, nu2)
@@ -198,6 +195,10 @@ hipError_t settle_cbar(Plan* P, LevelBuf& L, LevelScalars* sc);
 // whether level l runs its cycle's head in one launch (head.h)
 inline bool one_launch_head(const GridState& G, int l) {
     return l + 1 < (int)G.lev.size() && !G.lev[l].g.dir && G.lev[l].g.ncell <= HEAD_CELLS;
+}
+// whether bricks may run on the finest level of a periodic plan: their default there
+inline bool finest_may_run_bricks(const Plan* P) {
+    return P->periodic && P->grids[0].lev.size() > 1 && P->grids[0].lev[0].g.ncell <= BRICK_CELLS;
 }
 // schedule of the fused sweep on level l of a single-grid (periodic) plan
 SmoothCfg level_schedule(const Plan* P, int l, const Geom& g);
