@@ -60,16 +60,21 @@ hipError_t batch_set_level_cfg(Plan* P, int l, SmoothCfg cfg) {
     return upload(P, &B.d_sitems, items);
 }
 
-// Default schedules: bricks on the levels below the finest (they also refresh the
-// ghosts, a launch less per sweep) and on a finest level of few cells in all;
-// else marches of the finest level whose z chunk leaves enough work items.
-// V(2,2) cycles timed over batches of 1 to 128 grids of 16^3 to 128^3: mixed,
-// 8 x 32^3 / 48 ragged (1.6 M cells) / 96 of 16^3-64^3 (3.3 M): 506 / 1080 /
-// 1789 us so, 734 / 1245 / 2083 us with 64 x 8 x 16 tiles shortened on coarse
-// levels; FP64 267 / 589 / 986 us against 358 / 640 / 1062 us.  Bricks on the
-// finest level of the last two take 1240 and 2490 us (FP64 651 and 1192 us): the
-// rings' recomputation outweighs the march's fill once the chip is full.
+// Default schedules: bricks on levels of few cells in all, where the march's fill
+// dominates (below the finest level they also refresh the ghosts, a launch less per
+// sweep, and so pay up to twice the cells); else marches whose z chunk leaves enough
+// work items.  V(2,2) cycles timed over batches of 1 to 128 grids of 16^3 to 512^3:
+// * finest level, mixed, 8 x 32^3 (0.26 M cells) / 48 ragged (1.6 M) / 96 of
+//   16^3-64^3 (3.3 M): 506 / 1080 / 1789 us so, 734 / 1245 / 2083 us with 64 x 8 x 16
+//   tiles shortened on coarse levels; FP64 267 / 589 / 986 against 358 / 640 / 1062.
+//   Bricks on the finest level of the last two take 1240 and 2490 us (FP64 651 and
+//   1192): the rings' recomputation outweighs the march's fill once the chip is full;
+// * level 1 likewise, bricks against this march, FP64 (mixed): 0.26 M cells (one
+//   128^3 grid) 393 : 434 us (694 : 793), 0.8 M (24 x 64^3) 601 : 600 (1102 : 1104),
+//   2.1 M (one 256^3) 1600 : 1523 (2835 : 2620), 6.3 M (24 x 128^3) 3949 : 3576
+//   (6966 : 6085), 16.8 M (one 512^3) 11401 : 10482 (19125 : 16843).
 constexpr int64_t BATCH_BRICK_CELLS = (int64_t)1 << 19;
+constexpr int64_t BATCH_BRICK_CELLS_COARSE = (int64_t)1 << 20;
 hipError_t batch_build_smooth_items(Plan* P) {
     for (size_t l = 0; l < P->blev.size(); ++l) {
         const BatchLevel& B = P->blev[l];
@@ -83,7 +88,7 @@ hipError_t batch_build_smooth_items(Plan* P) {
             return n;
         };
         SmoothCfg cfg{8, 8, PIPE_BRICK};
-        if (l == 0 && B.cells_A > BATCH_BRICK_CELLS) {
+        if (B.cells_A > (l == 0 ? BATCH_BRICK_CELLS : BATCH_BRICK_CELLS_COARSE)) {
             if (P->mixed) cfg = SmoothCfg{16, count(SmoothCfg{16, 16, 1}) >= 1024 ? 16 : 8, 1};
             else if (count(SmoothCfg{16, 16, 1}) >= 1024) cfg = SmoothCfg{16, 16, 1};
             else cfg = SmoothCfg{8, count(SmoothCfg{8, 16, 1}) >= 512 ? 16 : 8, 1};
