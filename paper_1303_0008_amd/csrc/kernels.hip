@@ -973,7 +973,8 @@ __device__ __forceinline__ double parent_trilinear(const double* __restrict__ pa
 
 // Ghost shells (compact order) and interiors (x fastest) of many refinements,
 // interpolated from their parents in one launch: block b takes FILL_CELLS
-// consecutive values of the fill f.d[q] with f.first[q] <= b < f.first[q + 1].
+// consecutive values of the fill f.d[q] with f.first[q] <= b < f.first[q + 1] (and,
+// of a fill of more values than a launch has room for, every so many again).
 // A refinement's fill alone is one to a few dozen blocks, so a launch per
 // refinement and kind leaves the chip idle and costs the launch (5-6 us each);
 // together they stream.  96 patches of 16^3-64^3 under a 256^3 parent, ghosts
@@ -986,26 +987,27 @@ __global__ void __launch_bounds__(NT) k_parent_fills(ParentFills f) {
         if (q + step < f.n && (int)blockIdx.x >= f.first[q + step]) q += step;
     const ParentFill& d = f.d[q];
     const double* __restrict__ parent = d.parent;
-    const int64_t e0 = (int64_t)((int)blockIdx.x - f.first[q]) * FILL_CELLS;
+    const int64_t step = (int64_t)(f.first[q + 1] - f.first[q]) * FILL_CELLS;
+    for (int64_t e0 = (int64_t)((int)blockIdx.x - f.first[q]) * FILL_CELLS; e0 < d.count; e0 += step)
 #pragma unroll
-    for (int m = 0; m < FILL_CELLS / NT; ++m) {
-        const int64_t e = e0 + m * NT + threadIdx.x;
-        if (e >= d.count) break;
-        int c[3];
-        if (d.ghosts) {
-            ghost_coords(d.n[0], d.n[1], d.n[2], e, c[0], c[1], c[2]);
-        } else if (d.count <= 0x7fffffff) {
-            const unsigned u = (unsigned)e, r = u / (unsigned)d.n[0];
-            c[0] = (int)(u - r * (unsigned)d.n[0]);
-            c[2] = (int)(r / (unsigned)d.n[1]);
-            c[1] = (int)(r - (unsigned)c[2] * (unsigned)d.n[1]);
-        } else {
-            c[0] = (int)(e % d.n[0]);
-            c[1] = (int)((e / d.n[0]) % d.n[1]);
-            c[2] = (int)(e / ((int64_t)d.n[0] * d.n[1]));
+        for (int m = 0; m < FILL_CELLS / NT; ++m) {
+            const int64_t e = e0 + m * NT + threadIdx.x;
+            if (e >= d.count) break;
+            int c[3];
+            if (d.ghosts) {
+                ghost_coords(d.n[0], d.n[1], d.n[2], e, c[0], c[1], c[2]);
+            } else if (d.count <= 0x7fffffff) {
+                const unsigned u = (unsigned)e, r = u / (unsigned)d.n[0];
+                c[0] = (int)(u - r * (unsigned)d.n[0]);
+                c[2] = (int)(r / (unsigned)d.n[1]);
+                c[1] = (int)(r - (unsigned)c[2] * (unsigned)d.n[1]);
+            } else {
+                c[0] = (int)(e % d.n[0]);
+                c[1] = (int)((e / d.n[0]) % d.n[1]);
+                c[2] = (int)(e / ((int64_t)d.n[0] * d.n[1]));
+            }
+            d.out[e] = parent_trilinear(parent, d.np, d.H, d.h, d.o, c);
         }
-        d.out[e] = parent_trilinear(parent, d.np, d.H, d.h, d.o, c);
-    }
 }
 
 __global__ void k_gauge(Geom g, double* phi, const NormOut* no) {
@@ -1513,9 +1515,10 @@ hipError_t fills_launch(ParentFills& f, hipStream_t s) {
 hipError_t fills_add(ParentFills& f, const ParentFill& fill, hipStream_t s) {
     ParentFill d = fill;
     d.count = d.ghosts ? ghost_count(d.n[0], d.n[1], d.n[2]) : (int64_t)d.n[0] * d.n[1] * d.n[2];
-    const int64_t nb = (d.count + FILL_CELLS - 1) / FILL_CELLS;
-    if (nb > INT32_MAX) return hipErrorInvalidValue;
-    if (f.n == FILL_MAX || (f.n > 0 && nb > INT32_MAX - f.first[f.n])) {
+    // a launch holds fewer than 2^32 threads
+    constexpr int64_t most = (((int64_t)1 << 32) - 1) / NT;
+    const int64_t nb = std::min((d.count + FILL_CELLS - 1) / FILL_CELLS, most);
+    if (f.n == FILL_MAX || (f.n > 0 && nb > most - f.first[f.n])) {
         const hipError_t e = fills_launch(f, s);
         if (e != hipSuccess) return e;
     }
