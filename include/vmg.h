@@ -277,9 +277,9 @@ vmg_status vmg_total_force(const double *phi_newton, const double *phi, const in
  * particles.  The previous contents of delta are ignored.
  * workspace: device memory of at least vmg_mass_assign_workspace(n_particles,
  * n) bytes, 256-byte aligned, owned by the caller, contents ignored (it holds
- * the particles binned by brick of the grid and each brick's boundary sums); calls that share a workspace
- * must be ordered on one stream.  Enqueued on `stream`; the caller owns every
- * buffer.  Errors: VMG_EINVAL (null pointer, n_particles outside
+ * the particles binned by brick of the grid and each brick's boundary sums);
+ * calls that share a workspace must be ordered on one stream.  Enqueued on
+ * `stream`; the caller owns every buffer.  Errors: VMG_EINVAL (null pointer, n_particles outside
  * [1, 2^31 - 1], n < 1, n[1] or n[2] above 65535, unknown scheme, workspace
  * too small or misaligned), VMG_EHIP. */
 #define VMG_ASSIGN_CIC 1

@@ -978,7 +978,8 @@ __device__ __forceinline__ double parent_trilinear(const double* __restrict__ pa
 // A refinement's fill alone is one to a few dozen blocks, so a launch per
 // refinement and kind leaves the chip idle and costs the launch (5-6 us each);
 // together they stream.  96 patches of 16^3-64^3 under a 256^3 parent, ghosts
-// and interiors: 1169 us with a launch each, 96 us so (kernels 61 us, host 35).
+// and interiors: 1169 us with a launch each, 96 us so (kernels 61 us, host 35);
+// the first call on a new parent and new buffers some 1200 and 215 us.
 constexpr int FILL_CELLS = 4 * NT;
 __global__ void __launch_bounds__(NT) k_parent_fills(ParentFills f) {
     int q = 0;   // (uniform: scalar loads of the argument table)
@@ -1537,7 +1538,10 @@ hipError_t fills_add(ParentFills& f, const ParentFill& fill, hipStream_t s) {
 // (kept in a register) and the next plane's tile.  Bound by the bytes it moves
 // (48 per cell).  Outputs that fill the 256 MB last-level cache (2^23 cells) are
 // stored past the caches, which keeps the rings that neighbouring tiles share in
-// them: 256^3 cells 168 -> 157 us (5.1 TB/s), 208^3 114 -> 109 us.  Smaller outputs
+// them, and inputs that are there already: 256^3 cells 145 -> 137 us a call on the
+// same inputs again and again, 144 -> 140 us (5.8 TB/s) on six sets in turn; 208^3
+// 105 -> 94 and 104 -> 101 us, 320^3 275 -> 266 and 278 -> 269 us.  (On a card with
+// slower memory 169 -> 162 us and, on inputs not cached, no gain.)  Smaller outputs
 // (160^3: 46 us either way, and cached for whoever reads them next) and rows that
 // are not whole 128-byte lines (397 x 317 x 251: 427 us, 457 us streamed, for the
 // lines that two tiles share) keep ordinary stores.

@@ -850,8 +850,9 @@ hipError_t launch_mass_assign(const double* pos, int64_t np, int n0, int n1, int
                            listed, idx);
     else
         hipLaunchKernelGGL((k_bin<1, true>), dim3(chunks), dim3(NT), 0, s, g, pos, np, cursor, keys, idx);
-    // workgroups per brick: up to four per CU, each with at least 2048 particles of a
-    // brick of average content (4.3 M particles in random order onto 32 x 131 x 28
+    // workgroups per brick: doubled while there are fewer than four per CU (so fewer
+    // than eight in the end) and each keeps at least 2048 particles of a brick of
+    // average content (4.3 M particles in random order onto 32 x 131 x 28
     // cells, CIC: 172 us a call, 457 us with one workgroup per 16^3 brick; the 400
     // bricks above with ordered particles: 149 us, 222 us with one workgroup each)
     const double content = mean_count * (double)n0 * n1 * n2 / (double)nb;

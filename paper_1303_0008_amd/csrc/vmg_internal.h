@@ -269,7 +269,7 @@ struct ParentFill {
     int64_t count;           // values written (set by fills_add)
 };
 // The fills of one launch travel as its arguments (no device table to keep or
-// to wait for); 40 of them fill the 4 KB of a kernel's argument segment.
+// to wait for): 40 of them take 3.4 of the 4 KB of a kernel's argument segment.
 constexpr int FILL_MAX = 40;
 struct ParentFills {
     int n = 0;
