@@ -397,6 +397,7 @@ vmg_status vmg_plan_stats(const vmg_plan *plan, int64_t *cell_updates, int64_t *
  * every level of a Dirichlet batch, at plan creation, and installs a
  * cached cycle schedule of vmg_plan_tune_cycle; Sec. V of the paper notes the
  * code needed more tuning), pre/post sweeps and coarsest-level sweeps.
+ * Where the finest level runs bricks its tile height and z chunk read 8 and 8.
  * Errors: VMG_EINVAL. */
 vmg_status vmg_plan_config(const vmg_plan *plan, int32_t *tile_y, int32_t *z_chunk, int32_t *nu1,
                            int32_t *nu2, int32_t *coarse_sweeps);
